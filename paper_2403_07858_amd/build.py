@@ -17,6 +17,7 @@ PEAKS_SOURCES = ["bc_peaks.hip"]
 # Packed FP32 instructions are disabled for all device code.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-fconstexpr-steps=16777216",   # the kernels' tuple tables
              "-Wall", "-Wno-unused-function"]
 
 

@@ -39,6 +39,12 @@ struct Job {
     // bicliques each vertex is an L member of; NULL when not asked for (only
     // the global-set path fills them)
     uint64_t *pv;
+    // the leaf tables of searches with 1 .. kColFixed vertices of side B fixed:
+    // C(n, qA - 1), C(n, qA - 2), .., and where they pass the limits above
+    struct {
+        const u128 *binom;
+        uint32_t n_ovf, n_u64, n_u58, n_u28;
+    } less[3];
 };
 
 // One root of the global-set path (set intersections over the graph's own
@@ -83,6 +89,19 @@ struct ActiveRoot {
     uint32_t n_tasks;       // candidates that start a task: k - (pA - 2)
 };
 
+// One root of the column search, in schedule order: its candidate rows
+// transposed (one bitmap over the candidates per neighbour of the root), and
+// either one unit that counts the whole root or one unit per neighbour.
+struct ColRoot {
+    uint64_t col_off;       // word w of column c is cols[col_off + w * du + c]
+    uint64_t pool_off;      // its candidate rows in the pool
+    uint64_t unit_begin;    // global index of its first unit
+    uint32_t job;
+    uint32_t k, du, wk;     // candidates, neighbours (columns), words per column
+    uint32_t n_units;       // 1 (whole root) or du - (qA - 1): columns du - 1, du - 2, ...
+    uint32_t whole;
+};
+
 // Result slot: exact 128-bit count as two 64-bit limbs plus status flags.
 struct Slot {
     unsigned long long lo, hi;
@@ -107,10 +126,31 @@ constexpr int kWaveSize = 64;
 constexpr int kWavesPerBlock = 4;
 constexpr uint32_t kTripleRows = 96;   // nodes up to this many rows finish their last three levels at once
 constexpr int kBlockThreads = kWaveSize * kWavesPerBlock;
+constexpr uint32_t kColMax = 128;      // widest column search, in columns: lanes hold pairs,
+constexpr uint32_t kColTripleMax = 64; // triples,
+constexpr uint32_t kColQuadMax = 40;   // tuples of four,
+constexpr uint32_t kColQuintMax = 28;  // or of five
+constexpr uint32_t kColWords = 40;     // longest column searched, in 64-bit words
+constexpr uint32_t kColBuf = 960;      // LDS words for a wave's columns
+constexpr uint32_t kColMinQ = 2, kColMaxQ = 6;   // columns chosen
+constexpr uint32_t kColMinP = 2, kColMaxP = 5;   // rows chosen
+constexpr uint32_t kColRootWords = 64;     // longest column of a root searched unit by unit
+constexpr uint32_t kColRootPlanes = 16;    // and its widest row, in 64-bit words
+constexpr uint32_t kColFixed = 3;          // most columns fixed in a unit
+constexpr uint32_t kColLessLen = 64 * kColRootPlanes + 1;   // entries of a unit's leaf table, if so many
+constexpr uint32_t kNoJ = 0xffffffffu;     // no restriction to one child
 constexpr int kSortCap = 4096;          // candidates sorted in LDS up to this many
 constexpr int kRbWaves = 16;            // waves per block of the fused per-root kernel
 constexpr int kRbThreads = kWaveSize * kRbWaves;
 constexpr uint32_t kSlotFlag = 0x80000000u;
+
+// What the candidate pass finds of one root.
+struct RootOut {
+    uint64_t off;           // first word of its rows in the pool (~0: no rows)
+    uint32_t k;             // candidates
+    uint32_t bits;          // set bits of their rows (2^32 - 1 and more count as that; 0 from k_cand_count,
+                            // and for roots of at most kColTripleMax neighbours)
+};
 
 struct RootScratch {
     uint32_t *cnt;          // per block: nA_max counters, all zero between roots
@@ -119,12 +159,42 @@ struct RootScratch {
     uint64_t stride;        // elements per block in each array
 };
 
+struct ColParams {
+    const Job *jobs;
+    const ColRoot *roots;
+    uint32_t n_roots;
+    uint32_t n_whole;       // roots [0, n_whole) are one unit each, taken one by one
+    uint32_t unit_chunk;    // consecutive units of the other roots taken per queue pop
+    uint32_t instrument;
+    uint64_t n_units;       // units of roots [n_whole, n_roots), or room in `units`
+    const uint64_t *pool;   // candidate rows
+    uint64_t *cols;         // candidate columns (k_transpose writes, k_columns reads)
+    unsigned long long *queue;
+    uint64_t *slab;         // per-wave columns that exceed the LDS (NULL: none may)
+    // listed units are {root, col_pack of the fixed columns}
+    const uint2 *units;     // the units of a later run (NULL: those of the roots)
+    const unsigned long long *n_listed;   // and their number
+    uint2 *split;           // units split by a further column (NULL: none are)
+    unsigned long long *n_split;
+    uint64_t split_cap;     // room in split
+    uint4 *left;            // units that the row search takes: the same, and one child row or kNoJ
+    unsigned long long *n_left;
+    uint64_t left_cap;      // room in left: every unit fits, and a heavy one's children if they do
+    Slot *slots;
+};
+
 struct EnumParams {
     const Job *jobs;
     const ActiveRoot *roots;
     uint32_t n_roots;
     uint32_t task_chunk;    // consecutive tasks taken per queue pop (>= 1)
     uint64_t n_tasks;
+    // the column search's roots and the units that it left to the row search
+    // (the instances with COLS): tasks are left[0 .. *n_left)
+    const ColRoot *col_roots;
+    const uint4 *left;
+    const unsigned long long *n_left;
+    const uint64_t *cols;
     const uint64_t *pool;
     uint64_t *slab;         // per-wave global scratch
     uint64_t slab_words;    // words per wave
@@ -152,20 +222,24 @@ hipError_t launch_degree_sum(const Job *jobs, const uint32_t *job_ids, uint32_t 
                              Slot *slots, hipStream_t stream);
 hipError_t launch_cand_count(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
                              uint64_t total_roots, RootScratch scratch, uint32_t n_blocks,
-                             unsigned long long *queue, uint32_t *out_k, Slot *slots,
-                             hipStream_t stream);
-// Candidate counts and rows in one kernel; rows go to pool[out_off[r] ..]
-// (bump-allocated from counters[1], capacity pool_cap words; out_off = ~0 when
-// a root has no rows).  counters[0] is the root queue.  Blocks of kRbThreads
+                             unsigned long long *queue, RootOut *out, Slot *slots, hipStream_t stream);
+// Candidate counts and rows in one kernel; rows go to pool[out[r].off ..]
+// (bump-allocated from counters[1], capacity pool_cap words).  counters[0] is
+// the root queue.  Blocks of kRbThreads
 // threads with 144 KiB of LDS each.
 hipError_t launch_root_build(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
                              uint64_t total_roots, RootScratch scratch, uint64_t *pool, uint64_t pool_cap,
-                             uint32_t n_blocks, unsigned long long *counters, uint32_t *out_k, uint64_t *out_off,
-                             Slot *slots, bool per_vertex, hipStream_t stream);
+                             uint32_t n_blocks, unsigned long long *counters, RootOut *out, Slot *slots,
+                             bool per_vertex, hipStream_t stream);
 hipError_t launch_rows_build(const Job *jobs, const ActiveRoot *roots, uint32_t n_roots,
                              uint64_t *pool, RootScratch scratch, uint32_t n_blocks,
                              unsigned long long *queue, Slot *slots, hipStream_t stream);
 hipError_t launch_enumerate(const EnumParams &prm, uint32_t n_blocks, hipStream_t stream);
+// The column search: k_transpose writes the columns of n_roots roots, k_columns
+// counts their units and lists those that the row search has to take.
+hipError_t launch_columns(const ColParams &prm, uint32_t n_blocks, hipStream_t stream);
+// The row search over the units listed by k_columns.
+hipError_t launch_enumerate_left(const EnumParams &prm, uint32_t n_blocks, hipStream_t stream);
 // Candidate ids of the global-set roots: for root r, the w > u sharing >= qA
 // neighbours with u, in no particular order, written to ids[roots[r].id_off ..].
 hipError_t launch_cand_ids(const Job *jobs, const SetRoot *roots, uint32_t n_roots, uint32_t *ids,
@@ -174,6 +248,106 @@ hipError_t launch_cand_ids(const Job *jobs, const SetRoot *roots, uint32_t n_roo
 hipError_t launch_enumerate_sets(const SetParams &prm, uint32_t n_blocks, hipStream_t stream);
 
 uint32_t max_lds_words_per_wave();
+
+// The columns fixed in a unit, the last of its subsets first: ten bits each,
+// all ones for none.
+constexpr uint32_t kColNone = 1023;
+static_assert(64 * kColRootPlanes <= kColNone + 1, "columns are numbered below kColNone");
+__host__ __device__ constexpr uint32_t col_pack(uint32_t x, uint32_t y, uint32_t z) { return x | (y << 10) | (z << 20); }
+__host__ __device__ constexpr uint32_t col_fixed(uint32_t pack, uint32_t i) { return (pack >> (10 * i)) & kColNone; }
+
+// The column search chooses q of s columns of nw words.  It searches
+// col_words words of them, kept col_stride words apart (two words more, so
+// that the lanes' reads of different columns fall on different LDS banks, 20
+// banks apart at eight words, and an even number for 16-byte reads), in LDS or,
+// past kColBuf words, in the wave's slab (16 words and more only).
+// col_loops of the q columns run through loops, each of which keeps one more
+// AND in registers (hence fewer for long columns); the lanes hold tuples of
+// the rest.
+__host__ __device__ constexpr uint32_t col_stride(uint32_t nc) { return nc + 2; }
+__host__ __device__ constexpr uint32_t col_words(uint32_t nw, uint32_t s)
+{
+    const uint32_t nc = nw <= 8 ? (nw + 1) & ~1u : nw <= 12 ? 12u : nw <= 16 ? 16u : nw <= 24 ? 24u : 40u;
+    return nc < 16 && s * col_stride(nc) > kColBuf ? 16u : nc;
+}
+__host__ __device__ constexpr uint32_t col_loops(uint32_t q, uint32_t nc, uint32_t s)
+{
+    const uint32_t want = s > kColTripleMax ? (q > 2 ? q - 2 : 1) : q <= 4 ? 1 : q - 3;
+    const uint32_t most = nc <= 8 ? 3 : nc <= 16 ? 2 : 1;
+    return want < most ? want : most;
+}
+constexpr uint64_t kColSlabWords = (uint64_t)kColMax * (kColWords + 2);   // per wave
+
+// Whether it can: q columns, room, tuple tables.
+__host__ __device__ constexpr bool col_fits(uint32_t s, uint32_t nw, uint32_t q, bool slab)
+{
+    if (q < kColMinQ || q > kColMaxQ || s > kColMax || nw > kColWords) return false;
+    const uint32_t nc = col_words(nw, s), R = q - col_loops(q, nc, s);
+    return s <= (R <= 2 ? kColMax : R == 3 ? kColTripleMax : R == 4 ? kColQuadMax : kColQuintMax) &&
+           (slab || s * col_stride(nc) <= kColBuf);
+}
+
+__host__ __device__ constexpr uint64_t choose(uint64_t n, uint32_t k)
+{
+    if (n < k) return 0;
+    uint64_t c = 1;
+    for (uint32_t i = 0; i < k; ++i) c = c * (n - i) / (i + 1);
+    return c;
+}
+
+// Steps of the search with D loops: lane tuples, steps of the innermost loop
+// and of the loops around it.  The lanes take the tuples of R = q - D columns
+// that leave D behind them, 64 a round in colexicographic order (so that the
+// tuples with a last column below x are the first choose(x, R)), and a round's
+// loops start behind its first tuple's last column.
+struct ColCost {
+    uint32_t tuples, leaf, outer;
+};
+struct ColCosts {
+    ColCost at[kColMaxQ - kColMinQ + 1][3][kColMax + 1];
+    __host__ __device__ constexpr const ColCost &of(uint32_t q, uint32_t D, uint32_t s) const
+    {
+        return at[q - kColMinQ][D - 1][s];
+    }
+};
+constexpr ColCosts make_col_costs()
+{
+    ColCosts t{};
+    for (uint32_t q = kColMinQ; q <= kColMaxQ; ++q)
+        for (uint32_t D = 1; D <= 3 && D < q; ++D)
+            for (uint32_t s = q; s <= kColMax; ++s) {
+                const uint32_t R = q - D;
+                uint64_t leaf = 0, outer = 0, base = 0;
+                for (uint32_t last = R - 1; last + D < s; ++last) {
+                    const uint64_t n = s - 1 - last, end = choose(last + 1, R);
+                    const uint64_t rounds = base < end ? (end - base + kWaveSize - 1) / kWaveSize : 0;
+                    base += rounds * kWaveSize;
+                    leaf += rounds * choose(n, D);
+                    for (uint32_t d = 1; d < D; ++d) outer += rounds * choose(n, d);
+                }
+                ColCost &c = t.at[q - kColMinQ][D - 1][s];
+                c.tuples = (uint32_t)choose(s - D, R);   // below 2^32 wherever col_fits
+                c.leaf = leaf < 0xffffffffu ? (uint32_t)leaf : 0xffffffffu;
+                c.outer = outer < 0xffffffffu ? (uint32_t)outer : 0xffffffffu;
+            }
+    return t;
+}
+
+// Estimated wave instructions of the search with tuples of R columns of nc words.
+__host__ __device__ constexpr uint64_t col_estimate(const ColCost &c, uint64_t nc, uint32_t R)
+{
+    return c.leaf * (4 * nc + 8) + c.outer * (6 * nc + 8) + (c.tuples + 63) / 64 * (2 * R * nc + 40) + 100;
+}
+
+// Estimated wave instructions of the row search over m rows choosing p: one
+// 16 x 16 product of pair sizes with its table reads costs about as much as
+// 30 VALU instructions; below the pairs of the last list its nodes' own work
+// dominates (measured at p = 4: six times the products).
+__host__ __device__ constexpr uint64_t row_estimate(uint64_t m, uint32_t p)
+{
+    return p <= 1 ? m / 4 + 40 : p == 2 ? m * m / 17 + 60 : p == 3 ? m * m * m / 42 + 100
+         : p == 4 ? m * m * m * m / 43 + 100 : m * m * m * m * m / 100 + 100;
+}
 
 // Reads the device real-time clock (s_memrealtime) into *out (device memory).
 hipError_t launch_read_clock(uint64_t *out, hipStream_t stream);

@@ -4,6 +4,7 @@
 #include "bc.h"
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstddef>
 #include <chrono>
@@ -793,15 +794,26 @@ bc_status device_clock(int device, hipStream_t st, DevAlloc &mem, ClockCal &out)
     return BC_OK;
 }
 
-// C(n, q) for n in [0, nmax] as exact u128; n_ovf = first n that overflows.
-void binom_column(uint32_t nmax, uint32_t q, std::vector<u128> &col, uint32_t &n_ovf, uint32_t &n_u64,
-                  uint32_t &n_u58, uint32_t &n_u28)
+// One column of binomials: C(n, q) for n = 0, 1, .. as exact u128, and where
+// it passes the limits the kernels switch at.
+struct Binomials {
+    std::vector<u128> col;
+    uint32_t n_ovf = 0;   // first n whose entry overflows 128 bits (the length if none)
+    uint32_t n_u64 = 0, n_u58 = 0, n_u28 = 0;   // last n whose entry is below 2^64, 2^58, 2^28
+};
+
+// Columns q, q - 1, .., q - n_less: the first for n <= nmax, the others for at
+// most less_len entries, from one pass over Pascal's rows.
+void binomial_columns(uint32_t nmax, uint32_t q, uint32_t n_less, uint32_t less_len, Binomials *out)
 {
     std::vector<u128> c(q + 1, 0);
     std::vector<uint8_t> ov(q + 1, 0);
     c[0] = 1;
-    col.assign(nmax + 1, 0);
-    n_ovf = nmax + 1;
+    for (uint32_t x = 0; x <= n_less; ++x) {
+        const uint32_t len = x == 0 ? nmax + 1 : std::min(nmax + 1, less_len);
+        out[x].col.assign(len, 0);
+        out[x].n_ovf = len;
+    }
     for (uint32_t n = 0; n <= nmax; ++n) {
         if (n > 0) {
             for (uint32_t k = std::min(n, q); k >= 1; --k) {
@@ -811,12 +823,17 @@ void binom_column(uint32_t nmax, uint32_t q, std::vector<u128> &col, uint32_t &n
                 ov[k] = o;
             }
         }
-        if (ov[q] && n_ovf > nmax) n_ovf = n;
-        col[n] = ov[q] ? 0 : c[q];
-        // C(n, q) does not decrease with n, so the entries below 2^64 are a prefix
-        if (!ov[q] && (c[q] >> 64) == 0) n_u64 = n;
-        if (!ov[q] && (c[q] >> 58) == 0) n_u58 = n;
-        if (!ov[q] && (c[q] >> 28) == 0) n_u28 = n;
+        for (uint32_t x = 0; x <= n_less && n < out[x].col.size(); ++x) {
+            Binomials &b = out[x];
+            const u128 v = c[q - x];
+            const bool o = ov[q - x];
+            if (o && b.n_ovf == b.col.size()) b.n_ovf = n;
+            b.col[n] = o ? 0 : v;
+            // C(n, q) does not decrease with n, so the entries below 2^64 are a prefix
+            if (!o && (v >> 64) == 0) b.n_u64 = n;
+            if (!o && (v >> 58) == 0) b.n_u58 = n;
+            if (!o && (v >> 28) == 0) b.n_u28 = n;
+        }
     }
 }
 
@@ -926,6 +943,19 @@ std::vector<uint32_t> order_by_cost_desc(const std::vector<uint64_t> &cost)
     }
     return a;
 }
+
+// Whether the column search takes the roots of a (p_A, q_A) job: unit by unit
+// (choosing one column less) or whole.
+bool col_units_ok(uint32_t pA, uint32_t qA)
+{
+    return pA > bcdev::kColMinP && pA - 1 <= bcdev::kColMaxP && qA > bcdev::kColMinQ && qA - 1 <= bcdev::kColMaxQ;
+}
+bool col_whole_ok(uint32_t pA, uint32_t qA)
+{
+    return pA > bcdev::kColMinP && pA - 1 <= bcdev::kColMaxP && qA >= bcdev::kColMinQ && qA <= bcdev::kColMaxQ;
+}
+
+constexpr bcdev::ColCosts kColCosts = bcdev::make_col_costs();
 
 // Cost model of served deadlines: per enumeration depth p_A, the fewest
 // nanoseconds per unit of the whole-depth planning proxy (sum over a job's
@@ -1051,13 +1081,14 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     ClockCal clock;
     std::vector<bcdev::Job> hjobs(nj);
     std::vector<uint64_t> tab_off(nj + 1, 0);
-    std::vector<std::vector<u128>> cols(nj);
+    // C(n, qA), then C(n, qA - 1), .. for the column search
+    std::vector<std::array<Binomials, bcdev::kColFixed + 1>> cols(nj);
     for (uint32_t j = 0; j < nj; ++j) {
         const HostJob &hj = jobs[j];
         const bc_graph *g = specs[hj.spec].g;
         const Side &A = g->side[hj.anchor];
-        uint32_t n_ovf = 0, n_u64 = 0, n_u58 = 0, n_u28 = 0;
-        binom_column(A.max_deg, hj.qA, cols[j], n_ovf, n_u64, n_u58, n_u28);
+        const uint32_t n_less = col_units_ok(hj.pA, hj.qA) ? std::min(bcdev::kColFixed, hj.qA - 2) : 0;
+        binomial_columns(A.max_deg, hj.qA, n_less, bcdev::kColLessLen, cols[j].data());
         bcdev::Job &d = hjobs[j];
         memset(&d, 0, sizeof(d));
         d.ptrA = A.d_ptr;
@@ -1072,10 +1103,10 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         d.pA = hj.pA;
         d.qA = hj.qA;
         d.binom_n = A.max_deg + 1;
-        d.n_ovf = n_ovf;
-        d.n_u64 = n_u64;
-        d.n_u58 = n_u58;
-        d.n_u28 = n_u28;
+        d.n_ovf = cols[j][0].n_ovf;
+        d.n_u64 = cols[j][0].n_u64;
+        d.n_u58 = cols[j][0].n_u58;
+        d.n_u28 = cols[j][0].n_u28;
         d.slot = j;
         d.deadline = 0;
         const uint64_t dl = specs[hj.spec].deadline_ns;
@@ -1086,7 +1117,8 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             const double t = clock.offset + clock.ticks_per_ns * (double)dl;
             d.deadline = t < 1.0 ? 1ull : (uint64_t)t;
         }
-        tab_off[j + 1] = tab_off[j] + cols[j].size();
+        tab_off[j + 1] = tab_off[j];
+        for (const Binomials &bn : cols[j]) tab_off[j + 1] += bn.col.size();
     }
     // per-vertex counters (two 64-bit words per vertex of the anchor side)
     bool any_pv = false;
@@ -1106,19 +1138,33 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     BC_HIP(mem.get(&d_jobs, nj));
     BC_HIP(mem.get(&d_tab, tab_off[nj]));
     BC_HIP(mem.get(&d_slots, nj + 1));   // slot nj: sample jobs
-    BC_HIP(mem.get(&d_queue, 12));
+    BC_HIP(mem.get(&d_queue, 32));
     {
         std::vector<u128> tab(tab_off[nj]);
         for (uint32_t j = 0; j < nj; ++j) {
-            std::copy(cols[j].begin(), cols[j].end(), tab.begin() + tab_off[j]);
-            hjobs[j].binom = d_tab + tab_off[j];
+            uint64_t at = tab_off[j];
+            for (uint32_t x = 0; x <= bcdev::kColFixed; ++x) {
+                const Binomials &bn = cols[j][x];
+                std::copy(bn.col.begin(), bn.col.end(), tab.begin() + at);
+                if (x == 0) {
+                    hjobs[j].binom = d_tab + at;
+                } else {
+                    auto &l = hjobs[j].less[x - 1];
+                    l.binom = d_tab + at;
+                    l.n_ovf = bn.n_ovf;
+                    l.n_u64 = bn.n_u64;
+                    l.n_u58 = bn.n_u58;
+                    l.n_u28 = bn.n_u28;
+                }
+                at += bn.col.size();
+            }
         }
         BC_HIP(hipMemcpyAsync(d_tab, tab.data(), tab.size() * sizeof(u128), hipMemcpyHostToDevice, st));
         BC_HIP(hipMemcpyAsync(d_jobs, hjobs.data(), nj * sizeof(bcdev::Job), hipMemcpyHostToDevice, st));
         BC_HIP(hipStreamSynchronize(st));  // host vectors go out of scope
     }
     BC_HIP(bcdev::launch_fill_slots(d_slots, nj + 1, st));
-    BC_HIP(fill_u32((uint32_t *)d_queue, 24, 0u, st));
+    BC_HIP(fill_u32((uint32_t *)d_queue, 64, 0u, st));
 
     Timer tm(stats != nullptr && !ex.fixed);
     tm.mark(0, st);
@@ -1196,12 +1242,11 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         if (!sjobs.empty()) {
             const uint64_t s_roots = sprefix.back();
             bcdev::Job *d_sj;
-            uint64_t *d_sp, *d_soff, *d_spool;
-            uint32_t *d_sk;
+            uint64_t *d_sp, *d_spool;
+            bcdev::RootOut *d_sout;
             BC_HIP(mem.get(&d_sj, sjobs.size()));
             BC_HIP(mem.get(&d_sp, sprefix.size()));
-            BC_HIP(mem.get(&d_sk, s_roots));
-            BC_HIP(mem.get(&d_soff, s_roots));
+            BC_HIP(mem.get(&d_sout, s_roots));
             BC_HIP(mem.get(&d_spool, 1));
             BC_HIP(hipMemcpyAsync(d_sj, sjobs.data(), sjobs.size() * sizeof(bcdev::Job), hipMemcpyHostToDevice, st));
             BC_HIP(hipMemcpyAsync(d_sp, sprefix.data(), sprefix.size() * 8, hipMemcpyHostToDevice, st));
@@ -1209,9 +1254,9 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 std::min<uint64_t>(s_roots, rs_blocks),
                 std::max<uint64_t>(1, (uint64_t)ncu * std::min(waves_per_cu, 12u) / 12));
             BC_HIP(bcdev::launch_root_build(d_sj, d_sp, (uint32_t)sjobs.size(), s_roots, rs, d_spool, 1, s_blocks,
-                                            d_queue + 6, d_sk, d_soff, d_slots, false, st));
-            std::vector<uint32_t> sk(s_roots);
-            BC_HIP(hipMemcpyAsync(sk.data(), d_sk, s_roots * 4, hipMemcpyDeviceToHost, st));
+                                            d_queue + 6, d_sout, d_slots, false, st));
+            std::vector<bcdev::RootOut> sout(s_roots);
+            BC_HIP(hipMemcpyAsync(sout.data(), d_sout, s_roots * sizeof(bcdev::RootOut), hipMemcpyDeviceToHost, st));
             BC_HIP(hipStreamSynchronize(st));
             std::vector<double> est(nj, 0.0), seen(nj, 0.0);
             for (size_t s = 0; s < sjobs.size(); ++s) {
@@ -1219,7 +1264,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 const Side &A = specs[jobs[j].spec].g->side[jobs[j].anchor];
                 const uint32_t e = std::min<uint32_t>(jobs[j].pA - 1, 3);
                 for (uint64_t r = sprefix[s]; r < sprefix[s + 1]; ++r) {
-                    const double k = sk[r];
+                    const double k = sout[r].k;
                     const uint64_t u = sjobs[s].root_lo + (r - sprefix[s]);
                     seen[j] += 1.0;
                     if (k < jobs[j].pA - 1) continue;
@@ -1261,8 +1306,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         root_prefix.push_back(root_prefix.back() + (jobs[j].root_hi - jobs[j].root_lo));
     }
     const uint64_t total_roots = root_prefix.back();
-    std::vector<uint32_t> h_k(total_roots);
-    std::vector<uint64_t> h_off;
+    std::vector<bcdev::RootOut> found(total_roots);
     const uint32_t root_blocks =
         (uint32_t)std::min<uint64_t>(std::max<uint64_t>(total_roots, 1), std::max<uint32_t>(rs_blocks, 1));
     std::vector<bcdev::Job> cjobs;
@@ -1274,10 +1318,10 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         cjobs.reserve(cj.size());
         for (uint32_t j : cj) cjobs.push_back(hjobs[j]);
         uint64_t *d_rp;
-        uint32_t *d_k;
+        bcdev::RootOut *d_found;
         BC_HIP(mem.get(&d_cjobs, cjobs.size()));
         BC_HIP(mem.get(&d_rp, root_prefix.size()));
-        BC_HIP(mem.get(&d_k, total_roots));
+        BC_HIP(mem.get(&d_found, total_roots));
         BC_HIP(hipMemcpyAsync(d_cjobs, cjobs.data(), cjobs.size() * sizeof(bcdev::Job), hipMemcpyHostToDevice, st));
         BC_HIP(hipMemcpyAsync(d_rp, root_prefix.data(), root_prefix.size() * 8, hipMemcpyHostToDevice, st));
         if (fused) {
@@ -1289,8 +1333,6 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             // a fixed region gives the pool at most a third of what is left;
             // roots that find no room are rebuilt into an exactly sized pool
             if (ex.fixed || mem.cap) pool_cap = std::max<uint64_t>(1, std::min<uint64_t>(pool_cap, mem.room() / 3 / 8));
-            uint64_t *d_off;
-            BC_HIP(mem.get(&d_off, total_roots));
             BC_HIP(mem.get(&d_pool_fused, pool_cap));
             // one block of kRbThreads per CU (its LDS table takes most of the
             // CU's LDS); a reduced waves_per_cu takes the same share of CUs
@@ -1299,14 +1341,12 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 std::max<uint64_t>(1, (uint64_t)ncu * std::min(waves_per_cu, 12u) / 12));
             // per-vertex counts of p_A = 2 jobs are attributed by this pass
             BC_HIP(bcdev::launch_root_build(d_cjobs, d_rp, (uint32_t)cj.size(), total_roots, rs, d_pool_fused, pool_cap,
-                                            fused_blocks, d_queue + 4, d_k, d_off, d_slots, any_pv, st));
-            h_off.resize(total_roots);
-            BC_HIP(hipMemcpyAsync(h_off.data(), d_off, total_roots * 8, hipMemcpyDeviceToHost, st));
+                                            fused_blocks, d_queue + 4, d_found, d_slots, any_pv, st));
         } else {
             BC_HIP(bcdev::launch_cand_count(d_cjobs, d_rp, (uint32_t)cj.size(), total_roots, rs, root_blocks,
-                                            d_queue + 0, d_k, d_slots, st));
+                                            d_queue + 0, d_found, d_slots, st));
         }
-        BC_HIP(hipMemcpyAsync(h_k.data(), d_k, total_roots * 4, hipMemcpyDeviceToHost, st));
+        BC_HIP(hipMemcpyAsync(found.data(), d_found, total_roots * sizeof(bcdev::RootOut), hipMemcpyDeviceToHost, st));
     }
     tm.mark(1, st);
     BC_HIP(hipStreamSynchronize(st));
@@ -1321,7 +1361,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         uint64_t cost = 0, weight = 0;
         const uint32_t e = std::min<uint32_t>(hj.pA - 1, 3);
         for (uint64_t r = root_prefix[c]; r < root_prefix[c + 1]; ++r) {
-            uint64_t k = h_k[r];
+            uint64_t k = found[r].k;
             uint64_t u = hj.root_lo + (r - root_prefix[c]);
             uint64_t w1 = (A.h_ptr[u + 1] - A.h_ptr[u] + 63) / 64;
             uint64_t x = k * w1;
@@ -1376,15 +1416,15 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         const Side &A = specs[hj.spec].g->side[hj.anchor];
         const std::vector<uint8_t> *mask = specs[hj.spec].root_mask;
         for (uint64_t r = root_prefix[c]; r < root_prefix[c + 1]; ++r) {
-            cand_edges += h_k[r];
+            cand_edges += found[r].k;
             // per-vertex counts of p_A = 2 jobs: the fused candidate pass
             // attributes their leaves; the two-kernel pass does not, so then
             // their roots take the global-set path
-            if (hj.pA < (specs[hj.spec].pv_out && !fused ? 2u : 3u) || h_k[r] < hj.pA - 1) continue;
+            if (hj.pA < (specs[hj.spec].pv_out && !fused ? 2u : 3u) || found[r].k < hj.pA - 1) continue;
             uint32_t u = (uint32_t)(hj.root_lo + (r - root_prefix[c]));
             if (mask && !(*mask)[u]) continue;
             uint32_t w1 = (uint32_t)((A.h_ptr[u + 1] - A.h_ptr[u] + 63) / 64);
-            uint64_t k = h_k[r];
+            uint64_t k = found[r].k;
             uint64_t x = k * w1;
             const uint32_t e = std::min<uint32_t>(hj.pA - 1, 3);
             for (uint32_t t = 1; t < e; ++t) x = std::min<uint64_t>(x * k, 1ull << 62);
@@ -1464,35 +1504,156 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             set_slab_need = std::max<uint64_t>(set_slab_need, (uint64_t)pA * (mu + pl.k / 2 + 2) + 16);
         }
     }
-    std::vector<bcdev::ActiveRoot> aroots(plan.size());
-    uint64_t pool_words = 0, tasks = 0, slab_need = 64;
     // rows already built by the fused kernel, unless some root found no room
     bool rows_ready = fused;
     for (const Plan &pl : plan)
-        if (fused && h_off[pl.item] == ~0ull) rows_ready = false;
+        if (fused && found[pl.item].off == ~0ull) rows_ready = false;
+    // Which search a root takes, by its estimated wave instructions: by rows
+    // (a task per candidate, of which about a third keep enough common
+    // neighbours), by columns (a unit per neighbour: transposes of its share
+    // of the rows), or whole (one column search over all its neighbours).
+    // For p_A >= 4 the searches under the units cost about four times what
+    // their setup does (sampled on 0.3M - 2M edge power-law graphs at (4,4),
+    // (4,6), (6,4), (5,5) and (6,6); any factor from 2 to 8 is within 10 %),
+    // but with q_A well above p_A the subsets of a hub's neighbours outgrow
+    // its candidates' (at (4,6) columns are 2.1x the cheaper for 128 to 181
+    // neighbours and 1.5x the dearer for 181 to 256), as long as its rows are
+    // short enough for the matrix cores; for p_A = 3 the row search is one pair
+    // sum over the root's candidates.
+    enum : uint8_t { kByRows = 0, kByColumns = 1, kWhole = 2 };
+    const bool col_slab = !ex.fixed && !mem.cap;   // columns past the LDS: not with limited scratch
+    std::vector<uint8_t> mode(plan.size(), kByRows);
+    std::vector<uint64_t> whole_cost(plan.size(), 0);
+    uint64_t rows_spared = 0;
+    auto side_of = [&](const Plan &pl) -> const Side & { return specs[jobs[cj[pl.c]].spec].g->side[jobs[cj[pl.c]].anchor]; };
+    auto degree_of = [&](const Plan &pl) {
+        const Side &A = side_of(pl);
+        return (uint32_t)(A.h_ptr[pl.root + 1] - A.h_ptr[pl.root]);
+    };
     for (size_t r = 0; r < plan.size(); ++r) {
         const Plan &pl = plan[r];
-        const uint32_t pA = cjobs[pl.c].pA;
-        bcdev::ActiveRoot &a = aroots[r];
-        a.pool_off = rows_ready ? h_off[pl.item] : pool_words;
-        a.task_begin = tasks;
-        a.job = pl.c;
-        a.root = pl.root;
-        a.k = pl.k;
-        a.n_tasks = pl.k - (pA - 2);
-        pool_words += (uint64_t)pl.k * pl.w1;
-        tasks += a.n_tasks;
-        // per task: S2 and its prefix counts (2 W1), the compress table of
-        // S2's nonzero words (8 W1), the kept-row list of the level-2 filter
-        // (k / 2 + 1), then one block per DFS level 2 .. pA-2, each at most
-        // (k - 1) rows of at most W1 words
-        // (p_A >= 5: plus the pair rows of one small node's three-level sum,
-        // at most kTripleRows (kTripleRows - 1) / 2 rows of at most 4 words
-        // and their u32 indices)
-        const uint64_t pairs3 = (uint64_t)bcdev::kTripleRows * (bcdev::kTripleRows - 1) / 2;
-        uint64_t need = 10ull * pl.w1 + pl.k / 2 + 1 + (pA >= 5 ? pairs3 * 4 + (pairs3 + 1) / 2 : 0) +
-                        (pA >= 4 ? (uint64_t)(pA - 3) * (pl.k - 1) * pl.w1 : 0) + 8;
-        slab_need = std::max(slab_need, need);
+        const uint32_t pA = cjobs[pl.c].pA, q = cjobs[pl.c].qA, du = degree_of(pl), wk = (pl.k + 63) / 64;
+        const uint64_t k = pl.k, w1 = pl.w1;
+        const uint64_t rows = pA == 3 ? k * k * w1 / 34 + 100
+                                      : k * (250 + 6ull * wk * w1 + bcdev::row_estimate(k / 3, pA - 2));
+        const uint64_t units = du * (400 + 10ull * wk + 65 * w1 * std::max<uint64_t>(1, wk / 4));
+        if (col_units_ok(pA, q) && wk <= bcdev::kColRootWords && w1 <= bcdev::kColRootPlanes &&
+            units * (pA == 3 ? 1 : 4) < rows && (pA == 3 || q <= pA + 1 || du <= 192 || found[pl.item].bits > 100 * k))
+            mode[r] = kByColumns;
+        // a dense root (bits: set bits of its rows): nothing is pruned, so the
+        // searches cost what all its subsets do, of columns or of rows
+        if (mode[r] == kByColumns && du > bcdev::kColTripleMax && fused) {
+            const double fill = (double)found[pl.item].bits / ((double)k * du);
+            if (fill > 0.35) {
+                const double by_cols = (double)bcdev::choose(du, q) / 64 * (4.0 * fill * wk + 8);
+                const double by_rows = (double)k * (double)bcdev::row_estimate(2 * k / 3, pA == 3 ? 1 : pA - 2);
+                if (by_cols > 2.0 * by_rows) mode[r] = kByRows;
+            }
+        }
+        if (col_whole_ok(pA, q) && bcdev::col_fits(du, wk, q, col_slab)) {
+            const uint32_t nc = bcdev::col_words(wk, du), D = bcdev::col_loops(q, nc, du);
+            const uint64_t whole = bcdev::col_estimate(kColCosts.of(q, D, du), nc, q - D);
+            if (whole <= std::min(rows, units)) {
+                mode[r] = kWhole;
+                whole_cost[r] = whole;
+            }
+        }
+        if (mode[r] != kByRows) rows_spared += rows;
+    }
+    // The column search is up to five launches more: below about 0.3 ms of row
+    // search at the device's rate (6e8 wave instructions a millisecond) they
+    // cost what they spare (a 20k-edge count of 0.45 ms took 0.58 ms).
+    if (rows_spared < 200000000) std::fill(mode.begin(), mode.end(), (uint8_t)kByRows);
+    std::vector<bcdev::ActiveRoot> aroots(plan.size());
+    std::vector<bcdev::ColRoot> croots;
+    uint64_t pool_words = 0, tasks = 0, row_tasks = 0, col_words = 0, col_units = 0;
+    uint64_t slab_need = 64, left_slab_need = 64;   // words per wave: row search, its run over left units
+    uint32_t n_row_roots = 0, n_whole = 0;
+    auto lay_out = [&]() {
+        pool_words = tasks = row_tasks = col_words = col_units = 0;
+        slab_need = left_slab_need = 64;
+        n_row_roots = n_whole = 0;
+        croots.clear();
+        // active roots: by rows, then by columns, then whole ones, the longest first
+        std::vector<uint32_t> order, whole;
+        std::vector<uint64_t> wc;
+        order.reserve(plan.size());
+        for (size_t r = 0; r < plan.size(); ++r)
+            if (mode[r] == kByRows) order.push_back((uint32_t)r);
+        n_row_roots = (uint32_t)order.size();
+        for (size_t r = 0; r < plan.size(); ++r) {
+            if (mode[r] == kByColumns) order.push_back((uint32_t)r);
+            if (mode[r] == kWhole) {
+                whole.push_back((uint32_t)r);
+                wc.push_back(whole_cost[r]);
+            }
+        }
+        n_whole = (uint32_t)whole.size();
+        for (uint32_t x : order_by_cost_desc(wc)) order.push_back(whole[x]);
+        croots.resize(order.size() - n_row_roots);
+        for (size_t x = 0; x < order.size(); ++x) {
+            const Plan &pl = plan[order[x]];
+            const uint8_t m = mode[order[x]];
+            const uint32_t pA = cjobs[pl.c].pA;
+            bcdev::ActiveRoot &a = aroots[x];
+            a.pool_off = rows_ready ? found[pl.item].off : pool_words;
+            a.task_begin = tasks;
+            a.job = pl.c;
+            a.root = pl.root;
+            a.k = pl.k;
+            a.n_tasks = pl.k - (pA - 2);
+            pool_words += (uint64_t)pl.k * pl.w1;
+            tasks += a.n_tasks;
+            if (m == kByRows) row_tasks += a.n_tasks;
+            if (m != kByRows) {   // the column search's list: whole ones first
+                bcdev::ColRoot &c = croots[m == kWhole ? x - (order.size() - n_whole) : x - n_row_roots + n_whole];
+                c.col_off = col_words;
+                c.pool_off = a.pool_off;
+                c.unit_begin = col_units;
+                c.job = pl.c;
+                c.k = pl.k;
+                c.du = degree_of(pl);
+                c.wk = (pl.k + 63) / 64;
+                c.whole = m == kWhole;
+                c.n_units = m == kWhole ? 1u : c.du - (cjobs[pl.c].qA - 1);
+                col_words += (uint64_t)c.du * c.wk;
+                if (m == kByColumns) col_units += c.n_units;
+            }
+            if (m == kWhole) continue;   // no row search, no slab
+            // per task: S2 and its prefix counts (2 W1), the compress table of
+            // S2's nonzero words (8 W1), the kept-row list of the level-2 filter
+            // (k / 2 + 1), then one block per DFS level 2 .. pA-2, each at most
+            // (k - 1) rows of at most W1 words
+            // (p_A >= 5: plus the pair rows of one small node's three-level sum,
+            // at most kTripleRows (kTripleRows - 1) / 2 rows of at most 4 words
+            // and their u32 indices); a left unit chooses one row more
+            const uint32_t depth = m == kByRows ? pA : pA + 1;
+            const uint64_t pairs3 = (uint64_t)bcdev::kTripleRows * (bcdev::kTripleRows - 1) / 2;
+            uint64_t need = 10ull * pl.w1 + pl.k / 2 + 1 + (depth >= 5 ? pairs3 * 4 + (pairs3 + 1) / 2 : 0) +
+                            (depth >= 4 ? (uint64_t)(depth - 3) * pl.k * pl.w1 : 0) + 8;
+            uint64_t &most = m == kByRows ? slab_need : left_slab_need;
+            most = std::max(most, need);
+        }
+    };
+    lay_out();
+    // units split by a further column, twice: room for 16 per unit, 8M at most;
+    // units left to the row search child by child: 4 per unit, 1M at most
+    uint64_t n_split = std::min<uint64_t>(col_units * 16, 8ull << 20);
+    uint64_t n_children = std::min<uint64_t>(col_units * 4, 1ull << 20);
+    if ((ex.fixed || mem.cap) && !croots.empty()) {
+        // limited scratch: shorter lists, and columns only when they leave half
+        // of the room, and a block's slabs, to what the row search takes
+        n_split = std::min<uint64_t>(n_split, mem.room() / 8 / 48);
+        n_children = std::min<uint64_t>(n_children, mem.room() / 16 / 16);
+        const uint64_t col_bytes =
+            col_words * 8 + (col_units + n_children + 2 * n_split) * 16 + n_split * 16 + croots.size() * sizeof(bcdev::ColRoot) + 2048;
+        const uint64_t other = aroots.size() * sizeof(bcdev::ActiveRoot) + (rows_ready ? 0 : pool_words * 8) +
+                               (uint64_t)bcdev::kWavesPerBlock * std::max(slab_need, left_slab_need) * 8 + 4096;
+        if (col_bytes > mem.room() / 2 || col_bytes + other > mem.room()) {
+            std::fill(mode.begin(), mode.end(), (uint8_t)kByRows);
+            lay_out();
+            n_split = n_children = 0;
+        }
     }
     const double ms_plan =
         std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_plan0).count();
@@ -1522,7 +1683,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         uint64_t *d_heap = nullptr;
         uint64_t heap_words = 0;
         bool any_deep = false;
-        for (const bcdev::ActiveRoot &a : aroots) any_deep = any_deep || cjobs[a.job].pA >= 5;
+        for (uint32_t r = 0; r < n_row_roots; ++r) any_deep = any_deep || cjobs[aroots[r].job].pA >= 5;
         if (any_deep && split_rows != 0 && split_rows != 0xffffffffu) {
             uint64_t cap = 1ull << 22;
             if (ex.fixed || mem.cap) cap = std::min<uint64_t>(cap, mem.room() / 4 / sizeof(uint4));
@@ -1541,21 +1702,68 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         // Enumeration grid: waves_per_cu wavefronts per CU; each wave owns a
         // slab big enough for the deepest task of this plan.
         uint32_t blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / bcdev::kWavesPerBlock);
+        bcdev::ColParams cp{};
+        if (!croots.empty()) {
+            bcdev::ColRoot *d_croots;
+            BC_HIP(mem.get(&d_croots, croots.size()));
+            BC_HIP(mem.get(&cp.cols, col_words));
+            uint2 *d_split2 = nullptr;
+            if (col_units) {
+                BC_HIP(mem.get(&cp.left, col_units + 2 * n_split + n_children));
+                BC_HIP(mem.get(&cp.split, n_split));
+                BC_HIP(mem.get(&d_split2, n_split));
+            }
+            BC_HIP(hipMemcpyAsync(d_croots, croots.data(), croots.size() * sizeof(bcdev::ColRoot),
+                                  hipMemcpyHostToDevice, st));
+            cp.jobs = d_cjobs;
+            cp.roots = d_croots;
+            cp.n_roots = (uint32_t)croots.size();
+            cp.n_whole = n_whole;
+            cp.unit_chunk = roots_per_wave ? roots_per_wave : 4u;
+            cp.instrument = instrument ? 1u : 0u;
+            cp.n_units = col_units;
+            cp.pool = d_pool;
+            cp.queue = d_queue + 10;
+            cp.n_left = d_queue + 16;   // and the children's counter behind it
+            cp.left_cap = n_children;
+            cp.slots = d_slots;
+            // 16 wavefronts per CU, and the same share of them as of the row search's 12
+            uint32_t col_blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / 3);
+            // no more than there are units for (the split ones: 16 a unit at most)
+            col_blocks = (uint32_t)std::min<uint64_t>(col_blocks, (n_whole + col_units * 16) / bcdev::kWavesPerBlock + 1);
+            if (col_slab)
+                BC_HIP(mem.get(&cp.slab, (uint64_t)col_blocks * bcdev::kWavesPerBlock * bcdev::kColSlabWords));
+            cp.split_cap = n_split;
+            cp.n_split = d_queue + 18;
+            BC_HIP(bcdev::launch_columns(cp, col_blocks, st));
+            // the units that were split by a second column, then by a third
+            for (uint32_t x = 0; x < 2 && col_units; ++x) {
+                bcdev::ColParams sp = cp;
+                sp.units = x == 0 ? cp.split : d_split2;
+                sp.n_listed = d_queue + 18 + x;
+                sp.n_units = n_split;
+                sp.split = x == 0 ? d_split2 : nullptr;
+                sp.n_split = d_queue + 19;
+                sp.queue = d_queue + 20 + x;
+                BC_HIP(bcdev::launch_columns(sp, col_blocks, st));
+            }
+        }
         uint64_t slab_budget = 64ull << 30;   // bytes of HBM for all slabs
         slab_budget = std::min(slab_budget, mem.room() > 512 ? mem.room() - 512 : 0);
-        while (blocks > 1 && (uint64_t)blocks * bcdev::kWavesPerBlock * slab_need * 8 > slab_budget) blocks /= 2;
+        const uint64_t slab_words = std::max(slab_need, left_slab_need);   // the two runs share the slabs
+        while (blocks > 1 && (uint64_t)blocks * bcdev::kWavesPerBlock * slab_words * 8 > slab_budget) blocks /= 2;
         uint64_t *d_slab;
-        BC_HIP(mem.get(&d_slab, (uint64_t)blocks * bcdev::kWavesPerBlock * slab_need));
+        BC_HIP(mem.get(&d_slab, (uint64_t)blocks * bcdev::kWavesPerBlock * slab_words));
         bcdev::EnumParams prm{};
         prm.jobs = d_cjobs;
         prm.roots = d_roots;
-        prm.n_roots = (uint32_t)aroots.size();
-        prm.n_tasks = tasks;
+        prm.n_roots = n_row_roots;
+        prm.n_tasks = row_tasks;
         // launches with many tasks per wave take them 8 at a time (fewer
         // queue atomics and root searches; consecutive tasks share their
         // root's rows), small ones 4 at a time (a more even spread)
         prm.task_chunk = roots_per_wave ? roots_per_wave
-                                        : (tasks >= 1024ull * blocks * bcdev::kWavesPerBlock ? 8u : 4u);
+                                        : (row_tasks >= 1024ull * blocks * bcdev::kWavesPerBlock ? 8u : 4u);
         prm.triple = switch_depth == 2 ? 0u : 1u;
         prm.split_rows = split_rows ? split_rows : 256u;
         prm.split_cap = split_cap;
@@ -1572,12 +1780,24 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         prm.split_heap_words = heap_words;
         prm.pool = d_pool;
         prm.slab = d_slab;
-        prm.slab_words = slab_need;
+        prm.slab_words = slab_words;
         prm.lds_words = lds_words;
         prm.instrument = instrument ? 1u : 0u;
         prm.queue = d_queue + 2;
         prm.slots = d_slots;
         BC_HIP(bcdev::launch_enumerate(prm, blocks, st));
+        if (col_units) {
+            bcdev::EnumParams lp = prm;
+            lp.col_roots = cp.roots;
+            lp.cols = cp.cols;
+            lp.left = cp.left;
+            lp.n_left = cp.n_left;
+            lp.split_cap = 0;
+            lp.task_chunk = roots_per_wave ? roots_per_wave : 1u;
+            lp.wave_clock = nullptr;
+            lp.queue = d_queue + 12;
+            BC_HIP(bcdev::launch_enumerate_left(lp, blocks, st));
+        }
     } else {
         tm.mark(3, st);
     }
@@ -1787,13 +2007,12 @@ extern "C" bc_status bc_count_per_vertex(const bc_graph *g, uint32_t p, uint32_t
     std::vector<bc_u128> by_rank(A.n, bc_u128{0, 0});
     if (pA == 1) {
         // each vertex x is the whole L of C(d(x), q_A) bicliques
-        std::vector<u128> col;
-        uint32_t n_ovf = 0, n64 = 0, n58 = 0, n28 = 0;
-        binom_column(A.max_deg, qA, col, n_ovf, n64, n58, n28);
+        Binomials b;
+        binomial_columns(A.max_deg, qA, 0, 0, &b);
         for (uint64_t r = 0; r < A.n; ++r) {
             const uint64_t d = A.h_ptr[r + 1] - A.h_ptr[r];
-            if (d >= n_ovf) return set_error(BC_E_OVERFLOW, "count exceeds 128 bits");
-            by_rank[r] = bc_u128{(uint64_t)col[d], (uint64_t)(col[d] >> 64)};
+            if (d >= b.n_ovf) return set_error(BC_E_OVERFLOW, "count exceeds 128 bits");
+            by_rank[r] = bc_u128{(uint64_t)b.col[d], (uint64_t)(b.col[d] >> 64)};
         }
     } else {
         std::vector<JobSpec> sp{JobSpec{g, p, q, side, 0, 0, false, opts_deadline(opts)}};

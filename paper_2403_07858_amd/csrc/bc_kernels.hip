@@ -376,7 +376,7 @@ __device__ __forceinline__ void wedges_flat_capped(const Job &jb, uint64_t ub, u
 __global__ __launch_bounds__(kBlockThreads) void k_cand_count(const Job *jobs, const uint64_t *job_root_prefix,
                                                               uint32_t n_jobs, uint64_t total_roots,
                                                               RootScratch sc, unsigned long long *queue,
-                                                              uint32_t *out_k, Slot *slots)
+                                                              RootOut *out, Slot *slots)
 {
     __shared__ unsigned long long s_item;
     __shared__ uint32_t s_nt, s_k, s_late;
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_cand_count(const Job *jobs, c
             __syncthreads();
             k = s_k;
         }
-        if (tid == 0) out_k[item] = k;
+        if (tid == 0) out[item] = RootOut{~0ull, k, 0u};
         __syncthreads();
     }
     if (cur_job != 0xffffffffu) wave_flush(slots, jobs[cur_job].slot, acc, ovf, 0, 0);
@@ -442,11 +442,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_cand_count(const Job *jobs, c
 
 hipError_t launch_cand_count(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
                              uint64_t total_roots, RootScratch scratch, uint32_t n_blocks,
-                             unsigned long long *queue, uint32_t *out_k, Slot *slots, hipStream_t stream)
+                             unsigned long long *queue, RootOut *out, Slot *slots, hipStream_t stream)
 {
     if (total_roots == 0) return hipSuccess;
     hipLaunchKernelGGL(k_cand_count, dim3(n_blocks), dim3(kBlockThreads), 0, stream, jobs, job_root_prefix,
-                       n_jobs, total_roots, scratch, queue, out_k, slots);
+                       n_jobs, total_roots, scratch, queue, out, slots);
     return hipGetLastError();
 }
 
@@ -686,15 +686,15 @@ template <bool PV>
 __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, const uint64_t *job_root_prefix,
                                                            uint32_t n_jobs, uint64_t total_roots, RootScratch sc,
                                                            uint64_t *pool, uint64_t pool_cap,
-                                                           unsigned long long *counters, uint32_t *out_k,
-                                                           uint64_t *out_off, Slot *slots)
+                                                           unsigned long long *counters, RootOut *out,
+                                                           Slot *slots)
 {
     __shared__ uint32_t s_key[kHashSlots];               // w + 1, 0 = empty
     __shared__ unsigned long long s_row[kHashSlots];     // row word or count of the slot; later LDS rows
     __shared__ uint16_t s_map[kHashSlots];               // row index of the slot's vertex, kNoRow if none
     __shared__ uint32_t s_sort[kHashSlots];              // candidates being sorted
     __shared__ uint32_t s_wsum[kRbWaves];
-    __shared__ unsigned long long s_item, s_off;
+    __shared__ unsigned long long s_item, s_off, s_bits;
     __shared__ uint32_t s_k, s_nt, s_flag, s_claimed;
     unsigned long long *queue = counters;        // roots
     unsigned long long *pool_head = counters + 1;
@@ -719,6 +719,7 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
             s_flag = 0;
             s_off = ~0ull;
             s_claimed = 0;
+            s_bits = 0;
         }
         __syncthreads();
         const uint64_t item = s_item;
@@ -742,16 +743,14 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
         }
         __syncthreads();
         if (du < jb.qA || s_flag == 4) {
-            if (tid == 0) {
-                out_k[item] = 0;
-                out_off[item] = ~0ull;
-            }
+            if (tid == 0) out[item] = RootOut{~0ull, 0u, 0u};
             __syncthreads();
             continue;
         }
         const bool one = W1 == 1;
         const bool rows = jb.pA >= 3;
         u128 rsum = 0;   // PV: this thread's part of the root's leaves
+        uint64_t bits = 0;   // row bits of this thread's candidates
 
         // pass 1: insert every 2-hop vertex; one-word roots OR in the row bit,
         // wider ones count.  It gives up at the first insert that finds no
@@ -825,6 +824,7 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
                     const uint32_t c = one ? (uint32_t)__popcll(e) : (uint32_t)e;
                     if (s_key[h] != 0u && c >= jb.qA) {
                         ++mine;
+                        bits += c;
                         if (rows) continue;
                         if (c >= jb.n_ovf) ovf = true;
                         else ovf |= __builtin_add_overflow(acc, jb.binom[c], &acc);
@@ -914,6 +914,7 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
                 const uint32_t c = one ? (uint32_t)__popcll(e) : (uint32_t)e;
                 if (s_key[h] != 0u && c >= jb.qA) {
                     ++mine;
+                    bits += c;
                     if (rows) continue;
                     if (c >= jb.n_ovf) ovf = true;
                     else ovf |= __builtin_add_overflow(acc, jb.binom[c], &acc);
@@ -990,6 +991,7 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
                 const uint32_t c = atomicAdd(&cnt[w], 0u);
                 if (c >= jb.qA) {
                     const uint32_t s = atomicAdd(&s_k, 1u);
+                    bits += c;
                     if (rows) {
                         cand_g[s] = w;
                         atomicExch(&cnt[w], kSlotFlag | s);
@@ -1045,11 +1047,12 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
                 if (lane_id() == 0 && t != 0) pv_add(jb.pv, u, t);
             }
         }
-        if (tid == 0) {
-            out_k[item] = k;
-            out_off[item] = build ? off : ~0ull;
+        if (rows && du > kColTripleMax) {   // (what the plan asks of it)
+            bits = wave_sum_u64(bits);
+            if (lane_id() == 0 && bits) atomicAdd(&s_bits, (unsigned long long)bits);
         }
         __syncthreads();
+        if (tid == 0) out[item] = RootOut{build ? off : ~0ull, k, (uint32_t)min(s_bits, 0xffffffffull)};
         for (uint32_t x = tid; x < kHashSlots; x += kRbThreads) {
             s_key[x] = 0;
             s_row[x] = 0;
@@ -1061,16 +1064,16 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
 
 hipError_t launch_root_build(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
                              uint64_t total_roots, RootScratch scratch, uint64_t *pool, uint64_t pool_cap,
-                             uint32_t n_blocks, unsigned long long *counters, uint32_t *out_k, uint64_t *out_off,
-                             Slot *slots, bool per_vertex, hipStream_t stream)
+                             uint32_t n_blocks, unsigned long long *counters, RootOut *out, Slot *slots,
+                             bool per_vertex, hipStream_t stream)
 {
     if (total_roots == 0) return hipSuccess;
     if (per_vertex)
         hipLaunchKernelGGL(k_root_build<true>, dim3(n_blocks), dim3(kRbThreads), 0, stream, jobs, job_root_prefix,
-                           n_jobs, total_roots, scratch, pool, pool_cap, counters, out_k, out_off, slots);
+                           n_jobs, total_roots, scratch, pool, pool_cap, counters, out, slots);
     else
         hipLaunchKernelGGL(k_root_build<false>, dim3(n_blocks), dim3(kRbThreads), 0, stream, jobs, job_root_prefix,
-                           n_jobs, total_roots, scratch, pool, pool_cap, counters, out_k, out_off, slots);
+                           n_jobs, total_roots, scratch, pool, pool_cap, counters, out, slots);
     return hipGetLastError();
 }
 
@@ -1703,8 +1706,6 @@ struct SplitCtx {
     uint32_t root_idx;              // index of the task's root in the active-root list
 };
 
-constexpr uint32_t kNoJ = 0xffffffffu;   // no restriction to one child
-
 // Reserves n consecutive ring entries (lane 0 decides, every lane learns);
 // ~0 when the ring cannot hold them.
 __device__ unsigned long long ring_reserve(const SplitCtx &sp, uint32_t n)
@@ -1751,6 +1752,49 @@ __device__ unsigned long long heap_take(const SplitCtx &sp, uint64_t n)
     return bcast64(got, 0);
 }
 
+// Word `lane` of the candidates that hold a unit's fixed columns.
+__device__ __forceinline__ uint64_t unit_rows(const uint64_t *cols, uint32_t du, uint32_t wk, uint32_t pack)
+{
+    const uint32_t ln = lane_id();
+    if (ln >= wk) return 0;
+    uint64_t x = ~0ull;
+    for (uint32_t i = 0; i < kColFixed; ++i)
+        if (col_fixed(pack, i) != kColNone) x &= cols[(uint64_t)ln * du + col_fixed(pack, i)];
+    return x;
+}
+
+// The first of a unit's fixed columns (the others lie behind it), and their number.
+__device__ __forceinline__ uint32_t unit_first(uint32_t pack, uint32_t *n)
+{
+    uint32_t c = 0;
+    *n = 0;
+    for (uint32_t i = 0; i < kColFixed; ++i)
+        if (col_fixed(pack, i) != kColNone) {
+            c = col_fixed(pack, i);
+            ++*n;
+        }
+    return c;
+}
+
+// Of a root's plane pl (columns 64 pl ..), in lane l the number of the
+// candidates cw (word w in lane w) that hold column 64 pl + l; 0 from column
+// `end` on.
+__device__ __forceinline__ uint32_t col_plane_count(const uint64_t *cols, uint32_t du, uint32_t wk, uint64_t cw,
+                                                    uint32_t pl, uint32_t end)
+{
+    const uint32_t j = pl * kWaveSize + lane_id();
+    const uint64_t *col = cols + (j < end ? j : 0u);
+    uint32_t n = 0;
+    for (uint32_t w = 0; w < wk; w += 4) {   // four loads at once; past wk the last word, ANDed with lane wk's 0
+        uint64_t x[4];
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) x[t] = col[(uint64_t)min(w + t, wk - 1) * du];
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) n += (uint32_t)__popcll(x[t] & readlane64(cw, w + t < wk ? w + t : 63u));
+    }
+    return j < end ? n : 0u;
+}
+
 __device__ __attribute__((always_inline)) inline void dfs_level2(
     const Job &jb, uint32_t jidx, const uint64_t *blk2, uint32_t stride2, uint32_t m2, uint32_t W2, uint32_t s2n,
     uint32_t only_child, Arena &ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct, bool instrument, bool triple,
@@ -1758,23 +1802,37 @@ __device__ __attribute__((always_inline)) inline void dfs_level2(
 
 // One task: the node {u, c_i} of the search tree.  SPLIT compiles in the
 // hand-off of heavy tasks to the subtask ring; without it sp is unused.
-template <bool SPLIT>
+// COLS: the task is a unit of the column search instead, fixed columns (the
+// col_pack i) of the root (columns at cols): S2 are the columns before them
+// that share enough candidates with them, the rows are the candidates that
+// hold them, and jb chooses one row more and those columns less; only_child
+// restricts the search to one child row.
+template <bool SPLIT, bool COLS>
 __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uint32_t i, const uint64_t *pool,
-                         Arena ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct, bool instrument, bool triple,
-                         const SplitCtx *sp, bool *cap_fail, bool *timed_out)
+                         const uint64_t *cols, uint32_t only_child, Arena ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct,
+                         bool instrument, bool triple, const SplitCtx *sp, bool *cap_fail, bool *timed_out)
 {
     const uint32_t ln = lane_id();
     const uint32_t u = rt.root;
-    const uint32_t du = (uint32_t)(jb.ptrA[u + 1] - jb.ptrA[u]);
+    const uint32_t du = COLS ? rt.n_tasks : (uint32_t)(jb.ptrA[u + 1] - jb.ptrA[u]);
     const uint32_t W1 = (du + 63) >> 6;
     const uint32_t k = rt.k;
     glb_u64 *base = (glb_u64 *)(pool + rt.pool_off);   // the root's rows (global: typed loads)
     const uint32_t q = jb.qA, pA = jb.pA;
     uint64_t t0 = instrument ? cycles() : 0;
 
-    const uint32_t s = i;   // the candidates are the rows after i
-    const uint32_t rem = k - s - 1;
-    if (pA == 3 && W1 <= kTileWords && du <= jb.n_u28 && table_ready(tb, jb, jidx, du + 1)) {
+    const uint32_t b_first = COLS ? 0u : i + 1;   // the candidates are the rows after i, or all of them
+    const uint32_t rem = k - b_first;
+    const uint32_t s = COLS ? 0u : i;             // a row that exists
+    // COLS: word `lane` of the rows that hold the fixed columns, and the
+    // first of those columns
+    const uint64_t cw = COLS ? unit_rows(cols, du, (k + 63) >> 6, i) : 0ull;
+    uint32_t n_fixed = 0;
+    const uint32_t c_end = COLS ? unit_first(i, &n_fixed) : 0u;
+    auto kept_plane = [&](uint32_t pl) {
+        return __ballot(col_plane_count(cols, du, (k + 63) >> 6, cw, pl, c_end) >= pA - 2);
+    };
+    if (!COLS && pA == 3 && W1 <= kTileWords && du <= jb.n_u28 && table_ready(tb, jb, jidx, du + 1)) {
         // the root's leaves {u, c_a, c_b} are the pair sum over its rows:
         // task i = 16 I takes row block I on the matrix cores, the root's
         // other tasks have nothing left to do
@@ -1807,7 +1865,7 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
     uint64_t *nzt = nullptr;
     if (W1 == 1) {
         // one-word root: nothing to scan or tabulate
-        const uint64_t x = base[i];
+        const uint64_t x = COLS ? kept_plane(0) : base[i];
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)x);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
         s0 = ((uint64_t)hi << 32) | lo;
@@ -1823,7 +1881,14 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
         uint64_t *s2 = arena_alloc(ar, 2ull * W1, cap_fail);
         if (!s2) return;
         uint64_t *pre = s2 + W1;
-        for (uint32_t w = ln; w < W1; w += kWaveSize) s2[w] = base[(uint64_t)w * k + i];
+        if constexpr (COLS) {
+            for (uint32_t w = 0; w < W1; ++w) {
+                const uint64_t x = w <= c_end >> 6 ? kept_plane(w) : 0ull;
+                if (ln == 0) s2[w] = x;
+            }
+        } else {
+            for (uint32_t w = ln; w < W1; w += kWaveSize) s2[w] = base[(uint64_t)w * k + i];
+        }
         wave_sync();
         uint32_t running = 0;
         for (uint32_t x0 = 0; x0 < W1; x0 += kWaveSize) {
@@ -1886,7 +1951,7 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
     const uint32_t W2 = (s2n + 63) >> 6;
     if (instrument) ct.filter_words += (unsigned long long)rem * nz;
 
-    if (pA == 3) {
+    if (!COLS && pA == 3) {
         // Leaves {u, c_i, c_b}: sum of C(|S2 n row_b|, q).
         for (uint32_t b0 = s + 1; b0 < k; b0 += kWaveSize) {
             const uint32_t b = b0 + ln;
@@ -1930,7 +1995,7 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
         if (!blk2) return;
         glb_u64 *r0 = base + (uint64_t)w0 * k;
         glb_u64 *r1 = base + (uint64_t)(nz > 1 ? w1 : w0) * k;
-        for (uint32_t b0 = s + 1; b0 < k; b0 += kFilterDepth * kWaveSize) {
+        for (uint32_t b0 = b_first; b0 < k; b0 += kFilterDepth * kWaveSize) {
             uint64_t x0[kFilterDepth], x1[kFilterDepth];
 #pragma unroll
             for (uint32_t c = 0; c < kFilterDepth; ++c) {
@@ -1943,7 +2008,8 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
                 const uint32_t b = b0 + c * kWaveSize + ln;
                 const uint64_t v0 = x0[c] & s0, v1 = x1[c] & s1;
                 const uint32_t n = (uint32_t)(__popcll(v0) + __popcll(v1));
-                const bool keep = b < k && n >= q;
+                bool keep = b < k && n >= q;
+                if constexpr (COLS) keep = keep && ((readlane64(cw, ((b0 >> 6) + c) & 63) >> ln) & 1u) != 0;
                 const uint64_t mask = __ballot(keep);
                 if (m2 + (uint32_t)__popcll(mask) > stride2) {
                     // the LDS block is full: give its words back and move the
@@ -1978,7 +2044,7 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
         // those, 64 per step, so that no lane packs a row that was dropped.
         uint32_t *kept = (uint32_t *)arena_alloc(ar, (rem + 1) / 2, cap_fail);
         if (!kept) return;
-        for (uint32_t b0 = s + 1; b0 < k; b0 += kWaveSize) {
+        for (uint32_t b0 = b_first; b0 < k; b0 += kWaveSize) {
             const uint32_t b = b0 + ln;
             const bool valid = b < k;
             const uint32_t bb = valid ? b : s;
@@ -1987,7 +2053,8 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
                 const uint32_t w = (uint32_t)nzt[8ull * e + 7];
                 n += __popcll(nzt[8ull * e] & base[(uint64_t)w * k + bb]);
             }
-            const bool keep = valid && n >= q;
+            bool keep = valid && n >= q;
+            if constexpr (COLS) keep = keep && ((readlane64(cw, b0 >> 6) >> ln) & 1u) != 0;
             const uint64_t mask = __ballot(keep);
             if (keep) kept[m2 + mbcnt64(mask)] = b;
             m2 += (uint32_t)__popcll(mask);
@@ -2085,7 +2152,7 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
         // (a heap block taken without ring room stays unused until the launch ends)
     }
     }
-    dfs_level2(jb, jidx, blk2, stride2, m2, W2, s2n, kNoJ, ar, stack, tb, acc, ct, instrument, triple, cap_fail, timed_out,
+    dfs_level2(jb, jidx, blk2, stride2, m2, W2, s2n, COLS ? only_child : kNoJ, ar, stack, tb, acc, ct, instrument, triple, cap_fail, timed_out,
                t0);
 }
 
@@ -2127,7 +2194,7 @@ __device__ __attribute__((always_inline)) inline void dfs_level2(
         uint32_t a = (uint32_t)stack[4 * d + 2];
         // a small node two levels above the leaves: its last three levels in
         // one matrix-core sweep, then the node is done
-        if (triple && d + 3 == pA && a == 0 && m >= 3 && m <= kTripleRows && W2 <= kTileWords && s2n <= jb.n_u28 &&
+        if (triple && d + 3 == pA && a == 0 && (d > 2 || only_child == kNoJ) && m >= 3 && m <= kTripleRows && W2 <= kTileWords && s2n <= jb.n_u28 &&
             table_ready(tb, jb, jidx, s2n + 1)) {
             const uint32_t pcap = m * (m - 1) / 2;
             const uint64_t mark = (uint64_t)ar.lds_used | (ar.slab_used << 32);
@@ -2226,8 +2293,9 @@ __device__ void enum_flush(Slot *slots, uint32_t slot, Acc &acc, Counters &ct, b
 
 // Three waves per SIMD (12 per CU): the register budget is capped at 168 VGPRs.
 // SPLIT = runtime splitting of heavy tasks (the subtask ring and its drain);
-// the plain variant carries none of that code.
-template <bool SPLIT>
+// COLS = the units left by the column search (prm.left) instead of the tasks of
+// the active roots.  The plain variant carries none of that code.
+template <bool SPLIT, bool COLS>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_enumerate(
     EnumParams prm)
 {
@@ -2279,38 +2347,72 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
     sp.cap = prm.split_cap;
     sp.rows = prm.split_rows;
     sp.root_idx = 0;
+    const unsigned long long n_tasks = COLS ? *prm.n_left : prm.n_tasks;
     for (;;) {
         // pop task_chunk consecutive tasks; only the first needs the root
         // search, the rest advance through the (contiguous) task ranges
         unsigned long long t0 = 0;
         if (ln == 0) t0 = atomicAdd(prm.queue, (unsigned long long)prm.task_chunk + (split ? kProducer : 0ull));
         t0 = bcast64(t0, 0) & kPopMask;
-        if (t0 >= prm.n_tasks) {
+        if (t0 >= n_tasks) {
             if (split && ln == 0)
                 __hip_atomic_fetch_add(prm.queue, 0ull - kProducer, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             break;
         }
-        const unsigned long long t_end = min(t0 + prm.task_chunk, (unsigned long long)prm.n_tasks);
-        // root owning task t0: largest r with roots[r].task_begin <= t0
-        uint32_t r = 0, hi = prm.n_roots;
-        while (hi - r > 1) {
-            const uint32_t mid = (r + hi) >> 1;
-            if (prm.roots[mid].task_begin <= t0) r = mid;
-            else hi = mid;
+        const unsigned long long t_end = min(t0 + prm.task_chunk, n_tasks);
+        uint32_t r = 0;
+        ActiveRoot rt;
+        if constexpr (!COLS) {
+            // root owning task t0: largest r with roots[r].task_begin <= t0
+            uint32_t hi = prm.n_roots;
+            while (hi - r > 1) {
+                const uint32_t mid = (r + hi) >> 1;
+                if (prm.roots[mid].task_begin <= t0) r = mid;
+                else hi = mid;
+            }
+            rt = prm.roots[r];
         }
-        ActiveRoot rt = prm.roots[r];
         for (unsigned long long t = t0; t < t_end; ++t) {
-            while (t >= rt.task_begin + rt.n_tasks) rt = prm.roots[++r];   // every active root owns >= 1 task
+            uint32_t i, child = kNoJ, n_fixed = 1;
+            const uint64_t *cols = nullptr;
+            if constexpr (COLS) {
+                const uint4 e = prm.left[t];
+                r = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
+                i = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
+                child = (uint32_t)__builtin_amdgcn_readfirstlane(e.z);
+                unit_first(i, &n_fixed);
+                const ColRoot cr = prm.col_roots[r];
+                cols = prm.cols + cr.col_off;
+                rt.pool_off = cr.pool_off;
+                rt.job = cr.job;
+                rt.root = 0;
+                rt.k = cr.k;
+                rt.n_tasks = cr.du;
+            } else {
+                while (t >= rt.task_begin + rt.n_tasks) rt = prm.roots[++r];   // every active root owns >= 1 task
+                i = (uint32_t)(t - rt.task_begin);
+            }
             if (rt.job != cur_job) {
                 if (cur_job != 0xffffffffu) enum_flush(prm.slots, prm.jobs[cur_job].slot, acc, ct, instrument);
                 cur_job = rt.job;
             }
-            const Job jb = prm.jobs[rt.job];
+            Job jb = prm.jobs[rt.job];
+            if constexpr (COLS) {
+                const uint32_t x = n_fixed - 1;
+                jb.pA += 1;
+                jb.qA -= n_fixed;
+                jb.binom = jb.less[x].binom;
+                jb.n_ovf = jb.less[x].n_ovf;
+                jb.n_u64 = jb.less[x].n_u64;
+                jb.n_u58 = jb.less[x].n_u58;
+                jb.n_u28 = jb.less[x].n_u28;
+                jb.binom_n = min(jb.binom_n, kColLessLen);
+            }
             bool cap_fail = false, timed_out = past_deadline(jb.deadline);
             sp.root_idx = r;
             if (!timed_out)
-                run_task<SPLIT>(jb, rt.job, rt, (uint32_t)(t - rt.task_begin), prm.pool, arena, stack, tb, acc, ct,
-                                instrument, prm.triple != 0, &sp, &cap_fail, &timed_out);
+                run_task<SPLIT, COLS>(jb, kColFixed * rt.job + n_fixed - 1, rt, i, prm.pool, cols, child, arena, stack, tb, acc, ct, instrument,
+                                      prm.triple != 0, &sp, &cap_fail, &timed_out);
             if (cap_fail && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_CAPACITY);
             if (timed_out && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
         }
@@ -2395,8 +2497,611 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 hipError_t launch_enumerate(const EnumParams &prm, uint32_t n_blocks, hipStream_t stream)
 {
     if (prm.n_tasks == 0) return hipSuccess;
-    if (prm.split_cap != 0) hipLaunchKernelGGL(k_enumerate<true>, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
-    else hipLaunchKernelGGL(k_enumerate<false>, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    if (prm.split_cap != 0) hipLaunchKernelGGL((k_enumerate<true, false>), dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    else hipLaunchKernelGGL((k_enumerate<false, false>), dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    return hipGetLastError();
+}
+
+hipError_t launch_enumerate_left(const EnumParams &prm, uint32_t n_blocks, hipStream_t stream)
+{
+    hipLaunchKernelGGL((k_enumerate<false, true>), dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// The column search.  A node of the row search fixes rows (vertices of the
+// anchor side) and sums C(|common neighbours|, q) over their subsets.  The
+// same sum over a root's (or a task's) candidates, grouped by the other
+// side, is
+//     sum over T, |T| = q, of C(number of candidates adjacent to all of T, p)
+// with T a subset of the common neighbours S and p the vertices of L still to
+// choose: both count the pairs (subset of candidates, q-subset of their
+// common neighbours).  On power-law graphs most of a search lies where S has
+// a dozen vertices and hundreds of candidates share them, so that the
+// q-subsets of S are far fewer than the p-subsets of the candidates (a
+// 1.2M-edge graph at (5,5): 5e10 pair intersections' worth of work instead of
+// 3.3e12), and their cost does not grow with p.
+//
+// A column is the bitmap over the root's candidates of one neighbour of the
+// root; k_transpose writes them from the candidate rows.  A unit of k_columns
+// is a whole root (few neighbours), or a root and the last (sparsest) column c
+// of its subsets: the candidates adjacent to c, listed and transposed into a
+// compact block, and the columns before c that share p of them, out of which
+// q - 1 more are chosen.  Taking the sparsest column first leaves short
+// bitmaps (mostly one or two words, where the root has ten to forty), and each
+// q-subset is met once per root, not once per candidate.  Where the block has
+// fewer p-subsets of rows than (q - 1)-subsets of columns the unit is listed
+// for the row search instead.
+//
+// The search itself stages its columns in LDS and gives every lane a tuple of
+// columns in colexicographic order, kept as one AND in registers; the
+// remaining columns run through wave-uniform loops, their words broadcast from
+// LDS.  In that order the lanes of a wave share almost the same last column,
+// so the loops, which start behind it, waste few lanes.  What bounds it is the
+// VALU: two operations (AND, popcount with add) per 32 candidates and tuple.
+// Whole counts with and without it, power-law graphs: 1.2M edges (5,5) 48
+// against 989 ms, 300k (6,6) 43 against 445 ms, 2M (4,4) 26 against 86 ms,
+// (6,4) 38 against 47 ms, 5M (3,3) 65 against 89 ms.  The same search per task
+// of the row search instead of per root was slower ((5,5) 104 ms, (4,4) 52 ms:
+// its short units spend their time on staging).
+
+// Colexicographic tuples of columns, the largest highest, seven bits a column
+// (six in tuples of five): the tuples of the first s columns are a prefix.
+struct ColTuples {
+    uint16_t pair[choose(kColMax, 2)];
+    uint32_t triple[choose(kColTripleMax, 3)];
+    uint32_t quad[choose(kColQuadMax, 4)];
+    uint32_t quint[choose(kColQuintMax, 5)];
+};
+
+constexpr ColTuples make_col_tuples()
+{
+    ColTuples t{};
+    uint32_t n2 = 0, n3 = 0, n4 = 0, n5 = 0;
+    for (uint32_t b = 0; b < kColMax; ++b)
+        for (uint32_t a = 0; a < b; ++a) t.pair[n2++] = (uint16_t)(a | (b << 7));
+    for (uint32_t c = 0; c < kColTripleMax; ++c)
+        for (uint32_t x = 0; x < c * (c - 1) / 2; ++x) t.triple[n3++] = t.pair[x] | (c << 14);
+    for (uint32_t d = 0; d < kColQuadMax; ++d)
+        for (uint32_t x = 0, n = (uint32_t)choose(d, 3); x < n; ++x) t.quad[n4++] = t.triple[x] | (d << 21);
+    for (uint32_t e = 0; e < kColQuintMax; ++e)
+        for (uint32_t d = 0; d < e; ++d)
+            for (uint32_t c = 0; c < d; ++c)
+                for (uint32_t b = 0; b < c; ++b)
+                    for (uint32_t a = 0; a < b; ++a)
+                        t.quint[n5++] = a | (b << 6) | (c << 12) | (d << 18) | (e << 24);
+    return t;
+}
+static __device__ constexpr ColTuples col_tuples = make_col_tuples();
+static __device__ constexpr ColCosts col_costs = make_col_costs();
+
+__device__ __forceinline__ uint32_t col_tuple_at(uint32_t R, uint32_t idx)
+{
+    switch (R) {
+    case 1: return idx;
+    case 2: return col_tuples.pair[idx];
+    case 3: return col_tuples.triple[idx];
+    case 4: return col_tuples.quad[idx];
+    default: return col_tuples.quint[idx];
+    }
+}
+
+typedef uint64_t v2u64 __attribute__((ext_vector_type(2)));
+// Where a search of NC words a column finds them: LDS below 16 words, else LDS
+// or the wave's slab (flat loads serve both).
+template <int NC>
+using col_ptr = std::conditional_t<(NC < 16), __attribute__((address_space(3))) const v2u64 *, const v2u64 *>;
+
+// n (n - 1) ... (n - P + 1), n <= 64 kColWords = 2560.
+template <int P, int NC = kColWords>
+__device__ __forceinline__ uint64_t falling(uint32_t n)
+{
+    const uint32_t a = __umul24(n, n - 1);
+    if constexpr (P == 2) return a;
+    if constexpr (P == 3 && NC <= 24) return (uint32_t)__umul24(a, n - 2);   // below 1536^3 < 2^32
+    if constexpr (P == 3) return (uint64_t)a * (n - 2);
+    const uint32_t b = __umul24(n - 2, n - 3);
+    if constexpr (P == 4) return (uint64_t)a * b;
+    return (uint64_t)a * b * (n - 4);
+}
+
+// x / P! for x a multiple of it: a shift and the inverse of the odd part mod 2^64.
+template <int P>
+__device__ __forceinline__ uint64_t div_factorial(uint64_t x)
+{
+    if constexpr (P == 2) return x >> 1;
+    if constexpr (P == 3) return (x >> 1) * 0xAAAAAAAAAAAAAAABull;
+    if constexpr (P == 4) return (x >> 3) * 0xAAAAAAAAAAAAAAABull;
+    return (x >> 3) * 0xEEEEEEEEEEEEEEEFull;
+}
+
+template <int NC>
+__device__ __forceinline__ uint32_t col_count(const uint64_t (&v)[NC], col_ptr<NC> c)
+{
+    uint32_t n = 0;
+#pragma unroll
+    for (int w = 0; w < NC / 2; ++w) {
+        const v2u64 x = c[w];
+        n += (uint32_t)__popcll(v[2 * w] & x[0]);
+        n += (uint32_t)__popcll(v[2 * w + 1] & x[1]);
+    }
+    return n;
+}
+
+// Adds falling<P>(candidates of v and D more columns) over the D-subsets of
+// columns k0 .. s-1.  One loop's sum stays below 2^64: falling<5>(1024) <
+// 2^50, and at most C(126, 2) terms are added between two folds.
+template <int NC, int D, int P>
+__device__ __forceinline__ void col_level(const uint64_t (&v)[NC], col_ptr<NC> buf, uint32_t k0, uint32_t s,
+                                          uint64_t &sum)
+{
+    constexpr uint32_t st = col_stride(NC) / 2;
+    if constexpr (D == 1) {
+        if constexpr (P == 2) {   // 126 terms below 2^23
+            uint32_t part = 0;
+            for (uint32_t l = k0; l < s; ++l) part += (uint32_t)falling<2>(col_count<NC>(v, buf + l * st));
+            sum += part;
+        } else {
+            for (uint32_t l = k0; l < s; ++l) sum += falling<P, NC>(col_count<NC>(v, buf + l * st));
+        }
+    } else {
+        for (uint32_t k = k0; k + D <= s; ++k) {
+            uint64_t u[NC];
+            uint32_t n = 0;
+#pragma unroll
+            for (int w = 0; w < NC / 2; ++w) {
+                const v2u64 x = buf[k * st + w];
+                u[2 * w] = v[2 * w] & x[0];
+                u[2 * w + 1] = v[2 * w + 1] & x[1];
+                n += (uint32_t)__popcll(u[2 * w]) + (uint32_t)__popcll(u[2 * w + 1]);
+            }
+            if (__ballot(n >= (uint32_t)P) == 0) continue;   // no lane's subsets hold p candidates
+            col_level<NC, D - 1, P>(u, buf, k + 1, s, sum);
+        }
+    }
+}
+
+// The whole sum over s columns of NC words in LDS: tuples of R columns per
+// lane, D columns in the loops.
+template <int NC, int D, int P>
+__device__ __forceinline__ void col_search(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, Acc &acc)
+{
+    const uint32_t ln = lane_id();
+    constexpr uint32_t st = col_stride(NC) / 2;
+    for (uint32_t base = 0; base < n_tup; base += kWaveSize) {
+        const uint32_t idx = min(base + ln, n_tup - 1);
+        const uint32_t e = col_tuple_at(R, idx);
+        const uint32_t bits = R == 5 ? 6 : 7, last = e >> (bits * (R - 1));
+        uint64_t v[NC];
+#pragma unroll
+        for (int w = 0; w < NC / 2; ++w) {
+            const v2u64 x = buf[last * st + w];
+            v[2 * w] = x[0];
+            v[2 * w + 1] = x[1];
+        }
+        for (uint32_t t = 0; t + 1 < R; ++t) {
+            const uint32_t c = (e >> (bits * t)) & ((1u << bits) - 1u);
+#pragma unroll
+            for (int w = 0; w < NC / 2; ++w) {
+                const v2u64 x = buf[c * st + w];
+                v[2 * w] &= x[0];
+                v[2 * w + 1] &= x[1];
+            }
+        }
+        if (base + kWaveSize > n_tup) {   // lanes past the last tuple hold no candidates
+            const bool valid = base + ln < n_tup;
+#pragma unroll
+            for (int w = 0; w < NC; ++w) v[w] = valid ? v[w] : 0ull;
+        }
+        // columns up to the lanes' largest last one count only for the lanes
+        // whose own last one lies before
+        const uint32_t lmin = __builtin_amdgcn_readfirstlane(last);
+        const uint32_t lmax = (uint32_t)__builtin_amdgcn_readlane((int)last, kWaveSize - 1);
+        uint64_t sum = 0;
+        uint32_t k = lmin + 1;
+        for (; k <= lmax && k + D <= s; ++k) {
+            if constexpr (D == 1) {
+                const uint32_t n = col_count<NC>(v, buf + k * st);
+                sum += falling<P, NC>(k > last ? n : 0u);
+            } else {
+                uint64_t u[NC];
+#pragma unroll
+                for (int w = 0; w < NC / 2; ++w) {
+                    const v2u64 x = buf[k * st + w];
+                    u[2 * w] = k > last ? v[2 * w] & x[0] : 0ull;
+                    u[2 * w + 1] = k > last ? v[2 * w + 1] & x[1] : 0ull;
+                }
+                col_level<NC, D - 1, P>(u, buf, k + 1, s, sum);
+                if constexpr (D > 2) {
+                    acc.t += div_factorial<P>(sum);
+                    sum = 0;
+                }
+            }
+        }
+        if constexpr (D > 2) {
+            for (; k + D <= s; ++k) {
+                uint64_t u[NC];
+#pragma unroll
+                for (int w = 0; w < NC / 2; ++w) {
+                    const v2u64 x = buf[k * st + w];
+                    u[2 * w] = v[2 * w] & x[0];
+                    u[2 * w + 1] = v[2 * w + 1] & x[1];
+                }
+                col_level<NC, D - 1, P>(u, buf, k + 1, s, sum);
+                acc.t += div_factorial<P>(sum);
+                sum = 0;
+            }
+        } else {
+            col_level<NC, D, P>(v, buf, k, s, sum);
+            acc.t += div_factorial<P>(sum);
+        }
+    }
+    acc_flush(acc);
+}
+
+template <int NC, int D>
+__device__ __forceinline__ void col_search_p(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, uint32_t p,
+                                             Acc &acc)
+{
+    switch (p) {
+    case 2: col_search<NC, D, 2>(buf, s, R, n_tup, acc); break;
+    case 3: col_search<NC, D, 3>(buf, s, R, n_tup, acc); break;
+    case 4: col_search<NC, D, 4>(buf, s, R, n_tup, acc); break;
+    default: col_search<NC, D, 5>(buf, s, R, n_tup, acc); break;
+    }
+}
+
+// q columns out of s: the loops take D = col_loops(q, words) of them.
+template <int NC>
+__device__ __forceinline__ void col_search_q(col_ptr<NC> buf, uint32_t s, uint32_t q, uint32_t D, uint32_t n_tup,
+                                             uint32_t p, Acc &acc)
+{
+    switch (D) {
+    case 1: col_search_p<NC, 1>(buf, s, q - 1, n_tup, p, acc); break;
+    case 2:
+        if constexpr (NC <= 16) col_search_p<NC, 2>(buf, s, q - 2, n_tup, p, acc);
+        break;
+    default:
+        if constexpr (NC <= 8) col_search_p<NC, 3>(buf, s, q - 3, n_tup, p, acc);
+        break;
+    }
+}
+
+// 64 x 64 bit transpose across the wave: lane r's bit c becomes lane c's bit r.
+__device__ __forceinline__ uint64_t transpose64(uint64_t x)
+{
+    const uint32_t ln = lane_id();
+    uint64_t m = 0x00000000ffffffffull;
+#pragma unroll
+    for (int j = 32; j; j >>= 1) {
+        const uint64_t t = __shfl_xor((unsigned long long)x, j);
+        x = (ln & j) ? (x & ~m) | ((t & ~m) >> j) : (x & m) | ((t & m) << j);
+        m ^= m << (j >> 1);
+    }
+    return x;
+}
+
+// Columns of every root: one wave per 64 candidates and row word.
+__global__ __launch_bounds__(kBlockThreads) void k_transpose(ColParams prm)
+{
+    const uint32_t wv = threadIdx.x / kWaveSize, ln = lane_id();
+    for (uint32_t r = blockIdx.x; r < prm.n_roots; r += gridDim.x) {
+        const ColRoot rt = prm.roots[r];
+        const uint32_t W1 = (rt.du + 63) >> 6;
+        for (uint32_t x = wv; x < W1 * rt.wk; x += kWavesPerBlock) {
+            const uint32_t w = x / rt.wk, ch = x - w * rt.wk, row = ch * kWaveSize + ln;
+            const uint64_t v = row < rt.k ? prm.pool[rt.pool_off + (uint64_t)w * rt.k + row] : 0ull;
+            const uint64_t c = transpose64(v);
+            const uint32_t col = w * kWaveSize + ln;
+            if (col < rt.du) prm.cols[rt.col_off + (uint64_t)ch * rt.du + col] = c;
+        }
+    }
+}
+
+constexpr uint32_t kLeftBuf = 64;   // listed units a wave gathers before it writes them out
+constexpr uint64_t kColLong = 400000;   // wave instructions (about a millisecond) past which a unit is split up
+
+// Leaf sum for one more column: lane's column shares n candidates, choose p.
+__device__ __forceinline__ uint64_t leaf_falling(uint32_t n, uint32_t p)
+{
+    switch (p) {
+    case 2: return div_factorial<2>(falling<2>(n));
+    case 3: return div_factorial<3>(falling<3>(n));
+    case 4: return div_factorial<4>(falling<4>(n));
+    default: return div_factorial<5>(falling<5>(n));
+    }
+}
+
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_columns(ColParams prm)
+{
+    __shared__ __align__(16) uint64_t s_buf[kWavesPerBlock][kColBuf];
+    __shared__ uint64_t s_kept[kWavesPerBlock][kColRootPlanes];
+    __shared__ uint32_t s_rank[kWavesPerBlock][kColRootPlanes];
+    __shared__ uint16_t s_list[kWavesPerBlock][2 * kWaveSize];
+    __shared__ uint4 s_left[kWavesPerBlock][kLeftBuf];
+    const uint32_t wv = threadIdx.x / kWaveSize, ln = lane_id();
+    uint64_t *lds = &s_buf[wv][0];
+    uint64_t *slab = prm.slab ? prm.slab + ((uint64_t)blockIdx.x * kWavesPerBlock + wv) * kColSlabWords : nullptr;
+    uint16_t *list = &s_list[wv][0];
+    const bool instrument = prm.instrument != 0;
+    Acc acc;
+    acc.v = 0;
+    acc.ovf = false;
+    acc.t = 0;
+    Counters ct{};
+    uint32_t cur_job = 0xffffffffu, n_left = 0;
+    auto write_left = [&]() {
+        unsigned long long at = 0;
+        if (ln == 0) at = atomicAdd(prm.n_left, (unsigned long long)n_left);
+        at = bcast64(at, 0);
+        wave_sync();
+        if (ln < n_left) prm.left[at + ln] = s_left[wv][ln];
+        wave_sync();
+        n_left = 0;
+    };
+    const uint64_t n_units = prm.units ? min((uint64_t)*prm.n_listed, prm.n_units) : prm.n_units;
+    const uint32_t n_whole = prm.units ? 0u : prm.n_whole;
+    for (;;) {
+        // tickets: first the whole roots one by one, then chunks of units
+        unsigned long long tk = 0;
+        if (ln == 0) tk = atomicAdd(prm.queue, 1ull);
+        tk = bcast64(tk, 0);
+        uint32_t r = 0;
+        uint64_t t0 = 0, t1 = 1;
+        ColRoot rt;
+        if (tk < n_whole) {
+            r = (uint32_t)tk;
+            rt = prm.roots[r];
+        } else {
+            t0 = (tk - n_whole) * prm.unit_chunk;
+            if (t0 >= n_units) break;
+            t1 = min(t0 + prm.unit_chunk, n_units);
+            if (!prm.units) {
+                uint32_t hi = prm.n_roots;
+                r = prm.n_whole;
+                while (hi - r > 1) {
+                    const uint32_t mid = (r + hi) >> 1;
+                    if (prm.roots[mid].unit_begin <= t0) r = mid;
+                    else hi = mid;
+                }
+                rt = prm.roots[r];
+            }
+        }
+        for (uint64_t t = t0; t < t1; ++t) {
+            uint32_t fixed = col_pack(kColNone, kColNone, kColNone);   // the unit's fixed columns
+            if (prm.units) {
+                const uint2 e = prm.units[t];
+                r = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
+                fixed = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
+                if (r == kNoJ) continue;
+                rt = prm.roots[r];
+            } else if (tk >= n_whole) {
+                while (t >= rt.unit_begin + rt.n_units) rt = prm.roots[++r];   // every root owns >= 1 unit
+                fixed = col_pack(rt.du - 1 - (uint32_t)(t - rt.unit_begin), kColNone, kColNone);
+            }
+            if (rt.job != cur_job) {
+                if (cur_job != 0xffffffffu) enum_flush(prm.slots, prm.jobs[cur_job].slot, acc, ct, instrument);
+                cur_job = rt.job;
+            }
+            const Job &jb = prm.jobs[rt.job];
+            if (past_deadline(jb.deadline)) {
+                if (ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
+                continue;
+            }
+            uint64_t c0 = instrument ? cycles() : 0;
+            // the search below: q of s items (bitmaps of nw words) that share p
+            const uint64_t *cols = prm.cols + rt.col_off;
+            uint32_t q = jb.qA, p = jb.pA - 1, s, nc;
+            uint64_t *buf = lds;
+            if (!prm.units && tk < n_whole) {
+                s = rt.du;
+                const uint32_t nw = rt.wk;
+                nc = col_words(nw, s);
+                const uint32_t st = col_stride(nc);
+                if (s * st > kColBuf) buf = slab;
+                for (uint32_t x = ln; x < s * nc; x += kWaveSize) {
+                    const uint32_t w = x / s, c = x - w * s;
+                    buf[c * st + w] = w < nw ? cols[(uint64_t)w * s + c] : 0ull;
+                }
+            } else {
+                // the fixed columns are the last of the unit's subsets: q more
+                // before them, and p of the candidates that hold them
+                uint32_t n_fixed;
+                const uint32_t end = unit_first(fixed, &n_fixed), planes = (end + 63) >> 6;
+                q -= n_fixed;
+                const uint64_t cw = unit_rows(cols, rt.du, rt.wk, fixed);
+                const uint32_t m = (uint32_t)wave_sum_u64(__popcll(cw));
+                if (m < p) continue;
+                s = 0;
+                for (uint32_t pl = 0; pl < planes; ++pl) {
+                    const uint32_t n = col_plane_count(cols, rt.du, rt.wk, cw, pl, end);
+                    if (q == 1) {   // each of these columns ends a subset
+                        acc.t += leaf_falling(n, p);
+                        continue;
+                    }
+                    const uint64_t kept = __ballot(n >= p);
+                    if (ln == 0) {
+                        s_kept[wv][pl] = kept;
+                        s_rank[wv][pl] = s;
+                    }
+                    s += (uint32_t)__popcll(kept);
+                }
+                if (q == 1) acc_flush(acc);
+                if (instrument) ct.filter_words += (uint64_t)end * rt.wk;
+                if (s < q) {
+                    if (instrument) ct.cyc_setup += cycles() - c0;
+                    continue;
+                }
+                // the cheapest of: q-subsets of the columns, p-subsets of the
+                // rows as bitmaps over the columns, units with one more column
+                // fixed (about 700 instructions each, and a search over half
+                // the columns and words), the row search
+                wave_sync();
+                const uint32_t mw = (m + 63) >> 6, sw = (s + 63) >> 6;
+                const uint32_t mc = col_words(mw, s), sc = col_words(sw, m);
+                const uint32_t dc = col_loops(q, mc, s), dr = col_loops(p, sc, m);
+                const uint64_t er = row_estimate(m, p) + 400 + 20ull * rt.wk;
+                uint64_t best = er;
+                uint32_t how = 0;
+                if (col_fits(s, mw, q, slab != nullptr)) {
+                    const uint64_t e = col_estimate(col_costs.of(q, dc, s), mc, q - dc);
+                    if (e <= best) {
+                        best = e;
+                        how = 1;
+                    }
+                }
+                if (m <= (uint32_t)kWaveSize && q <= kColMaxP && sc < 16 && col_fits(m, sw, p, false) &&
+                    m * col_stride(sc) + s <= kColBuf) {
+                    const uint64_t e = col_estimate(col_costs.of(p, dr, m), sc, p - dr);
+                    if (e < best) {
+                        best = e;
+                        how = 2;
+                    }
+                }
+                if (prm.split) {
+                    uint64_t e = 700;
+                    if (q > 2) {
+                        const uint32_t sh = min(s / 2, kColTripleMax), hc = col_words((mw + 1) / 2, sh);
+                        const uint32_t dh = col_loops(q - 1, hc, sh);
+                        e += col_estimate(col_costs.of(q - 1, dh, sh), hc, q - 1 - dh);
+                    }
+                    // (a long unit is split in any case: it runs on one wave)
+                    if (s * e < best || best > kColLong) {
+                        const uint32_t n_sub = s - (q - 1);   // kept columns with q - 1 more below them
+                        unsigned long long at = 0;
+                        if (ln == 0) at = atomicAdd(prm.n_split, (unsigned long long)n_sub);
+                        at = bcast64(at, 0);
+                        if (at + n_sub <= prm.split_cap) {
+                            for (uint32_t pl = 0; pl < planes; ++pl) {
+                                const uint64_t kept = s_kept[wv][pl];
+                                const uint32_t rank = s_rank[wv][pl] + mbcnt64(kept), c = pl * kWaveSize + ln;
+                                const uint32_t more = n_fixed == 1 ? col_pack(col_fixed(fixed, 0), c, kColNone)
+                                                                   : col_pack(col_fixed(fixed, 0), col_fixed(fixed, 1), c);
+                                if (((kept >> ln) & 1u) && rank >= q - 1)
+                                    prm.split[at + rank - (q - 1)] = make_uint2(r, more);
+                            }
+                            if (instrument) ct.cyc_setup += cycles() - c0;
+                            continue;
+                        }
+                        // no room (from now on): the entries up to the end
+                        // are marked unused, and the next best is taken
+                        for (uint64_t x = at + ln; x < prm.split_cap; x += kWaveSize)
+                            prm.split[x] = make_uint2(kNoJ, 0);
+                    }
+                }
+                if (how == 0) {
+                    // a long one goes child by child (p >= 3: its search
+                    // descends into them), when there is room for them
+                    bool one = true;
+                    if (er > kColLong && p >= 3) {
+                        unsigned long long at = 0;
+                        if (ln == 0) at = atomicAdd(prm.n_left + 1, (unsigned long long)m);
+                        at = bcast64(at, 0);
+                        if (at + m <= prm.left_cap) {
+                            if (ln == 0) at = atomicAdd(prm.n_left, (unsigned long long)m);
+                            at = bcast64(at, 0);
+                            for (uint32_t x = ln; x < m; x += kWaveSize) prm.left[at + x] = make_uint4(r, fixed, x, 0);
+                            one = false;
+                        }
+                    }
+                    if (one) {
+                        if (ln == 0) s_left[wv][n_left] = make_uint4(r, fixed, kNoJ, 0);
+                        if (++n_left == kLeftBuf) write_left();
+                    }
+                    if (instrument) ct.cyc_setup += cycles() - c0;
+                    continue;
+                }
+                if (instrument) {
+                    const uint64_t c1 = cycles();
+                    ct.cyc_setup += c1 - c0;
+                    c0 = c1;
+                }
+                // list the rows, and transpose them 64 at a time into the kept
+                // columns (one word a column when the rows are what is searched)
+                const uint64_t *rows = prm.pool + rt.pool_off;
+                const uint32_t cst = how == 1 ? col_stride(mc) : 1u;
+                if (how == 1 && s * cst > kColBuf) buf = slab;
+                uint64_t *cbuf = how == 1 ? buf : buf + (kColBuf - s);
+                uint32_t have = 0, done = 0, ch = 0;
+                auto chunk = [&]() {
+                    wave_sync();
+                    const bool live = done + ln < have;
+                    const uint32_t row = list[(done + ln) & (2 * kWaveSize - 1)];
+                    for (uint32_t pl = 0; pl < planes; ++pl) {
+                        const uint64_t kept = s_kept[wv][pl];
+                        if (kept == 0) continue;
+                        const uint64_t x = transpose64(live ? rows[(uint64_t)pl * rt.k + row] : 0ull);
+                        if ((kept >> ln) & 1u) cbuf[(s_rank[wv][pl] + mbcnt64(kept)) * cst + ch] = x;
+                    }
+                    wave_sync();
+                    done = min(done + kWaveSize, have);
+                    ++ch;
+                };
+                for (uint64_t nz = __ballot(cw != 0); nz != 0; nz &= nz - 1) {
+                    const uint32_t w = (uint32_t)__builtin_ctzll(nz);
+                    const uint64_t word = readlane64(cw, w);
+                    if ((word >> ln) & 1u)
+                        list[(have + mbcnt64(word)) & (2 * kWaveSize - 1)] = (uint16_t)(w * kWaveSize + ln);
+                    have += (uint32_t)__popcll(word);
+                    if (have - done >= (uint32_t)kWaveSize) chunk();
+                }
+                if (have > done) chunk();
+                if (how == 1) {
+                    nc = mc;
+                    for (uint32_t c = ln; c < s; c += kWaveSize)
+                        for (uint32_t w = mw; w < nc; ++w) buf[c * cst + w] = 0;
+                } else {   // back into rows of the kept columns
+                    nc = sc;
+                    const uint32_t st = col_stride(nc);
+                    for (uint32_t w = 0; w < nc; ++w) {
+                        const uint32_t c = w * kWaveSize + ln;
+                        const uint64_t x = transpose64(c < s ? cbuf[c] : 0ull);
+                        if (ln < m) buf[ln * st + w] = x;
+                    }
+                    s = m;
+                    const uint32_t x = p;
+                    p = q;
+                    q = x;
+                }
+            }
+            wave_sync();
+            if (instrument) {
+                const uint64_t c1 = cycles();
+                ct.cyc_compact += c1 - c0;
+                c0 = c1;
+            }
+            s = __builtin_amdgcn_readfirstlane(s);
+            const uint32_t D = col_loops(q, nc, s);
+            const ColCost cost = col_costs.of(q, D, s);
+            const uint32_t n_tup = __builtin_amdgcn_readfirstlane(cost.tuples);
+            switch (nc) {
+            case 2: col_search_q<2>((col_ptr<2>)buf, s, q, D, n_tup, p, acc); break;
+            case 4: col_search_q<4>((col_ptr<4>)buf, s, q, D, n_tup, p, acc); break;
+            case 6: col_search_q<6>((col_ptr<6>)buf, s, q, D, n_tup, p, acc); break;
+            case 8: col_search_q<8>((col_ptr<8>)buf, s, q, D, n_tup, p, acc); break;
+            case 12: col_search_q<12>((col_ptr<12>)buf, s, q, D, n_tup, p, acc); break;
+            case 16: col_search_q<16>((col_ptr<16>)buf, s, q, D, n_tup, p, acc); break;
+            case 24: col_search_q<24>((col_ptr<24>)buf, s, q, D, n_tup, p, acc); break;
+            default: col_search_q<40>((col_ptr<40>)buf, s, q, D, n_tup, p, acc); break;
+            }
+            wave_sync();   // the next unit writes the same words
+            if (instrument) {   // lane steps, and the words they AND
+                ct.pairs += cost.leaf * 64ull;
+                ct.pair_slots += cost.leaf * 64ull;
+                ct.pair_words += ((uint64_t)cost.leaf + cost.outer) * 64 * nc;
+                ct.cyc_pair += cycles() - c0;
+            }
+        }
+    }
+    if (n_left) write_left();
+    if (cur_job != 0xffffffffu) enum_flush(prm.slots, prm.jobs[cur_job].slot, acc, ct, instrument);
+}
+
+hipError_t launch_columns(const ColParams &prm, uint32_t n_blocks, hipStream_t stream)
+{
+    if (prm.n_roots == 0) return hipSuccess;
+    if (!prm.units) hipLaunchKernelGGL(k_transpose, dim3(min(prm.n_roots, 4096u)), dim3(kBlockThreads), 0, stream, prm);
+    hipLaunchKernelGGL(k_columns, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
     return hipGetLastError();
 }
 
