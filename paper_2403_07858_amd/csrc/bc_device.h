@@ -140,8 +140,10 @@ constexpr uint32_t kColFixed = 3;          // most columns fixed in a unit
 constexpr uint32_t kColLessLen = 64 * kColRootPlanes + 1;   // entries of a unit's leaf table, if so many
 constexpr uint32_t kNoJ = 0xffffffffu;     // no restriction to one child
 constexpr int kSortCap = 4096;          // candidates sorted in LDS up to this many
-constexpr int kRbWaves = 16;            // waves per block of the fused per-root kernel
+constexpr int kRbWaves = 8;             // waves per large block of the fused per-root kernel
 constexpr int kRbThreads = kWaveSize * kRbWaves;
+constexpr uint32_t kRbBigPerCu = 2;     // large blocks of it on a CU
+constexpr uint32_t kRbSmallPerCu = 5;   // small blocks (four waves)
 constexpr uint32_t kSlotFlag = 0x80000000u;
 
 // What the candidate pass finds of one root.
@@ -157,6 +159,27 @@ struct RootScratch {
     uint32_t *touched;      // per block: nA_max touched ids
     uint32_t *cand;         // per block: nA_max candidate ids (when k > kSortCap)
     uint64_t stride;        // elements per block in each array
+};
+
+struct RootParams {
+    const Job *jobs;
+    const uint64_t *job_root_prefix;   // first item of each job
+    uint32_t n_jobs;
+    uint32_t run, period;              // a job's items: `run` ranks out of every `period` (run 0: all)
+    uint64_t total_roots;
+    RootScratch sc;                    // of the large blocks
+    uint64_t *pool;                    // candidate rows
+    uint64_t pool_cap;                 // words
+    uint64_t chunk;                    // pool words a block reserves at once (0: what each root needs)
+    unsigned long long *pool_head;
+    unsigned long long *queue;         // items of the first launch
+    unsigned long long *queue_big;     // of the second
+    unsigned long long *n_retry;       // roots left to the large blocks
+    uint32_t *retry;                   // their items
+    const uint32_t *list;              // items of the launch (null: all)
+    const unsigned long long *n_list;
+    RootOut *out;
+    Slot *slots;
 };
 
 struct ColParams {
@@ -224,13 +247,12 @@ hipError_t launch_cand_count(const Job *jobs, const uint64_t *job_root_prefix, u
                              uint64_t total_roots, RootScratch scratch, uint32_t n_blocks,
                              unsigned long long *queue, RootOut *out, Slot *slots, hipStream_t stream);
 // Candidate counts and rows in one kernel; rows go to pool[out[r].off ..]
-// (bump-allocated from counters[1], capacity pool_cap words).  counters[0] is
-// the root queue.  Blocks of kRbThreads
-// threads with 144 KiB of LDS each.
-hipError_t launch_root_build(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
-                             uint64_t total_roots, RootScratch scratch, uint64_t *pool, uint64_t pool_cap,
-                             uint32_t n_blocks, unsigned long long *counters, RootOut *out, Slot *slots,
-                             bool per_vertex, hipStream_t stream);
+// (bump-allocated from *pool_head, capacity pool_cap words).  n_small blocks of
+// four waves take every root and list those too large for them in retry; then
+// n_big blocks of kRbThreads threads with 77 KiB of LDS each take these
+// (n_small 0: all).
+hipError_t launch_root_build(const RootParams &prm, uint32_t n_small, uint32_t n_big, bool per_vertex,
+                             hipStream_t stream);
 hipError_t launch_rows_build(const Job *jobs, const ActiveRoot *roots, uint32_t n_roots,
                              uint64_t *pool, RootScratch scratch, uint32_t n_blocks,
                              unsigned long long *queue, Slot *slots, hipStream_t stream);

@@ -1206,6 +1206,37 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         }
     }
 
+    // Launches the fused kernel over prm.total_roots items: the small blocks'
+    // list of what they leave lies in the counter scratch that no large block
+    // uses (half of it, where scratch is limited), or in memory of its own; a
+    // limited call with no room for it runs large blocks alone.  A
+    // reduced waves_per_cu takes the same share of both.  q: four counters.
+    auto root_build = [&](bcdev::RootParams &prm, unsigned long long *q, bool pv) -> bc_status {
+        const uint32_t wpc = std::min(waves_per_cu, 12u);
+        const bool limited = ex.fixed || mem.cap;
+        const uint32_t room = limited ? std::max(1u, rs_blocks / 2) : rs_blocks;
+        const uint32_t n_big = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(prm.total_roots, room),
+                                                            std::max<uint64_t>(1, (uint64_t)ncu * bcdev::kRbBigPerCu * wpc / 12));
+        uint32_t n_small = (uint32_t)std::min<uint64_t>(
+            prm.total_roots, std::max<uint64_t>(1, (uint64_t)ncu * bcdev::kRbSmallPerCu * wpc / 12));
+        prm.sc = rs;
+        prm.queue = q;
+        prm.pool_head = q + 1;
+        prm.n_retry = q + 2;
+        prm.queue_big = q + 3;
+        prm.slots = d_slots;
+        if (prm.total_roots >> 32)
+            n_small = 0;
+        else if ((uint64_t)(rs_blocks - n_big) * rs.stride >= prm.total_roots)
+            prm.retry = rs.cand + (uint64_t)n_big * rs.stride;
+        else if (!limited)
+            BC_HIP(mem.get(&prm.retry, prm.total_roots));
+        else
+            n_small = 0;
+        BC_HIP(bcdev::launch_root_build(prm, n_small, n_big, pv, st));
+        return BC_OK;
+    };
+
     // 4a. Specs with both anchors as candidates: estimate each side's
     //     planning cost from a rank-stratified sample of its roots
     //     (kSampleChunk consecutive ranks out of every kSamplePeriod), counted
@@ -1226,17 +1257,15 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             const uint64_t span = (uint64_t)(jobs[a].root_hi - jobs[a].root_lo) + (jobs[b].root_hi - jobs[b].root_lo);
             if (span < kSampleMinRoots) continue;
             for (int j : {a, b}) {
-                for (uint64_t c = jobs[j].root_lo; c < jobs[j].root_hi; c += kSamplePeriod) {
-                    bcdev::Job sj = hjobs[j];
-                    sj.root_lo = (uint32_t)c;
-                    sj.root_hi = (uint32_t)std::min<uint64_t>(c + kSampleChunk, jobs[j].root_hi);
-                    sj.pA = 2;
-                    sj.slot = nj;
-                    sj.pv = nullptr;
-                    sjobs.push_back(sj);
-                    sowner.push_back((uint32_t)j);
-                    sprefix.push_back(sprefix.back() + (sj.root_hi - sj.root_lo));
-                }
+                const uint64_t n = jobs[j].root_hi - jobs[j].root_lo;
+                bcdev::Job sj = hjobs[j];
+                sj.pA = 2;
+                sj.slot = nj;
+                sj.pv = nullptr;
+                sjobs.push_back(sj);
+                sowner.push_back((uint32_t)j);
+                sprefix.push_back(sprefix.back() + n / kSamplePeriod * kSampleChunk +
+                                  std::min<uint64_t>(n % kSamplePeriod, kSampleChunk));
             }
         }
         if (!sjobs.empty()) {
@@ -1250,11 +1279,18 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             BC_HIP(mem.get(&d_spool, 1));
             BC_HIP(hipMemcpyAsync(d_sj, sjobs.data(), sjobs.size() * sizeof(bcdev::Job), hipMemcpyHostToDevice, st));
             BC_HIP(hipMemcpyAsync(d_sp, sprefix.data(), sprefix.size() * 8, hipMemcpyHostToDevice, st));
-            const uint32_t s_blocks = (uint32_t)std::min<uint64_t>(
-                std::min<uint64_t>(s_roots, rs_blocks),
-                std::max<uint64_t>(1, (uint64_t)ncu * std::min(waves_per_cu, 12u) / 12));
-            BC_HIP(bcdev::launch_root_build(d_sj, d_sp, (uint32_t)sjobs.size(), s_roots, rs, d_spool, 1, s_blocks,
-                                            d_queue + 6, d_sout, d_slots, false, st));
+            bcdev::RootParams rp{};
+            rp.jobs = d_sj;
+            rp.job_root_prefix = d_sp;
+            rp.n_jobs = (uint32_t)sjobs.size();
+            rp.run = kSampleChunk;
+            rp.period = kSamplePeriod;
+            rp.total_roots = s_roots;
+            rp.pool = d_spool;
+            rp.pool_cap = 1;
+            rp.out = d_sout;
+            const bc_status bs = root_build(rp, d_queue + 22, false);
+            if (bs != BC_OK) return bs;
             std::vector<bcdev::RootOut> sout(s_roots);
             BC_HIP(hipMemcpyAsync(sout.data(), d_sout, s_roots * sizeof(bcdev::RootOut), hipMemcpyDeviceToHost, st));
             BC_HIP(hipStreamSynchronize(st));
@@ -1265,7 +1301,8 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 const uint32_t e = std::min<uint32_t>(jobs[j].pA - 1, 3);
                 for (uint64_t r = sprefix[s]; r < sprefix[s + 1]; ++r) {
                     const double k = sout[r].k;
-                    const uint64_t u = sjobs[s].root_lo + (r - sprefix[s]);
+                    const uint64_t x0 = r - sprefix[s];
+                    const uint64_t u = sjobs[s].root_lo + x0 / kSampleChunk * kSamplePeriod + x0 % kSampleChunk;
                     seen[j] += 1.0;
                     if (k < jobs[j].pA - 1) continue;
                     double x = k * (double)((A.h_ptr[u + 1] - A.h_ptr[u] + 63) / 64);
@@ -1334,14 +1371,19 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             // roots that find no room are rebuilt into an exactly sized pool
             if (ex.fixed || mem.cap) pool_cap = std::max<uint64_t>(1, std::min<uint64_t>(pool_cap, mem.room() / 3 / 8));
             BC_HIP(mem.get(&d_pool_fused, pool_cap));
-            // one block of kRbThreads per CU (its LDS table takes most of the
-            // CU's LDS); a reduced waves_per_cu takes the same share of CUs
-            const uint32_t fused_blocks = (uint32_t)std::min<uint64_t>(
-                std::min<uint64_t>(total_roots, rs_blocks),
-                std::max<uint64_t>(1, (uint64_t)ncu * std::min(waves_per_cu, 12u) / 12));
+            bcdev::RootParams rp{};
+            rp.jobs = d_cjobs;
+            rp.job_root_prefix = d_rp;
+            rp.n_jobs = (uint32_t)cj.size();
+            rp.total_roots = total_roots;
+            rp.pool = d_pool_fused;
+            rp.pool_cap = pool_cap;
+            // a limited pool is not reserved ahead of need
+            rp.chunk = ex.fixed || mem.cap ? 0 : 4096;
+            rp.out = d_found;
             // per-vertex counts of p_A = 2 jobs are attributed by this pass
-            BC_HIP(bcdev::launch_root_build(d_cjobs, d_rp, (uint32_t)cj.size(), total_roots, rs, d_pool_fused, pool_cap,
-                                            fused_blocks, d_queue + 4, d_found, d_slots, any_pv, st));
+            const bc_status bs = root_build(rp, d_queue + 4, any_pv);
+            if (bs != BC_OK) return bs;
         } else {
             BC_HIP(bcdev::launch_cand_count(d_cjobs, d_rp, (uint32_t)cj.size(), total_roots, rs, root_blocks,
                                             d_queue + 0, d_found, d_slots, st));

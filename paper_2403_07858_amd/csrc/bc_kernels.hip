@@ -579,52 +579,57 @@ hipError_t launch_rows_build(const Job *jobs, const ActiveRoot *roots, uint32_t 
 
 // ---------------------------------------------------------------------------
 // k_root_build: the candidate count and the candidate rows of every root in
-// one kernel, one root per block of kRbWaves waves at a time.
+// one kernel, one root per block of NW waves at a time.
 //
-// The 2-hop vertices of u live in an LDS open-addressing table (key w + 1,
-// linear probing).  When u has at most 64 neighbours (one row word), the
-// table entry accumulates w's row itself -- v_j's column set for the wedge
-// u - v_j - w -- so one wedge pass yields both |N(u) n N(w)| (the popcount)
-// and the row.
-// Wider roots count in the first pass, index their candidates, and set the
-// row bits in a second pass into LDS (or the pool when the rows do not fit).
-// Roots whose 2-hop set overflows the table fall back to the per-block dense
-// counter array in HBM.  Row storage is taken from the pool with one atomic
-// bump per root, so counting and row building need no host round trip.
+// The 2-hop vertices of u live in an LDS open-addressing table of SLOTS
+// entries (key w + 1, linear probing).  A small block's entry of a root with at
+// most 64 neighbours (one row word) accumulates w's row itself -- v_j's column
+// set for the wedge u - v_j - w -- so one wedge pass yields both
+// |N(u) n N(w)| (the popcount) and the row.  Wider roots, and all of a large
+// block's, count in the first pass, index their candidates, and set the row
+// bits in a second pass in LDS, a group of row words at a time.  Row storage is
+// taken from the pool by bumping a chunk the block reserved, so counting and
+// row building need no host round trip.
+//
+// What bounds it is the chain of latencies of a root: its queue ticket, the
+// offsets of its neighbours' rows, the wedges, the scans between barriers.  So
+// it runs twice: blocks of four waves with a small table, five to a CU, which
+// take the roots whose 2-hop vertices fit and list the others (BIG false); then
+// blocks of eight waves, two to a CU, over that list, with 16-bit counts.  A
+// job's fields and leaf values are read when the job changes.  Against one
+// block of sixteen waves a CU for every root, one ticket a root and a sort of
+// each root's candidates: 2M edges (4,4) 7.0 against 8.9 ms, 5M (3,3) 14.2
+// against 22.6, 1.2M (5,5) 3.2 against 4.5, 256 small graphs 3.6 against 17.4,
+// 150k edges 0.44 against 0.79 ms.
 
-constexpr uint32_t kHashSlots = 8192;       // LDS table entries
+constexpr uint32_t kHashSlots = 8192;       // LDS table entries of the large blocks
+constexpr uint32_t kSmallSlots = 2048;      // and of the small ones
+constexpr uint32_t kBigRowBuf = 3072;       // words of rows a large block builds at once
+constexpr uint32_t kSmallDistinct = 1500;   // 2-hop vertices a small table is tried for
+constexpr uint32_t kSmallCap = 1800;        // and holds
 constexpr uint32_t kHashProbes = 128;       // longest probe sequence before falling back
-constexpr uint32_t kSlotsPerThread = kHashSlots / kRbThreads;
 constexpr uint16_t kNoRow = 0xffffu;
 constexpr uint32_t kHintDistinct = 8192;    // 2-hop vertices above which the next root starts with id ranges
 constexpr uint32_t kCapRange = 5120;        // distinct 2-hop vertices of one id range
 constexpr uint32_t kRowsCap = 4096;         // candidates of a root counted by id ranges
+constexpr uint32_t kLeafLen = 256;          // leaf values kept in LDS
+constexpr uint32_t kListed = 32;            // roots a small block lists at once
 
-__device__ __forceinline__ uint32_t hash_slot(uint32_t w) { return (w * 0x9E3779B1u) >> (32 - 13); }
-
-// Slot of w, inserting it if new; -1 when the probe limit is reached.
-__device__ __forceinline__ int hash_insert(uint32_t *key, uint32_t w)
+template <uint32_t SLOTS>
+__device__ __forceinline__ uint32_t hash_slot(uint32_t w)
 {
-    const uint32_t kv = w + 1u;
-    uint32_t h = hash_slot(w);
-    for (uint32_t p = 0; p < kHashProbes; ++p, h = (h + 1) & (kHashSlots - 1)) {
-        const uint32_t e = key[h];
-        if (e == kv) return (int)h;
-        if (e == 0u) {
-            const uint32_t old = atomicCAS(&key[h], 0u, kv);
-            if (old == 0u || old == kv) return (int)h;
-        }
-    }
-    return -1;
+    return (w * 0x9E3779B1u) >> (32 - __builtin_ctz(SLOTS));
 }
 
-// As hash_insert; *fresh tells whether this call claimed the slot.
-__device__ __forceinline__ int hash_insert_new(uint32_t *key, uint32_t w, bool *fresh)
+// Slot of w, inserting it if new; -1 when the probe limit is reached.  *fresh
+// tells whether this call claimed the slot.
+template <uint32_t SLOTS>
+__device__ __forceinline__ int hash_insert(uint32_t *key, uint32_t w, bool *fresh)
 {
     const uint32_t kv = w + 1u;
-    uint32_t h = hash_slot(w);
+    uint32_t h = hash_slot<SLOTS>(w);
     *fresh = false;
-    for (uint32_t p = 0; p < kHashProbes; ++p, h = (h + 1) & (kHashSlots - 1)) {
+    for (uint32_t p = 0; p < kHashProbes; ++p, h = (h + 1) & (SLOTS - 1)) {
         const uint32_t e = key[h];
         if (e == kv) return (int)h;
         if (e == 0u) {
@@ -640,29 +645,32 @@ __device__ __forceinline__ int hash_insert_new(uint32_t *key, uint32_t w, bool *
 }
 
 // Slot of w, or -1 when w is absent (the table must have an empty slot).
+template <uint32_t SLOTS>
 __device__ __forceinline__ int hash_lookup(const uint32_t *key, uint32_t w)
 {
     const uint32_t kv = w + 1u;
-    uint32_t h = hash_slot(w);
+    uint32_t h = hash_slot<SLOTS>(w);
     for (;;) {
         const uint32_t e = key[h];
         if (e == kv) return (int)h;
         if (e == 0u) return -1;
-        h = (h + 1) & (kHashSlots - 1);
+        h = (h + 1) & (SLOTS - 1);
     }
 }
 
 // Slot of w (w must be present).
+template <uint32_t SLOTS>
 __device__ __forceinline__ uint32_t hash_find(const uint32_t *key, uint32_t w)
 {
     const uint32_t kv = w + 1u;
-    uint32_t h = hash_slot(w);
-    while (key[h] != kv) h = (h + 1) & (kHashSlots - 1);
+    uint32_t h = hash_slot<SLOTS>(w);
+    while (key[h] != kv) h = (h + 1) & (SLOTS - 1);
     return h;
 }
 
-// Exclusive prefix of v over the block (thread order); *total gets the sum.
-// Uses s_wsum[kRbWaves]; the caller separates consecutive uses by a barrier.
+// Exclusive prefix of v over a block of NW waves (thread order); *total gets
+// the sum.  Uses s_wsum[NW]; the caller separates consecutive uses by a barrier.
+template <int NW>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wsum, uint32_t *total)
 {
     const uint32_t wv = threadIdx.x / kWaveSize;
@@ -671,7 +679,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wsum
     __syncthreads();
     uint32_t before = 0, tot = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < (uint32_t)kRbWaves; ++w) {
+    for (uint32_t w = 0; w < (uint32_t)NW; ++w) {
         const uint32_t t = s_wsum[w];
         before += w < wv ? t : 0u;
         tot += t;
@@ -682,38 +690,68 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wsum
 
 // PV: per-vertex counts for p_A = 2 jobs that ask for them (each leaf {u, w}
 // adds its C(|N(u) n N(w)|, q_A) to w at once and, summed per wave, to u).
-template <bool PV>
-__global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, const uint64_t *job_root_prefix,
-                                                           uint32_t n_jobs, uint64_t total_roots, RootScratch sc,
-                                                           uint64_t *pool, uint64_t pool_cap,
-                                                           unsigned long long *counters, RootOut *out,
-                                                           Slot *slots)
+template <bool PV, int NW, uint32_t SLOTS>
+__global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k_root_build(RootParams prm)
 {
-    __shared__ uint32_t s_key[kHashSlots];               // w + 1, 0 = empty
-    __shared__ unsigned long long s_row[kHashSlots];     // row word or count of the slot; later LDS rows
-    __shared__ uint16_t s_map[kHashSlots];               // row index of the slot's vertex, kNoRow if none
-    __shared__ uint32_t s_sort[kHashSlots];              // candidates being sorted
-    __shared__ uint32_t s_wsum[kRbWaves];
+    constexpr bool BIG = SLOTS == kHashSlots;
+    constexpr uint32_t NT = NW * kWaveSize, PER = SLOTS / NT;   // threads; slots of each in the scans
+    constexpr uint32_t BUF = BIG ? kBigRowBuf : SLOTS;
+    static_assert(!BIG || 2 * BUF >= kRowsCap);
+    __shared__ uint32_t s_key[SLOTS];                 // w + 1, 0 = empty
+    __shared__ unsigned long long s_row[BUF];         // small: row word or count of the slot; LDS rows
+    __shared__ __align__(4) uint16_t s_map[SLOTS];    // row index of the slot's vertex, kNoRow if none;
+                                                      // large: the slot's count before that
+    uint32_t *s_sort = (uint32_t *)s_row;             // large: candidates being sorted (id ranges)
+    __shared__ uint32_t s_bkt[NT];                  // candidates by rank interval
+    __shared__ uint64_t s_leaf[kLeafLen];           // C(n, qA) below 2^64
+    __shared__ uint32_t s_wsum[NW];
+    __shared__ uint32_t s_listed[BIG ? 1 : kListed];  // roots for the large blocks
     __shared__ unsigned long long s_item, s_off, s_bits;
     __shared__ uint32_t s_k, s_nt, s_flag, s_claimed;
-    unsigned long long *queue = counters;        // roots
-    unsigned long long *pool_head = counters + 1;
-    uint32_t *cnt = sc.cnt + (uint64_t)blockIdx.x * sc.stride;
-    uint32_t *touched = sc.touched + (uint64_t)blockIdx.x * sc.stride;
-    uint32_t *cand_g = sc.cand + (uint64_t)blockIdx.x * sc.stride;
+    const Job *jobs = prm.jobs;
+    Slot *slots = prm.slots;
+    uint64_t *pool = prm.pool;
     const uint32_t tid = threadIdx.x;
-    const uint32_t h0 = tid * kSlotsPerThread;   // this thread's slots in the per-root scans
-    for (uint32_t x = tid; x < kHashSlots; x += kRbThreads) {
-        s_key[x] = 0;
-        s_row[x] = 0;
-    }
+    if (prm.list && *prm.n_list == 0) return;
+    auto clear_table = [&] {
+        for (uint32_t x = tid; x < SLOTS; x += NT) {
+            s_key[x] = 0;
+            if constexpr (!BIG) s_row[x] = 0;
+            else if (x < SLOTS / 2) ((uint32_t *)s_map)[x] = 0;
+        }
+    };
+    clear_table();
     u128 acc = 0;
     bool ovf = false;
     uint32_t cur_job = 0xffffffffu;
-    uint32_t parts_hint = 1;   // id ranges the previous root needed
+    uint64_t job_lo = 1, job_hi = 0;   // roots of the current job
+    uint32_t leaf_len = 0;             // entries of s_leaf
+    Job jb{};
+    uint32_t parts_hint = 1;           // id ranges the previous root needed
+    float per_wedge = 0.0f;            // 2-hop vertices per wedge of the previous root
+    // thread 0's: pool words reserved, items taken, the next ticket, roots listed
+    unsigned long long chunk_at = 0, chunk_end = 0, at = 0, at_end = 0, ticket = 0;
+    uint32_t n_listed = 0;
+    if (tid == 0) ticket = atomicAdd(prm.queue, 1ull);
+    const unsigned long long n_items = prm.list ? *prm.n_list : prm.total_roots;
+    // A ticket is up to eight roots: the queue's atomics go one after another,
+    // about 20 ns each (100k roots at one a ticket: 2.3 ms, whatever they held).
+    const uint32_t batch = (uint32_t)max(1ull, min(8ull, n_items / (8ull * gridDim.x)));
+    auto flush_listed = [&] {
+        const unsigned long long o = atomicAdd(prm.n_retry, (unsigned long long)n_listed);
+        for (uint32_t x = 0; x < n_listed; ++x) prm.retry[o + x] = s_listed[x];
+        n_listed = 0;
+    };
     for (;;) {
         if (tid == 0) {
-            s_item = atomicAdd(queue, 1ull);
+            const bool fetch = at == at_end;
+            if (fetch) {
+                at = ticket * batch;
+                at_end = min(at + batch, n_items);
+            }
+            s_item = at >= n_items ? ~0ull : prm.list ? (unsigned long long)prm.list[at] : at;
+            if (fetch) ticket = atomicAdd(prm.queue, 1ull);
+            ++at;
             s_k = 0;
             s_nt = 0;
             s_flag = 0;
@@ -723,58 +761,164 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
         }
         __syncthreads();
         const uint64_t item = s_item;
-        if (item >= total_roots) break;
-        const uint32_t j = find_segment(job_root_prefix, n_jobs, item);
-        if (j != cur_job) {
-            if (cur_job != 0xffffffffu) wave_flush(slots, jobs[cur_job].slot, acc, ovf, 0, 0);
+        if (item == ~0ull) break;
+        if (item < job_lo || item >= job_hi) {
+            const uint32_t j = find_segment(prm.job_root_prefix, prm.n_jobs, item);
+            job_lo = prm.job_root_prefix[j];
+            job_hi = prm.job_root_prefix[j + 1];
+            if (cur_job != 0xffffffffu) wave_flush(slots, jb.slot, acc, ovf, 0, 0);
             acc = 0;
             ovf = false;
             cur_job = j;
+            jb = jobs[j];
+            per_wedge = 0.0f;
+            if (jb.pA == 2) {
+                leaf_len = min(jb.n_u64 + 1, kLeafLen);
+                for (uint32_t n = tid; n < leaf_len; n += NT) s_leaf[n] = (uint64_t)jb.binom[n];
+            }
         }
-        const Job jb = jobs[j];
-        const uint32_t u = jb.root_lo + (uint32_t)(item - job_root_prefix[j]);
+        const uint32_t i_job = (uint32_t)(item - job_lo);
+        const uint32_t u = jb.root_lo + (prm.run ? i_job / prm.run * prm.period + i_job % prm.run : i_job);
         const uint64_t ub = jb.ptrA[u];
         const uint32_t du = (uint32_t)(jb.ptrA[u + 1] - ub);
         const uint32_t W1 = (du + 63) >> 6;
-        // one thread reads the clock so that the whole block takes the same branch
-        if (tid == 0 && past_deadline(jb.deadline)) {
-            s_flag = 4;
-            atomicOr(&slots[jb.slot].flags, FLAG_TIMEOUT);
+        if (jb.deadline) {
+            // one thread reads the clock so that the whole block takes the same branch
+            if (tid == 0 && past_deadline(jb.deadline)) {
+                s_flag = 4;
+                atomicOr(&slots[jb.slot].flags, FLAG_TIMEOUT);
+            }
+            __syncthreads();
         }
-        __syncthreads();
         if (du < jb.qA || s_flag == 4) {
-            if (tid == 0) out[item] = RootOut{~0ull, 0u, 0u};
+            if (tid == 0) prm.out[item] = RootOut{~0ull, 0u, 0u};
             __syncthreads();
             continue;
         }
-        const bool one = W1 == 1;
+        const bool one = !BIG && W1 == 1;
         const bool rows = jb.pA >= 3;
-        u128 rsum = 0;   // PV: this thread's part of the root's leaves
+        u128 rsum = 0;       // PV: this thread's part of the root's leaves
         uint64_t bits = 0;   // row bits of this thread's candidates
+        // a candidate's leaf (p_A = 2)
+        auto leaf = [&](uint32_t w, uint32_t c) {
+            u128 x = 0;
+            if (c < leaf_len) x = s_leaf[c];
+            else if (c < jb.n_ovf) x = jb.binom[c];
+            else ovf = true;
+            ovf |= __builtin_add_overflow(acc, x, &acc);
+            if constexpr (PV) {
+                if (jb.pv && c < jb.n_ovf) {
+                    pv_add(jb.pv, w, x);
+                    rsum += x;
+                }
+            }
+        };
+        // rows of need words: from the block's chunk, or a new one, or as they are
+        auto take_rows = [&](unsigned long long need) {
+            if (chunk_end - chunk_at < need) {
+                const unsigned long long want = need > prm.chunk ? need : prm.chunk;
+                const unsigned long long o = atomicAdd(prm.pool_head, want);
+                if (o + want > prm.pool_cap) {
+                    chunk_at = chunk_end = 0;
+                    if (o + need <= prm.pool_cap) s_off = o;
+                    return;
+                }
+                chunk_at = o;
+                chunk_end = o + want;
+            }
+            s_off = chunk_at;
+            chunk_at += need;
+        };
+        // The rows' bits, from a second wedge pass: groups of row planes that
+        // fit the LDS, each from its own 64-neighbour runs, so that no wedge is
+        // met twice and no bit is set in memory.  find(w): the row of w or kNoRow.
+        auto rows_by_planes = [&](uint32_t k, uint64_t off, auto find) {
+            // (more rows than fit: one plane at a time, in parts)
+            const uint32_t group = max(BUF / k, 1u);
+            for (uint32_t p0 = 0; p0 < W1; p0 += group) {
+                const uint32_t p1 = min(W1, p0 + group);
+                // bit jj stands for neighbour du - 1 - jj
+                const uint32_t jlo = du - min(du, p1 * 64u), jhi = du - p0 * 64u;
+                for (uint32_t m0 = 0; m0 < k; m0 += BUF) {
+                    const uint32_t words = min((p1 - p0) * k - m0, BUF);
+                    for (uint32_t x = tid; x < words; x += NT) s_row[x] = 0;
+                    __syncthreads();
+                    wedges_flat<NW>(jb, ub + jlo, jhi - jlo, [&](uint32_t jj, uint32_t w) {
+                        const uint32_t m = find(w);
+                        const uint32_t x = (jj >> 6) * k + m - m0;
+                        if (m != kNoRow && x < words) atomicOr(&s_row[x], 1ull << (jj & 63));
+                    });
+                    __syncthreads();
+                    for (uint32_t x = tid; x < words; x += NT) pool[off + (uint64_t)p0 * k + m0 + x] = s_row[x];
+                    __syncthreads();
+                }
+            }
+        };
+        volatile uint32_t *flag = &s_flag;
+        // large blocks: the slot's 16-bit count, two to a word (du < 2^16)
+        auto count_one = [&](int h) { atomicAdd((uint32_t *)s_map + (h >> 1), 1u << (16 * (h & 1))); };
+        bool in_lds = false;
+        if constexpr (!BIG) {
+            // wedges of the root: every wave sums them over its lanes
+            uint32_t wedges = 0;
+            if (jb.nA - u - 1u > kSmallDistinct) {
+                for (uint32_t j = lane_id(); j < du; j += kWaveSize) {
+                    const uint32_t v = jb.adjA[ub + j];
+                    wedges += (uint32_t)(jb.ptrB[v + 1] - (jb.ptrB[v] + jb.rposA[ub + j] + 1));
+                }
+                wedges = (uint32_t)wave_sum_u64(wedges);
+                wedges = (uint32_t)__builtin_amdgcn_readfirstlane((int)wedges);
+            }
+            // more 2-hop vertices than the table is for, by the previous
+            // root's ratio (neighbouring ranks are alike): a large block's
+            const bool try_it = (float)wedges * per_wedge <= (float)kSmallDistinct;
+            if (try_it) {
+                wedges_flat_capped<NW, true>(jb, ub, du, kSmallCap, &s_claimed, flag, [&](uint32_t jj, uint32_t w) {
+                    bool fresh;
+                    const int h = hash_insert<SLOTS>(s_key, w, &fresh);
+                    if (h < 0) *flag = 1u;
+                    else if (one) atomicOr(&s_row[h], 1ull << jj);
+                    else atomicAdd(&s_row[h], 1ull);
+                    return fresh;
+                });
+                __syncthreads();
+                in_lds = s_flag == 0;
+                if (wedges) per_wedge = (float)(in_lds ? s_claimed : 2 * SLOTS) / (float)wedges;
+            } else {
+                per_wedge *= 0.98f;   // so that a change of the ratio is found out
+            }
+            if (!in_lds) {
+                if (tid == 0) {
+                    s_listed[n_listed++] = (uint32_t)item;
+                    if (n_listed == kListed) flush_listed();
+                }
+                __syncthreads();
+                if (try_it) clear_table();
+                __syncthreads();
+                continue;
+            }
+        }
 
         // pass 1: insert every 2-hop vertex; one-word roots OR in the row bit,
         // wider ones count.  It gives up at the first insert that finds no
         // slot within kHashProbes, and is skipped when the previous root of
         // this block needed several id ranges.
-        volatile uint32_t *flag = &s_flag;
-        bool in_lds = false;
-        if (parts_hint == 1) {
-            wedges_flat_capped<kRbWaves, false>(jb, ub, du, 0, &s_claimed, flag, [&](uint32_t jj, uint32_t w) {
-                const int h = hash_insert(s_key, w);
+        if (BIG && parts_hint == 1 && du < 65536u) {
+            wedges_flat_capped<NW, false>(jb, ub, du, 0, &s_claimed, flag, [&](uint32_t, uint32_t w) {
+                bool fresh;
+                const int h = hash_insert<SLOTS>(s_key, w, &fresh);
                 if (h < 0) *flag = 1u;
-                else if (one) atomicOr(&s_row[h], 1ull << jj);
-                else atomicAdd(&s_row[h], 1ull);
+                else count_one(h);
                 return false;
             });
             __syncthreads();
             in_lds = s_flag == 0;
-            if (in_lds) parts_hint = 1;
         }
         uint32_t k = 0;
         uint64_t off = ~0ull;
         bool build = false;
         bool done = in_lds;
-        if (!in_lds) {
+        if (BIG && !in_lds && du < 65536u) {
             // The candidates are the ids above u.  Take them in id ranges, each
             // counted in a fresh table of at most kCapRange distinct vertices;
             // a range that passes it is halved and counted again, and the width
@@ -786,25 +930,21 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
             bool fits = true;
             while (lo < jb.nA) {
                 const uint32_t hi = lo + (width < jb.nA - lo ? width : jb.nA - lo);
-                for (uint32_t x = tid; x < kHashSlots; x += kRbThreads) {
-                    s_key[x] = 0;
-                    s_row[x] = 0;
-                }
+                clear_table();
                 if (tid == 0) {
                     s_flag = 0;
                     s_claimed = 0;
                 }
                 __syncthreads();
-                wedges_flat_capped<kRbWaves, true>(jb, ub, du, kCapRange, &s_claimed, flag, [&](uint32_t jj, uint32_t w) {
+                wedges_flat_capped<NW, true>(jb, ub, du, kCapRange, &s_claimed, flag, [&](uint32_t, uint32_t w) {
                     if (w < lo || w >= hi) return false;
                     bool fresh;
-                    const int h = hash_insert_new(s_key, w, &fresh);
+                    const int h = hash_insert<SLOTS>(s_key, w, &fresh);
                     if (h < 0) {
                         *flag = 1u;
                         return false;
                     }
-                    if (one) atomicOr(&s_row[h], 1ull << jj);
-                    else atomicAdd(&s_row[h], 1ull);
+                    count_one(h);
                     return fresh;
                 });
                 __syncthreads();
@@ -817,37 +957,27 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
                 }
                 distinct += d;
                 uint32_t mine = 0;
-#pragma unroll
-                for (uint32_t i = 0; i < kSlotsPerThread; ++i) {
-                    const uint32_t h = h0 + i;
-                    const unsigned long long e = s_row[h];
-                    const uint32_t c = one ? (uint32_t)__popcll(e) : (uint32_t)e;
+#pragma unroll 4
+                for (uint32_t i = 0; i < PER; ++i) {
+                    const uint32_t h = i * NT + tid;
+                    const uint32_t c = s_map[h];
                     if (s_key[h] != 0u && c >= jb.qA) {
                         ++mine;
                         bits += c;
-                        if (rows) continue;
-                        if (c >= jb.n_ovf) ovf = true;
-                        else ovf |= __builtin_add_overflow(acc, jb.binom[c], &acc);
-                        if constexpr (PV) {
-                            if (jb.pv && c < jb.n_ovf) {
-                                pv_add(jb.pv, s_key[h] - 1u, jb.binom[c]);
-                                rsum += jb.binom[c];
-                            }
-                        }
+                        if (!rows) leaf(s_key[h] - 1u, c);
                     }
                 }
                 uint32_t kk;
-                uint32_t pos = block_excl_scan(mine, s_wsum, &kk);
+                uint32_t pos = block_excl_scan<NW>(mine, s_wsum, &kk);
                 if (rows) {
                     if (k + kk > kRowsCap) {
                         fits = false;
                         break;
                     }
-#pragma unroll
-                    for (uint32_t i = 0; i < kSlotsPerThread; ++i) {
-                        const uint32_t h = h0 + i;
-                        const unsigned long long e = s_row[h];
-                        const uint32_t c = one ? (uint32_t)__popcll(e) : (uint32_t)e;
+#pragma unroll 4
+                    for (uint32_t i = 0; i < PER; ++i) {
+                        const uint32_t h = i * NT + tid;
+                        const uint32_t c = s_map[h];
                         const uint32_t kv = s_key[h];
                         if (kv != 0u && c >= jb.qA) s_sort[k + pos++] = kv - 1u;
                     }
@@ -861,132 +991,103 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
             done = fits;
             if (fits) {
                 build = rows && k >= jb.pA - 1;
-                if (build && tid == 0) {
-                    const unsigned long long need = (unsigned long long)k * W1;
-                    const unsigned long long o = atomicAdd(pool_head, need);
-                    if (o + need <= pool_cap) s_off = o;
-                }
+                if (build && tid == 0) take_rows((unsigned long long)k * W1);
                 __syncthreads();
                 off = s_off;
                 if (build && off != ~0ull) {
                     // rows in increasing id order; a table of the candidates alone
                     // (at most half full) maps an id to its row
-                    block_sort_u32<kRbThreads>(s_sort, k);
-                    for (uint32_t x = tid; x < kHashSlots; x += kRbThreads) s_key[x] = 0;
+                    block_sort_u32<NT>(s_sort, k);
+                    for (uint32_t x = tid; x < SLOTS; x += NT) s_key[x] = 0;
                     __syncthreads();
-                    for (uint32_t x = tid; x < k; x += kRbThreads) {
+                    for (uint32_t x = tid; x < k; x += NT) {
                         const uint32_t kv = s_sort[x] + 1u;
-                        uint32_t h = hash_slot(kv - 1u);
-                        while (atomicCAS(&s_key[h], 0u, kv) != 0u) h = (h + 1) & (kHashSlots - 1);
+                        uint32_t h = hash_slot<SLOTS>(kv - 1u);
+                        while (atomicCAS(&s_key[h], 0u, kv) != 0u) h = (h + 1) & (SLOTS - 1);
                         s_map[h] = (uint16_t)x;
                     }
-                    const uint64_t words = (uint64_t)k * W1;
-                    const bool lds_rows = words <= kHashSlots;
-                    if (lds_rows)
-                        for (uint32_t x = tid; x < words; x += kRbThreads) s_row[x] = 0;
-                    else
-                        for (uint64_t x = tid; x < words; x += kRbThreads) pool[off + x] = 0;
-                    __threadfence();
-                    __syncthreads();
-                    wedges_flat<kRbWaves>(jb, ub, du, [&](uint32_t jj, uint32_t w) {
-                        const int h = hash_lookup(s_key, w);
-                        if (h >= 0) {
-                            const uint64_t x = (uint64_t)(jj >> 6) * k + s_map[h];
-                            if (lds_rows) atomicOr(&s_row[x], 1ull << (jj & 63));
-                            else atomicOr((unsigned long long *)&pool[off + x], 1ull << (jj & 63));
-                        }
+                    __syncthreads();   // s_sort has been read
+                    rows_by_planes(k, off, [&](uint32_t w) {
+                        const int h = hash_lookup<SLOTS>(s_key, w);
+                        return h >= 0 ? (uint32_t)s_map[h] : (uint32_t)kNoRow;
                     });
-                    __syncthreads();
-                    if (lds_rows)
-                        for (uint32_t x = tid; x < words; x += kRbThreads) pool[off + x] = s_row[x];
                 }
             } else {
                 k = 0;
             }
         }
         if (in_lds) {
-            // candidates: count >= qA, indexed in slot order (pA == 2 sums its leaves here)
+            // candidates: count >= qA (pA == 2 sums its leaves here).  Their
+            // rows go in the order of NT rank intervals, and in slot order
+            // within one: close to the rank order, in which a search that
+            // starts at a candidate has few neighbours before it and the
+            // hubs behind it.
+            const uint32_t span = jb.nA - u;
+            uint32_t sh = 0;
+            while ((span >> sh) >= NT) ++sh;
+            if (rows) {
+                s_bkt[tid] = 0;
+                __syncthreads();
+            }
             uint32_t mine = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < kSlotsPerThread; ++i) {
-                const uint32_t h = h0 + i;
-                const unsigned long long e = s_row[h];
-                const uint32_t c = one ? (uint32_t)__popcll(e) : (uint32_t)e;
-                if (s_key[h] != 0u && c >= jb.qA) {
+#pragma unroll 4
+            for (uint32_t i = 0; i < PER; ++i) {
+                const uint32_t h = i * NT + tid;
+                uint32_t c;
+                if constexpr (BIG) c = s_map[h];
+                else c = one ? (uint32_t)__popcll(s_row[h]) : (uint32_t)s_row[h];
+                const uint32_t kv = s_key[h];
+                const bool cand = kv != 0u && c >= jb.qA;
+                if (rows && !one) s_map[h] = cand ? 0u : kNoRow;
+                if (cand) {
                     ++mine;
                     bits += c;
-                    if (rows) continue;
-                    if (c >= jb.n_ovf) ovf = true;
-                    else ovf |= __builtin_add_overflow(acc, jb.binom[c], &acc);
-                    if constexpr (PV) {
-                        if (jb.pv && c < jb.n_ovf) {
-                            pv_add(jb.pv, s_key[h] - 1u, jb.binom[c]);
-                            rsum += jb.binom[c];
-                        }
-                    }
+                    if (rows) atomicAdd(&s_bkt[(kv - 1u - u) >> sh], 1u);
+                    else leaf(kv - 1u, c);
                 }
             }
-            uint32_t pos = block_excl_scan(mine, s_wsum, &k);
-            build = rows && k >= jb.pA - 1;
-            if (build && tid == 0) {
-                const unsigned long long need = (unsigned long long)k * W1;
-                const unsigned long long o = atomicAdd(pool_head, need);
-                if (o + need <= pool_cap) s_off = o;
+            if (!rows) {
+                block_excl_scan<NW>(mine, s_wsum, &k);
+            } else {
+                __syncthreads();
+                const uint32_t at = block_excl_scan<NW>(s_bkt[tid], s_wsum, &k);
+                s_bkt[tid] = at;
+                build = k >= jb.pA - 1;
+                if (build && tid == 0) take_rows((unsigned long long)k * W1);
+                __syncthreads();
+                off = s_off;
             }
-            __syncthreads();
-            off = s_off;
             if (build && off != ~0ull) {
-                // rows in increasing rank order of the candidates: list and sort them
-#pragma unroll
-                for (uint32_t i = 0; i < kSlotsPerThread; ++i) {
-                    const uint32_t h = h0 + i;
-                    const unsigned long long e = s_row[h];
-                    const uint32_t c = one ? (uint32_t)__popcll(e) : (uint32_t)e;
-                    const uint32_t kv = s_key[h];
-                    const bool cand = kv != 0u && c >= jb.qA;
-                    if (cand) s_sort[pos++] = kv - 1u;
-                    if (!one) s_map[h] = kNoRow;
-                }
-                block_sort_u32<kRbThreads>(s_sort, k);
                 // one-word roots write their rows now; wider ones record the row index
-                for (uint32_t x = tid; x < k; x += kRbThreads) {
-                    const uint32_t h = hash_find(s_key, s_sort[x]);
-                    if (one) pool[off + x] = s_row[h];
+#pragma unroll 4
+                for (uint32_t i = 0; i < PER; ++i) {
+                    const uint32_t h = i * NT + tid;
+                    const uint32_t kv = s_key[h];
+                    const unsigned long long e = one ? s_row[h] : 0ull;
+                    const bool cand = one ? kv != 0u && (uint32_t)__popcll(e) >= jb.qA : s_map[h] != kNoRow;
+                    if (!cand) continue;
+                    const uint32_t x = atomicAdd(&s_bkt[(kv - 1u - u) >> sh], 1u);
+                    if (one) pool[off + x] = e;
                     else s_map[h] = (uint16_t)x;
                 }
                 if (!one) {
-                    const uint64_t words = (uint64_t)k * W1;
-                    const bool lds_rows = words <= kHashSlots;
                     __syncthreads();   // every count has been read
-                    if (lds_rows)
-                        for (uint32_t x = tid; x < words; x += kRbThreads) s_row[x] = 0;
-                    else
-                        for (uint64_t x = tid; x < words; x += kRbThreads) pool[off + x] = 0;
-                    __threadfence();
-                    __syncthreads();
-                    // pass 2: set v_j's column bit of row(w) for every wedge u - v_j - w with w a candidate
-                    wedges_flat<kRbWaves>(jb, ub, du, [&](uint32_t jj, uint32_t w) {
-                        const uint32_t m = s_map[hash_find(s_key, w)];
-                        if (m != kNoRow) {
-                            const uint64_t x = (uint64_t)(jj >> 6) * k + m;
-                            if (lds_rows) atomicOr(&s_row[x], 1ull << (jj & 63));
-                            else atomicOr((unsigned long long *)&pool[off + x], 1ull << (jj & 63));
-                        }
-                    });
-                    __syncthreads();
-                    if (lds_rows)
-                        for (uint32_t x = tid; x < words; x += kRbThreads) pool[off + x] = s_row[x];
+                    rows_by_planes(k, off, [&](uint32_t w) { return (uint32_t)s_map[hash_find<SLOTS>(s_key, w)]; });
                 }
             }
         }
-        if (!done) {
+        if (BIG && !done) {
             // too many candidates for the id ranges: count again in the dense array
-            wedges_flat<kRbWaves>(jb, ub, du, [&](uint32_t, uint32_t w) {
+            uint32_t *cnt = prm.sc.cnt + (uint64_t)blockIdx.x * prm.sc.stride;
+            uint32_t *touched = prm.sc.touched + (uint64_t)blockIdx.x * prm.sc.stride;
+            uint32_t *cand_g = prm.sc.cand + (uint64_t)blockIdx.x * prm.sc.stride;
+            bits = 0;
+            wedges_flat<NW>(jb, ub, du, [&](uint32_t, uint32_t w) {
                 if (atomicAdd(&cnt[w], 1u) == 0u) touched[atomicAdd(&s_nt, 1u)] = w;
             });
             __syncthreads();
             const uint32_t nt = s_nt;
-            for (uint32_t t = tid; t < nt; t += kRbThreads) {
+            for (uint32_t t = tid; t < nt; t += NT) {
                 const uint32_t w = touched[t];
                 const uint32_t c = atomicAdd(&cnt[w], 0u);
                 if (c >= jb.qA) {
@@ -996,14 +1097,7 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
                         cand_g[s] = w;
                         atomicExch(&cnt[w], kSlotFlag | s);
                     } else {
-                        if (c >= jb.n_ovf) ovf = true;
-                        else ovf |= __builtin_add_overflow(acc, jb.binom[c], &acc);
-                        if constexpr (PV) {
-                            if (jb.pv && c < jb.n_ovf) {
-                                pv_add(jb.pv, w, jb.binom[c]);
-                                rsum += jb.binom[c];
-                            }
-                        }
+                        leaf(w, c);
                         atomicExch(&cnt[w], 0u);
                     }
                 } else {
@@ -1013,19 +1107,15 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
             __syncthreads();
             k = s_k;
             build = rows && k >= jb.pA - 1;
-            if (build && tid == 0) {
-                const unsigned long long need = (unsigned long long)k * W1;
-                const unsigned long long o = atomicAdd(pool_head, need);
-                if (o + need <= pool_cap) s_off = o;
-            }
+            if (build && tid == 0) take_rows((unsigned long long)k * W1);
             __syncthreads();
             off = s_off;
             if (build && off != ~0ull) {
                 const uint64_t words = (uint64_t)k * W1;
-                for (uint64_t x = tid; x < words; x += kRbThreads) pool[off + x] = 0;
+                for (uint64_t x = tid; x < words; x += NT) pool[off + x] = 0;
                 __threadfence();
                 __syncthreads();
-                wedges_flat<kRbWaves>(jb, ub, du, [&](uint32_t jj, uint32_t w) {
+                wedges_flat<NW>(jb, ub, du, [&](uint32_t jj, uint32_t w) {
                     const uint32_t e = atomicAdd(&cnt[w], 0u);
                     if (e & kSlotFlag)
                         atomicOr((unsigned long long *)&pool[off + (uint64_t)(jj >> 6) * k + (e & ~kSlotFlag)],
@@ -1035,7 +1125,7 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
             }
             // reset the candidates' counters
             if (rows)
-                for (uint32_t s = tid; s < k; s += kRbThreads) atomicExch(&cnt[cand_g[s]], 0u);
+                for (uint32_t s = tid; s < k; s += NT) atomicExch(&cnt[cand_g[s]], 0u);
         }
         if (build && off == ~0ull && tid == 0) atomicOr(&slots[jb.slot].flags, FLAG_POOL);
         if constexpr (PV) {
@@ -1052,28 +1142,33 @@ __global__ __launch_bounds__(kRbThreads) void k_root_build(const Job *jobs, cons
             if (lane_id() == 0 && bits) atomicAdd(&s_bits, (unsigned long long)bits);
         }
         __syncthreads();
-        if (tid == 0) out[item] = RootOut{build ? off : ~0ull, k, (uint32_t)min(s_bits, 0xffffffffull)};
-        for (uint32_t x = tid; x < kHashSlots; x += kRbThreads) {
-            s_key[x] = 0;
-            s_row[x] = 0;
-        }
+        if (tid == 0) prm.out[item] = RootOut{build ? off : ~0ull, k, (uint32_t)min(s_bits, 0xffffffffull)};
+        clear_table();
         __syncthreads();
     }
-    if (cur_job != 0xffffffffu) wave_flush(slots, jobs[cur_job].slot, acc, ovf, 0, 0);
+    if (!BIG && tid == 0 && n_listed) flush_listed();
+    if (cur_job != 0xffffffffu) wave_flush(slots, jb.slot, acc, ovf, 0, 0);
 }
 
-hipError_t launch_root_build(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
-                             uint64_t total_roots, RootScratch scratch, uint64_t *pool, uint64_t pool_cap,
-                             uint32_t n_blocks, unsigned long long *counters, RootOut *out, Slot *slots,
-                             bool per_vertex, hipStream_t stream)
+hipError_t launch_root_build(const RootParams &prm, uint32_t n_small, uint32_t n_big, bool per_vertex,
+                             hipStream_t stream)
 {
-    if (total_roots == 0) return hipSuccess;
+    if (prm.total_roots == 0) return hipSuccess;
+    RootParams p = prm;
+    if (n_small) {
+        if (per_vertex)
+            hipLaunchKernelGGL((k_root_build<true, 4, kSmallSlots>), dim3(n_small), dim3(4 * kWaveSize), 0, stream, p);
+        else
+            hipLaunchKernelGGL((k_root_build<false, 4, kSmallSlots>), dim3(n_small), dim3(4 * kWaveSize), 0, stream, p);
+        // what they listed
+        p.list = prm.retry;
+        p.n_list = prm.n_retry;
+        p.queue = prm.queue_big;
+    }
     if (per_vertex)
-        hipLaunchKernelGGL(k_root_build<true>, dim3(n_blocks), dim3(kRbThreads), 0, stream, jobs, job_root_prefix,
-                           n_jobs, total_roots, scratch, pool, pool_cap, counters, out, slots);
+        hipLaunchKernelGGL((k_root_build<true, kRbWaves, kHashSlots>), dim3(n_big), dim3(kRbThreads), 0, stream, p);
     else
-        hipLaunchKernelGGL(k_root_build<false>, dim3(n_blocks), dim3(kRbThreads), 0, stream, jobs, job_root_prefix,
-                           n_jobs, total_roots, scratch, pool, pool_cap, counters, out, slots);
+        hipLaunchKernelGGL((k_root_build<false, kRbWaves, kHashSlots>), dim3(n_big), dim3(kRbThreads), 0, stream, p);
     return hipGetLastError();
 }
 
