@@ -144,6 +144,9 @@ constexpr int kRbWaves = 8;             // waves per large block of the fused pe
 constexpr int kRbThreads = kWaveSize * kRbWaves;
 constexpr uint32_t kRbBigPerCu = 2;     // large blocks of it on a CU
 constexpr uint32_t kRbSmallPerCu = 5;   // small blocks (four waves)
+constexpr uint32_t kQueues = 16;        // counters of a task queue,
+constexpr uint32_t kQueueStride = 16;   // this many 64-bit words apart
+constexpr uint32_t kQueueWords = kQueues * kQueueStride;
 constexpr uint32_t kSlotFlag = 0x80000000u;
 
 // What the candidate pass finds of one root.

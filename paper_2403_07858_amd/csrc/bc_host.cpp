@@ -1138,7 +1138,10 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     BC_HIP(mem.get(&d_jobs, nj));
     BC_HIP(mem.get(&d_tab, tab_off[nj]));
     BC_HIP(mem.get(&d_slots, nj + 1));   // slot nj: sample jobs
-    BC_HIP(mem.get(&d_queue, 32));
+    // single counters, then the task queues of the searches' launches
+    constexpr uint32_t kSingles = 32, kTaskQueues = 6;
+    BC_HIP(mem.get(&d_queue, kSingles + kTaskQueues * bcdev::kQueueWords));
+    auto task_queue = [&](uint32_t x) { return d_queue + kSingles + x * bcdev::kQueueWords; };
     {
         std::vector<u128> tab(tab_off[nj]);
         for (uint32_t j = 0; j < nj; ++j) {
@@ -1164,7 +1167,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         BC_HIP(hipStreamSynchronize(st));  // host vectors go out of scope
     }
     BC_HIP(bcdev::launch_fill_slots(d_slots, nj + 1, st));
-    BC_HIP(fill_u32((uint32_t *)d_queue, 64, 0u, st));
+    BC_HIP(fill_u32((uint32_t *)d_queue, 2 * (kSingles + kTaskQueues * bcdev::kQueueWords), 0u, st));
 
     Timer tm(stats != nullptr && !ex.fixed);
     tm.mark(0, st);
@@ -1765,7 +1768,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             cp.instrument = instrument ? 1u : 0u;
             cp.n_units = col_units;
             cp.pool = d_pool;
-            cp.queue = d_queue + 10;
+            cp.queue = task_queue(2);
             cp.n_left = d_queue + 16;   // and the children's counter behind it
             cp.left_cap = n_children;
             cp.slots = d_slots;
@@ -1786,7 +1789,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 sp.n_units = n_split;
                 sp.split = x == 0 ? d_split2 : nullptr;
                 sp.n_split = d_queue + 19;
-                sp.queue = d_queue + 20 + x;
+                sp.queue = task_queue(3 + x);
                 BC_HIP(bcdev::launch_columns(sp, col_blocks, st));
             }
         }
@@ -1825,7 +1828,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         prm.slab_words = slab_words;
         prm.lds_words = lds_words;
         prm.instrument = instrument ? 1u : 0u;
-        prm.queue = d_queue + 2;
+        prm.queue = task_queue(0);
         prm.slots = d_slots;
         BC_HIP(bcdev::launch_enumerate(prm, blocks, st));
         if (col_units) {
@@ -1837,7 +1840,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             lp.split_cap = 0;
             lp.task_chunk = roots_per_wave ? roots_per_wave : 1u;
             lp.wave_clock = nullptr;
-            lp.queue = d_queue + 12;
+            lp.queue = task_queue(1);
             BC_HIP(bcdev::launch_enumerate_left(lp, blocks, st));
         }
     } else {
@@ -1872,7 +1875,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         sp.pure_dfs = (BC_OPT(opts, pure_dfs, 0u) && !any_pv) ? 1u : 0u;   // per-vertex needs the hybrid
         sp.slab = d_sslab;
         sp.slab_words = set_slab_need;
-        sp.queue = d_queue + 9;
+        sp.queue = task_queue(5);
         sp.slots = d_slots;
         BC_HIP(bcdev::launch_enumerate_sets(sp, blocks, st));
         tasks += set_tasks;
