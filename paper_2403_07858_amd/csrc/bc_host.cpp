@@ -97,7 +97,12 @@ struct Side {
 
 }  // namespace
 
+// Graphs alive in the process.
+static std::atomic<int> live_graphs{0};
+
 struct bc_graph {
+    bc_graph() { ++live_graphs; }
+    ~bc_graph() { --live_graphs; }
     Side side[2];
     uint64_t nnz = 0;
     int device = 0;
@@ -407,10 +412,97 @@ void relabel(const bc_csr *c, const std::vector<uint32_t> &sorted_rows, const st
     });
 }
 
+// Device memory that earlier calls have finished with, kept for the next ones:
+// at most kKeep bytes (kKeepIdle when the process's last graph goes), the
+// longest unused given back first, all of it when an allocation fails and when a
+// service sizes its budget.  A block is put here only when nothing on the
+// device uses it any more, so any thread and stream may take it.
+//
+// (The runtime's own stream-ordered pool, which held this scratch before, gave
+// blocks of hundreds of MiB back to the driver and took them again within a run
+// of like calls, 0.5 to 1 ms each and now and then hundreds of ms: 40k edges
+// (6,2) 0.74 against 1.8 ms a call, 50k edges (3,3) 0.51 against 1.37 ms, and
+// 6 to 7 ms from some 400 calls on.)
+class ScratchCache {
+public:
+    static constexpr uint64_t kKeep = 32ull << 30, kKeepIdle = 1ull << 30;
+    static ScratchCache &get()
+    {
+        static ScratchCache *c = new ScratchCache;   // outlives every static object that may hold a graph
+        return *c;
+    }
+    // a block of at least bytes and, if a kept one serves, at most `most`;
+    // *size is what it has
+    hipError_t take(int device, uint64_t bytes, uint64_t most, void **p, uint64_t *size)
+    {
+        {
+            std::lock_guard<std::mutex> g(mu);
+            size_t best = kept.size();
+            for (size_t i = 0; i < kept.size(); ++i)
+                if (kept[i].device == device && kept[i].size >= bytes && kept[i].size <= most &&
+                    (best == kept.size() || kept[i].size <= kept[best].size))
+                    best = i;
+            if (best != kept.size()) {
+                *p = kept[best].p;
+                *size = kept[best].size;
+                total -= kept[best].size;
+                kept.erase(kept.begin() + (ptrdiff_t)best);
+                return hipSuccess;
+            }
+        }
+        *size = bytes;
+        hipError_t e = hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();
+        trim(0);
+        e = hipMalloc(p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
+    }
+    void put(int device, void *p, uint64_t size)
+    {
+        {
+            std::lock_guard<std::mutex> g(mu);
+            kept.push_back({p, size, device});
+            total += size;
+        }
+        trim(kKeep);
+    }
+    // gives blocks back until at most `most` bytes are kept
+    void trim(uint64_t most)
+    {
+        std::vector<Block> out;
+        {
+            std::lock_guard<std::mutex> g(mu);
+            size_t n = 0;
+            while (n < kept.size() && total > most) total -= kept[n++].size;
+            out.assign(kept.begin(), kept.begin() + (ptrdiff_t)n);
+            kept.erase(kept.begin(), kept.begin() + (ptrdiff_t)n);
+        }
+        for (const Block &b : out) (void)hipFree(b.p);
+    }
+
+private:
+    struct Block {
+        void *p;
+        uint64_t size;
+        int device;
+    };
+    std::mutex mu;
+    std::vector<Block> kept;   // the longest unused first
+    uint64_t total = 0;
+};
+
 // A graph's device arrays: hipMalloc, or the caller's hook when bc_build had one.
 hipError_t graph_alloc(bc_graph *g, void **p, uint64_t bytes, hipStream_t st)
 {
-    if (!g->hooked) return hipMalloc(p, bytes);
+    if (!g->hooked) {
+        hipError_t e = hipMalloc(p, bytes);
+        if (e != hipErrorOutOfMemory) return e;
+        (void)hipGetLastError();
+        ScratchCache::get().trim(0);
+        return hipMalloc(p, bytes);
+    }
     *p = g->hook.alloc(g->hook.ctx, bytes, st);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
@@ -616,6 +708,7 @@ extern "C" void bc_free(bc_graph *g)
     free_side(g, g->side[0]);
     free_side(g, g->side[1]);
     delete g;
+    if (live_graphs == 0) ScratchCache::get().trim(ScratchCache::kKeepIdle);
 }
 
 extern "C" bc_status bc_graph_info(const bc_graph *g, uint64_t *n_u, uint64_t *n_v, uint64_t *n_edges)
@@ -662,26 +755,42 @@ extern "C" bc_status bc_ranks(const bc_graph *g, int32_t side, uint32_t *rank_of
 namespace {
 
 // Device scratch of one call, released when the call ends.  Three sources:
-// stream-ordered hipMallocAsync on the call's stream (default), the caller's
-// allocator hook, or a fixed device region carved by bumping an offset (the
-// no-allocation entry point; nothing is allocated or freed).  Every request
-// is rounded up to 256 bytes.  A failed request returns hipErrorOutOfMemory.
+// blocks of the cache above (default), the caller's allocator hook, or a fixed
+// device region carved by bumping an offset (the no-allocation entry point;
+// nothing is allocated or freed).  Every request is rounded up to 256 bytes.  A
+// failed request returns hipErrorOutOfMemory.
+//
+// Uncapped requests to the cache share blocks, each twice the one before
+// (kChunk, up to kMostChunk; larger requests are rounded up to an eighth of
+// their power of two), so that calls on graphs of a few sizes find each
+// other's; capped ones take blocks of their own, at most a quarter larger.
 struct DevAlloc {
-    std::vector<void *> ptrs;
+    static constexpr uint64_t kChunk = 32ull << 20, kMostChunk = 512ull << 20;
+    uint64_t next_chunk = kChunk;
+    uint8_t *chunk = nullptr;
+    uint64_t chunk_left = 0;
+    struct Owned {
+        void *p;
+        uint64_t size;
+    };
+    std::vector<Owned> ptrs;
     hipStream_t st;
+    int device = 0;
     const bc_allocator *hook = nullptr;
     uint8_t *fixed = nullptr;
     uint64_t fixed_cap = 0, fixed_used = 0;
     bool fixed_short = false;    // a request did not fit the fixed region
     uint64_t cap = 0;            // nonzero: at most this many bytes in all (other sources)
     uint64_t total = 0;          // bytes taken so far (nothing is released before the end)
-    DevAlloc(hipStream_t s, const bc_allocator *h) : st(s), hook(h) {}
+    DevAlloc(hipStream_t s, int dev, const bc_allocator *h) : st(s), device(dev), hook(h) {}
     DevAlloc(hipStream_t s, void *region, uint64_t cap) : st(s), fixed((uint8_t *)region), fixed_cap(cap) {}
     ~DevAlloc()
     {
-        for (void *p : ptrs) {
-            if (hook) hook->free(hook->ctx, p, st);
-            else (void)hipFreeAsync(p, st);
+        // (an error may have left work behind; with none this returns at once)
+        if (!hook && !ptrs.empty()) (void)hipStreamSynchronize(st);
+        for (const Owned &o : ptrs) {
+            if (hook) hook->free(hook->ctx, o.p, st);
+            else ScratchCache::get().put(device, o.p, o.size);
         }
     }
     // bytes left in the fixed region or under the cap (else unbounded)
@@ -709,11 +818,33 @@ struct DevAlloc {
         if (hook) {
             v = hook->alloc(hook->ctx, bytes, st);
             if (!v) return hipErrorOutOfMemory;
+            ptrs.push_back({v, bytes});
+        } else if (bytes <= chunk_left) {
+            v = chunk;
+            chunk += bytes;
+            chunk_left -= bytes;
         } else {
-            hipError_t e = hipMallocAsync(&v, bytes, st);
+            uint64_t size = bytes, got = 0;
+            const bool share = !cap && bytes <= kMostChunk;
+            if (share) {
+                while (next_chunk < bytes) next_chunk *= 2;
+                size = next_chunk;
+            } else if (!cap) {
+                const uint64_t step = 1ull << (60 - __builtin_clzll(bytes));
+                size = (bytes + step - 1) / step * step;
+            }
+            ScratchCache &cache = ScratchCache::get();
+            hipError_t e = cache.take(device, size, cap ? size + size / 4 : 2 * size, &v, &got);
+            if (e != hipSuccess && size != bytes)   // memory is short: no more than what is asked for
+                e = cache.take(device, bytes, 2 * bytes, &v, &got);
             if (e != hipSuccess) return e;
+            ptrs.push_back({v, got});
+            if (share && got > bytes) {
+                chunk = (uint8_t *)v + bytes;
+                chunk_left = got - bytes;
+                next_chunk = std::min(2 * next_chunk, kMostChunk);
+            }
         }
-        ptrs.push_back(v);
         total += bytes;
         *p = v;
         return hipSuccess;
@@ -849,14 +980,6 @@ int cu_count(int device)
         int v = 0;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || v <= 0) v = 256;
         cache[device] = v;
-        // keep up to 32 GiB of stream-ordered allocations cached between
-        // calls instead of returning them to the driver at every
-        // synchronization (more would starve other users of the device)
-        hipMemPool_t pool;
-        if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
-            uint64_t thr = 32ull << 30;
-            (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-        }
     }
     return cache[device];
 }
@@ -999,7 +1122,7 @@ bc_status run_jobs(const std::vector<JobSpec> &specs, const bc_opts *opts, std::
     DevAlloc *mem = nullptr;
     bc_status s = run_jobs_impl(specs, opts, out, item_status, stats, ex, read_back, mem);
     if (mem && ex.fixed_short && mem->fixed_short) *ex.fixed_short = true;
-    delete mem;   // stream-ordered release of the call's scratch
+    delete mem;   // the call's scratch goes back
     if (!read_back) {
         const bc_status e = s == BC_OK ? set_error(BC_E_DEVICE, "internal: counts were not read back") : s;
         item_status.assign(specs.size(), e);
@@ -1038,7 +1161,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     const int ncu = cu_count(device);
     auto t_host0 = std::chrono::steady_clock::now();
     mem_out = ex.fixed ? new DevAlloc(st, ex.fixed, ex.fixed_cap)
-                       : new DevAlloc(st, BC_OPT(opts, alloc, (const bc_allocator *)nullptr));
+                       : new DevAlloc(st, device, BC_OPT(opts, alloc, (const bc_allocator *)nullptr));
     DevAlloc &mem = *mem_out;
     mem.cap = ex.fixed ? 0 : scratch_cap;
 
@@ -2614,6 +2737,8 @@ uint64_t estimate_scratch_bytes(const bc_graph *g, uint32_t p, uint32_t q, uint3
 }
 
 int graph_device(const bc_graph *g) { return g->device; }
+
+void trim_scratch() { ScratchCache::get().trim(0); }
 
 double query_cost(const bc_graph *g, uint32_t p, uint32_t q)
 {

@@ -19,11 +19,7 @@ void hip_stream_destroy(void *s) { (void)hipStreamDestroy((hipStream_t)s); }
 uint64_t hip_default_budget()
 {
     // memory cached by earlier counts is not in use: give it back first
-    int dev = 0;
-    hipMemPool_t pool;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess &&
-        hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess)
-        (void)hipMemPoolTrimTo(pool, 0);
+    bcint::trim_scratch();
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b == 0) free_b = 8ull << 30;
     return free_b / 2;
