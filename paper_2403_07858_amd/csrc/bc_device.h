@@ -86,7 +86,9 @@ struct ActiveRoot {
     uint32_t job;
     uint32_t root;          // anchor-side vertex (rank)
     uint32_t k;             // number of candidates (rows)
-    uint32_t n_tasks;       // candidates that start a task: k - (pA - 2)
+    uint32_t n_tasks;       // candidates that start a task, k - (pA - 2), times shares
+    uint32_t shares;        // tasks each of these is shared out to, by its child rows (p_A >= 5; else 1)
+    uint32_t pad;
 };
 
 // One root of the column search, in schedule order: its candidate rows
@@ -139,6 +141,8 @@ constexpr uint32_t kColRootPlanes = 16;    // and its widest row, in 64-bit word
 constexpr uint32_t kColFixed = 3;          // most columns fixed in a unit
 constexpr uint32_t kColLessLen = 64 * kColRootPlanes + 1;   // entries of a unit's leaf table, if so many
 constexpr uint32_t kNoJ = 0xffffffffu;     // no restriction to one child
+constexpr uint32_t kOneChild = 0x40000000u;   // step of a child loop that ends after one
+constexpr uint32_t kMaxShares = 64;        // most tasks a candidate's search is shared out to
 constexpr int kSortCap = 4096;          // candidates sorted in LDS up to this many
 constexpr int kRbWaves = 8;             // waves per large block of the fused per-root kernel
 constexpr int kRbThreads = kWaveSize * kRbWaves;

@@ -1737,6 +1737,36 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     uint64_t pool_words = 0, tasks = 0, row_tasks = 0, col_words = 0, col_units = 0;
     uint64_t slab_need = 64, left_slab_need = 64;   // words per wave: row search, its run over left units
     uint32_t n_row_roots = 0, n_whole = 0;
+    // The work under a candidate grows with the (p_A - 2)-subsets of the rows it
+    // keeps, and one wavefront does it.  On a graph whose row search is that of
+    // a few hubs (some eighty candidates each, wide rows that keep each other)
+    // a handful of candidates outlast all others: such a candidate is shared
+    // out by its child rows, so that no task is more than a quarter of what a
+    // wavefront has to do in all.  Every share filters the level-2 block again
+    // (some 1e4 wave instructions), so short tasks stay whole.  Row search of
+    // 300k edges (6,6), where the hubs' candidates ran 28 ms and the rest 6: 6.2
+    // against 28.8 ms; of 256 small graphs 18.3 against 29.
+    const bool share_out = split_rows == 0 || split_rows == 0xffffffffu;
+    auto task_cost = [&](const Plan &pl) -> double {   // wave instructions of its first task
+        const bcdev::Job &jb = cjobs[pl.c];
+        const uint32_t du = degree_of(pl);
+        double rows = pl.k / 3.0, common = du / 3.0;
+        if (du > bcdev::kColTripleMax && fused) {
+            const double fill = (double)found[pl.item].bits / ((double)pl.k * du);
+            common = fill * du;
+            // (hubs' rows overlap more than chance)
+            if (std::pow(fill, (double)jb.pA - 4) * du >= jb.qA) rows = pl.k - 1.0;
+        }
+        double sets = 1;
+        for (uint32_t x = 0; x + 2 < jb.pA; ++x) sets *= std::max(0.0, rows - x) / (x + 1);
+        return sets * (common > 256 ? 5.0 : common > jb.n_u28 ? 2.5 : 0.3);   // per pair of rows
+    };
+    double row_cost = 0;   // of all row roots: the tasks of a root fall off as C(k - i, p_A - 2)
+    auto task_shares = [&](const Plan &pl) -> uint32_t {
+        if (cjobs[pl.c].pA < 5) return 1;
+        const double cost = task_cost(pl), most = std::max(1e5, row_cost / (4.0 * ncu * waves_per_cu));
+        return (uint32_t)std::max(1.0, std::min({cost / most, (double)bcdev::kMaxShares, (double)pl.k}));
+    };
     auto lay_out = [&]() {
         pool_words = tasks = row_tasks = col_words = col_units = 0;
         slab_need = left_slab_need = 64;
@@ -1749,6 +1779,9 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         for (size_t r = 0; r < plan.size(); ++r)
             if (mode[r] == kByRows) order.push_back((uint32_t)r);
         n_row_roots = (uint32_t)order.size();
+        row_cost = 0;
+        if (share_out)
+            for (uint32_t r : order) row_cost += plan[r].k * task_cost(plan[r]) / (cjobs[plan[r].c].pA - 1);
         for (size_t r = 0; r < plan.size(); ++r) {
             if (mode[r] == kByColumns) order.push_back((uint32_t)r);
             if (mode[r] == kWhole) {
@@ -1765,13 +1798,19 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             const uint32_t pA = cjobs[pl.c].pA;
             bcdev::ActiveRoot &a = aroots[x];
             a.pool_off = rows_ready ? found[pl.item].off : pool_words;
-            a.task_begin = tasks;
+            a.task_begin = row_tasks;
             a.job = pl.c;
             a.root = pl.root;
             a.k = pl.k;
             a.n_tasks = pl.k - (pA - 2);
+            a.shares = 1;
+            a.pad = 0;
             pool_words += (uint64_t)pl.k * pl.w1;
             tasks += a.n_tasks;
+            if (m == kByRows && share_out) {
+                a.shares = task_shares(pl);
+                a.n_tasks *= a.shares;
+            }
             if (m == kByRows) row_tasks += a.n_tasks;
             if (m != kByRows) {   // the column search's list: whole ones first
                 bcdev::ColRoot &c = croots[m == kWhole ? x - (order.size() - n_whole) : x - n_row_roots + n_whole];

@@ -1920,19 +1920,20 @@ __device__ __forceinline__ uint32_t col_plane_count(const uint64_t *cols, uint32
 
 __device__ __attribute__((always_inline)) inline void dfs_level2(
     const Job &jb, uint32_t jidx, const uint64_t *blk2, uint32_t stride2, uint32_t m2, uint32_t W2, uint32_t s2n,
-    uint32_t only_child, Arena &ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct, bool instrument, bool triple,
-    bool *cap_fail, bool *timed_out, uint64_t t0);
+    uint32_t child, uint32_t child_step, Arena &ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct,
+    bool instrument, bool triple, bool *cap_fail, bool *timed_out, uint64_t t0);
 
 // One task: the node {u, c_i} of the search tree.  SPLIT compiles in the
 // hand-off of heavy tasks to the subtask ring; without it sp is unused.
 // COLS: the task is a unit of the column search instead, fixed columns (the
 // col_pack i) of the root (columns at cols): S2 are the columns before them
 // that share enough candidates with them, the rows are the candidates that
-// hold them, and jb chooses one row more and those columns less; only_child
-// restricts the search to one child row.
+// hold them, and jb chooses one row more and those columns less.  child and
+// child_step: the task's share of its child rows (p_A >= 5; 0 and 1: all).
 template <bool SPLIT, bool COLS>
 __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uint32_t i, const uint64_t *pool,
-                         const uint64_t *cols, uint32_t only_child, Arena ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct,
+                         const uint64_t *cols, uint32_t child, uint32_t child_step, Arena ar, uint64_t *stack, Table &tb,
+                         Acc &acc, Counters &ct,
                          bool instrument, bool triple, const SplitCtx *sp, bool *cap_fail, bool *timed_out)
 {
     const uint32_t ln = lane_id();
@@ -2250,7 +2251,7 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
     // whichever wavefront takes it; if the heap or the ring is full, the task
     // carries on here.
     if constexpr (SPLIT) {
-    if (pA >= 5 && m2 > sp->rows && !(triple && m2 <= kTripleRows)) {
+    if (pA >= 5 && child_step == 1 && m2 > sp->rows && !(triple && m2 <= kTripleRows)) {
         const uint32_t n_sub = m2 - (pA - 3);   // children a <= m2 - (pA - 2)
         const unsigned long long off = heap_take(*sp, 4 + (uint64_t)m2 * W2);
         const unsigned long long at = off != ~0ull ? ring_reserve(*sp, n_sub) : ~0ull;
@@ -2275,19 +2276,19 @@ __device__ void run_task(const Job &jb, uint32_t jidx, const ActiveRoot &rt, uin
         // (a heap block taken without ring room stays unused until the launch ends)
     }
     }
-    dfs_level2(jb, jidx, blk2, stride2, m2, W2, s2n, COLS ? only_child : kNoJ, ar, stack, tb, acc, ct, instrument, triple, cap_fail, timed_out,
-               t0);
+    dfs_level2(jb, jidx, blk2, stride2, m2, W2, s2n, child, child_step, ar, stack, tb, acc, ct, instrument, triple,
+               cap_fail, timed_out, t0);
 }
 
 // The search below a level-2 node {u, c_i} whose block holds m2 rows of W2
 // words (column-major, stride2): pair sums for p_A = 4, else the DFS over
 // levels 2 .. pA-3, the node at level pA-2 finished by pair_sum (small nodes
-// at level pA-3 by the three-level sweep).  only_child != kNoJ restricts the
-// level-2 loop to that one child row (a subtask of a split task).
+// at level pA-3 by the three-level sweep).  The level-2 loop takes the rows
+// child, child + child_step, .. (a task shared out, or a subtask with one child).
 __device__ __attribute__((always_inline)) inline void dfs_level2(
     const Job &jb, uint32_t jidx, const uint64_t *blk2, uint32_t stride2, uint32_t m2, uint32_t W2, uint32_t s2n,
-    uint32_t only_child, Arena &ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct, bool instrument, bool triple,
-    bool *cap_fail, bool *timed_out, uint64_t t0)
+    uint32_t child, uint32_t child_step, Arena &ar, uint64_t *stack, Table &tb, Acc &acc, Counters &ct,
+    bool instrument, bool triple, bool *cap_fail, bool *timed_out, uint64_t t0)
 {
     const uint32_t q = jb.qA, pA = jb.pA;
     if (pA == 4) {
@@ -2300,11 +2301,10 @@ __device__ __attribute__((always_inline)) inline void dfs_level2(
     // [2] = cursor, [3] = arena marks (lds_used | slab_used << 32).
     auto enc_ptr = [&](const uint64_t *p) -> uint64_t { return (uint64_t)(uintptr_t)p; };
     auto dec_ptr = [&](uint64_t e) -> const uint64_t * { return (const uint64_t *)(uintptr_t)e; };
-    const uint32_t a_end = only_child == kNoJ ? 0xffffffffu : only_child + 1;
     uint32_t d = 2;
     stack[4 * 2 + 0] = enc_ptr(blk2);
     stack[4 * 2 + 1] = (uint64_t)stride2 | ((uint64_t)m2 << 32);
-    stack[4 * 2 + 2] = only_child == kNoJ ? 0 : only_child;
+    stack[4 * 2 + 2] = child;
     stack[4 * 2 + 3] = 0;
     for (;;) {
         if (past_deadline(jb.deadline)) {
@@ -2317,8 +2317,8 @@ __device__ __attribute__((always_inline)) inline void dfs_level2(
         uint32_t a = (uint32_t)stack[4 * d + 2];
         // a small node two levels above the leaves: its last three levels in
         // one matrix-core sweep, then the node is done
-        if (triple && d + 3 == pA && a == 0 && (d > 2 || only_child == kNoJ) && m >= 3 && m <= kTripleRows && W2 <= kTileWords && s2n <= jb.n_u28 &&
-            table_ready(tb, jb, jidx, s2n + 1)) {
+        if (triple && d + 3 == pA && a == 0 && (d > 2 || child_step == 1) && m >= 3 && m <= kTripleRows &&
+            W2 <= kTileWords && s2n <= jb.n_u28 && table_ready(tb, jb, jidx, s2n + 1)) {
             const uint32_t pcap = m * (m - 1) / 2;
             const uint64_t mark = (uint64_t)ar.lds_used | (ar.slab_used << 32);
             uint64_t *P = arena_alloc(ar, (uint64_t)pcap * W2 + (pcap + 1) / 2, cap_fail);
@@ -2354,8 +2354,8 @@ __device__ __attribute__((always_inline)) inline void dfs_level2(
             ar.slab_used = mark >> 32;
             a = m;   // exhausted: pop below
         }
-        // row a needs pA - d - 1 more rows after it (a subtask does one level-2 child)
-        if ((int64_t)a > (int64_t)m - (int64_t)pA + (int64_t)d || (d == 2 && a >= a_end)) {
+        // row a needs pA - d - 1 more rows after it
+        if ((int64_t)a > (int64_t)m - (int64_t)pA + (int64_t)d) {
             if (d == 2) break;
             // pop: release this level's block
             const uint64_t mk = stack[4 * d + 3];
@@ -2364,7 +2364,7 @@ __device__ __attribute__((always_inline)) inline void dfs_level2(
             --d;
             continue;
         }
-        stack[4 * d + 2] = a + 1;
+        stack[4 * d + 2] = a + (d == 2 ? child_step : 1u);
         const uint32_t cap = m - a - 1;
         const uint64_t mark = (uint64_t)ar.lds_used | (ar.slab_used << 32);
         uint64_t *nb = arena_alloc(ar, (uint64_t)cap * W2, cap_fail);
@@ -2503,13 +2503,17 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
             rt = prm.roots[r];
         }
         for (unsigned long long t = t0; t < t_end; ++t) {
-            uint32_t i, child = kNoJ, n_fixed = 1;
+            uint32_t i, child = 0, step = 1, n_fixed = 1;
             const uint64_t *cols = nullptr;
             if constexpr (COLS) {
                 const uint4 e = prm.left[t];
                 r = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
                 i = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
-                child = (uint32_t)__builtin_amdgcn_readfirstlane(e.z);
+                const uint32_t z = (uint32_t)__builtin_amdgcn_readfirstlane(e.z);
+                if (z != kNoJ) {
+                    child = z;
+                    step = kOneChild;
+                }
                 unit_first(i, &n_fixed);
                 const ColRoot cr = prm.col_roots[r];
                 cols = prm.cols + cr.col_off;
@@ -2521,6 +2525,11 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
             } else {
                 while (t >= rt.task_begin + rt.n_tasks) rt = prm.roots[++r];   // every active root owns >= 1 task
                 i = (uint32_t)(t - rt.task_begin);
+                if (rt.shares > 1) {
+                    step = rt.shares;
+                    child = i % step;
+                    i /= step;
+                }
             }
             if (rt.job != cur_job) {
                 if (cur_job != 0xffffffffu) enum_flush(prm.slots, prm.jobs[cur_job].slot, acc, ct, instrument);
@@ -2541,7 +2550,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
             bool cap_fail = false, timed_out = past_deadline(jb.deadline);
             sp.root_idx = r;
             if (!timed_out)
-                run_task<SPLIT, COLS>(jb, kColFixed * rt.job + n_fixed - 1, rt, i, prm.pool, cols, child, arena, stack, tb, acc, ct, instrument,
+                run_task<SPLIT, COLS>(jb, kColFixed * rt.job + n_fixed - 1, rt, i, prm.pool, cols, child, step, arena, stack, tb, acc, ct, instrument,
                                       prm.triple != 0, &sp, &cap_fail, &timed_out);
             if (cap_fail && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_CAPACITY);
             if (timed_out && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
@@ -2610,7 +2619,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
         bool cap_fail = false, timed_out = past_deadline(jb.deadline);
         if (!timed_out) {
             Arena ar = arena;
-            dfs_level2(jb, rt.job, hdr + 4, hm2, hm2, hW2, hs2n, ea, ar, stack, tb, acc, ct, instrument,
+            dfs_level2(jb, rt.job, hdr + 4, hm2, hm2, hW2, hs2n, ea, kOneChild, ar, stack, tb, acc, ct, instrument,
                        prm.triple != 0, &cap_fail, &timed_out, instrument ? cycles() : 0);
         }
         if (cap_fail && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_CAPACITY);
