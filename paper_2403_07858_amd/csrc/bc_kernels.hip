@@ -2678,9 +2678,10 @@ hipError_t launch_enumerate_left(const EnumParams &prm, uint32_t n_blocks, hipSt
 // LDS.  In that order the lanes of a wave share almost the same last column,
 // so the loops, which start behind it, waste few lanes.  What bounds it is the
 // VALU: two operations (AND, popcount with add) per 32 candidates and tuple.
-// Whole counts with and without it, power-law graphs: 1.2M edges (5,5) 48
-// against 989 ms, 300k (6,6) 43 against 445 ms, 2M (4,4) 26 against 86 ms,
-// (6,4) 38 against 47 ms, 5M (3,3) 65 against 89 ms.  The same search per task
+// Whole counts when it came, against rows alone, power-law graphs: 1.2M edges
+// (5,5) 48 against 989 ms, 300k (6,6) 43 against 445 ms, 2M (4,4) 26 against 86,
+// (6,4) 38 against 47, 5M (3,3) 65 against 89 (43, 22, 21, 33 and 47 with the
+// candidate pass, queues and shares as they are now).  The same search per task
 // of the row search instead of per root was slower ((5,5) 104 ms, (4,4) 52 ms:
 // its short units spend their time on staging).
 
