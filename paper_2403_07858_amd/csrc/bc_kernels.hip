@@ -941,6 +941,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
             });
             __syncthreads();
             in_lds = s_flag == 0;
+            __syncthreads();   // read by all before the id ranges reset it
         }
         uint32_t k = 0;
         uint64_t off = ~0ull;
