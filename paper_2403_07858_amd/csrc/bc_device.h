@@ -281,9 +281,12 @@ uint32_t max_lds_words_per_wave();
 // The columns fixed in a unit, the last of its subsets first: ten bits each,
 // all ones for none.
 constexpr uint32_t kColNone = 1023;
-static_assert(64 * kColRootPlanes <= kColNone + 1, "columns are numbered below kColNone");
+constexpr uint32_t kColRootMax = kColNone;   // most neighbours of a root searched unit by unit: columns 0 .. kColNone - 1
+static_assert(kColRootMax <= kColNone && kColRootMax <= 64 * kColRootPlanes, "a column's number is never kColNone");
 __host__ __device__ constexpr uint32_t col_pack(uint32_t x, uint32_t y, uint32_t z) { return x | (y << 10) | (z << 20); }
 __host__ __device__ constexpr uint32_t col_fixed(uint32_t pack, uint32_t i) { return (pack >> (10 * i)) & kColNone; }
+// Whether a root of du neighbours and wk words of candidates can be searched unit by unit.
+__host__ __device__ constexpr bool col_root_fits(uint32_t du, uint32_t wk) { return du <= kColRootMax && wk <= kColRootWords; }
 
 // The column search chooses q of s columns of nw words.  It searches
 // col_words words of them, kept col_stride words apart (two words more, so

@@ -1705,7 +1705,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         const uint64_t rows = pA == 3 ? k * k * w1 / 34 + 100
                                       : k * (250 + 6ull * wk * w1 + bcdev::row_estimate(k / 3, pA - 2));
         const uint64_t units = du * (400 + 10ull * wk + 65 * w1 * std::max<uint64_t>(1, wk / 4));
-        if (col_units_ok(pA, q) && wk <= bcdev::kColRootWords && w1 <= bcdev::kColRootPlanes &&
+        if (col_units_ok(pA, q) && bcdev::col_root_fits(du, wk) &&
             units * (pA == 3 ? 1 : 4) < rows && (pA == 3 || q <= pA + 1 || du <= 192 || found[pl.item].bits > 100 * k))
             mode[r] = kByColumns;
         // a dense root (bits: set bits of its rows): nothing is pruned, so the

@@ -1,0 +1,18 @@
+"""Limits shared by the host and the kernels (bc_device.h), checked on the CPU."""
+import os
+import subprocess
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2403_07858_amd", "csrc")
+
+
+def run_check(name, tmp_path):
+    exe = str(tmp_path / name)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC,
+                    os.path.join(HERE, name + ".cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_every_column_has_a_number_of_its_own(tmp_path):
+    run_check("column_limits_check", tmp_path)
