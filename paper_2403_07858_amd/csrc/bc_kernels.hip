@@ -1244,7 +1244,12 @@ struct Table {
     uint32_t job, len;
 };
 
-// Makes tbl hold entries [0, need) of job j; false if they do not all fit
+// The key a table is kept under: the leaf values of job j, or with n_fixed (1 ..
+// kColFixed) columns fixed.  One wavefront meets tasks, queued subtasks and left
+// units of all jobs.
+__device__ constexpr uint32_t table_key(uint32_t j, uint32_t n_fixed) { return (kColFixed + 1) * j + n_fixed; }
+
+// Makes tbl hold entries [0, need) under key j; false if they do not all fit
 // (table too short or some entry >= 2^64), in which case the caller uses the
 // u128 table in HBM.
 __device__ bool table_ready(Table &tb, const Job &jb, uint32_t j, uint32_t need)
@@ -2551,7 +2556,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
             bool cap_fail = false, timed_out = past_deadline(jb.deadline);
             sp.root_idx = r;
             if (!timed_out)
-                run_task<SPLIT, COLS>(jb, kColFixed * rt.job + n_fixed - 1, rt, i, prm.pool, cols, child, step, arena, stack, tb, acc, ct, instrument,
+                run_task<SPLIT, COLS>(jb, table_key(rt.job, COLS ? n_fixed : 0u), rt, i, prm.pool, cols, child, step, arena, stack, tb, acc, ct, instrument,
                                       prm.triple != 0, &sp, &cap_fail, &timed_out);
             if (cap_fail && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_CAPACITY);
             if (timed_out && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
@@ -2620,7 +2625,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
         bool cap_fail = false, timed_out = past_deadline(jb.deadline);
         if (!timed_out) {
             Arena ar = arena;
-            dfs_level2(jb, rt.job, hdr + 4, hm2, hm2, hW2, hs2n, ea, kOneChild, ar, stack, tb, acc, ct, instrument,
+            dfs_level2(jb, table_key(rt.job, 0), hdr + 4, hm2, hm2, hW2, hs2n, ea, kOneChild, ar, stack, tb, acc, ct, instrument,
                        prm.triple != 0, &cap_fail, &timed_out, instrument ? cycles() : 0);
         }
         if (cap_fail && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_CAPACITY);
