@@ -122,7 +122,9 @@ typedef struct {
     uint32_t timeout_ms;       /* device-side time limit of the call (0 = none); past it the
                                   call fails with BC_E_TIMEOUT and no count is returned */
     const bc_allocator *alloc; /* device memory for the call's scratch (and, in bc_build, the
-                                  graph's arrays); NULL = hipMallocAsync on the stream */
+                                  graph's arrays); NULL = hipMalloc, the scratch in blocks that the
+                                  library keeps between calls (a call gives them back once the
+                                  stream is idle) */
     int32_t order_key;         /* bc_build: BC_ORDER_DEGREE or BC_ORDER_TWO_HOP */
     uint32_t order_k;          /* bc_build, BC_ORDER_TWO_HOP: the sharing threshold k (0 = 2) */
     uint32_t roots_per_wave;   /* enumeration tasks a wavefront takes per queue pop, 1..64;

@@ -1,0 +1,211 @@
+// Device scratch of the calls: blocks kept between calls, and one call's
+// allocations out of them.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <mutex>
+#include <vector>
+
+#include "bc.h"
+
+namespace {
+
+// Device memory that earlier calls have finished with, kept for the next ones:
+// at most kKeep bytes (kKeepIdle when the process's last graph goes), the
+// longest unused given back first, all of it when an allocation fails and when a
+// service sizes its budget.  A block is put here only when nothing on the
+// device uses it any more, so any thread and stream may take it.
+//
+// (The runtime's own stream-ordered pool, which held this scratch before, gave
+// blocks of hundreds of MiB back to the driver and took them again within a run
+// of like calls, 0.5 to 1 ms each and now and then hundreds of ms: 40k edges
+// (6,2) 0.74 against 1.8 ms a call, 50k edges (3,3) 0.51 against 1.37 ms, and
+// 6 to 7 ms from some 400 calls on.)
+class ScratchCache {
+public:
+    static constexpr uint64_t kKeep = 32ull << 30, kKeepIdle = 1ull << 30;
+    static ScratchCache &get()
+    {
+        static ScratchCache *c = new ScratchCache;   // outlives every static object that may hold a graph
+        return *c;
+    }
+    // a block of at least bytes and, if a kept one serves, at most `most`;
+    // *size is what it has
+    hipError_t take(int device, uint64_t bytes, uint64_t most, void **p, uint64_t *size)
+    {
+        {
+            std::lock_guard<std::mutex> g(mu);
+            size_t best = kept.size();
+            for (size_t i = 0; i < kept.size(); ++i)
+                if (kept[i].device == device && kept[i].size >= bytes && kept[i].size <= most &&
+                    (best == kept.size() || kept[i].size <= kept[best].size))
+                    best = i;
+            if (best != kept.size()) {
+                *p = kept[best].p;
+                *size = kept[best].size;
+                total -= kept[best].size;
+                kept.erase(kept.begin() + (ptrdiff_t)best);
+                return hipSuccess;
+            }
+        }
+        *size = bytes;
+        hipError_t e = hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();
+        trim(0);
+        e = hipMalloc(p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
+    }
+    void put(int device, void *p, uint64_t size)
+    {
+        {
+            std::lock_guard<std::mutex> g(mu);
+            kept.push_back({p, size, device});
+            total += size;
+        }
+        trim(kKeep);
+    }
+    // gives blocks back until at most `most` bytes are kept
+    void trim(uint64_t most)
+    {
+        std::vector<Block> out;
+        {
+            std::lock_guard<std::mutex> g(mu);
+            size_t n = 0;
+            while (n < kept.size() && total > most) total -= kept[n++].size;
+            out.assign(kept.begin(), kept.begin() + (ptrdiff_t)n);
+            kept.erase(kept.begin(), kept.begin() + (ptrdiff_t)n);
+        }
+        for (const Block &b : out) (void)hipFree(b.p);
+    }
+
+private:
+    struct Block {
+        void *p;
+        uint64_t size;
+        int device;
+    };
+    std::mutex mu;
+    std::vector<Block> kept;   // the longest unused first
+    uint64_t total = 0;
+};
+
+// Device scratch of one call, released when the call ends.  Three sources:
+// blocks of the cache above (default), the caller's allocator hook, or a fixed
+// device region carved by bumping an offset (the no-allocation entry point;
+// nothing is allocated or freed).  Every request is rounded up to 256 bytes.  A
+// failed request returns hipErrorOutOfMemory.
+//
+// Uncapped requests to the cache share blocks, each twice the one before
+// (kChunk, up to kMostChunk; larger requests are rounded up to an eighth of
+// their power of two), so that calls on graphs of a few sizes find each
+// other's.  Capped ones take blocks of their own, at most a quarter larger than
+// that, and all of a block counts against the cap; a call that runs out of room
+// for it (padded) is run again on blocks of exactly what it asks for.
+struct DevAlloc {
+    static constexpr uint64_t kChunk = 32ull << 20, kMostChunk = 512ull << 20;
+    uint64_t next_chunk = kChunk;
+    uint8_t *chunk = nullptr;
+    uint64_t chunk_left = 0;
+    struct Owned {
+        void *p;
+        uint64_t size;
+    };
+    std::vector<Owned> ptrs;
+    hipStream_t st;
+    int device = 0;
+    const bc_allocator *hook = nullptr;
+    uint8_t *fixed = nullptr;
+    uint64_t fixed_cap = 0, fixed_used = 0;
+    bool fixed_short = false;    // a request did not fit the fixed region
+    uint64_t cap = 0;            // nonzero: at most this many bytes in all (other sources)
+    bool exact = false;          // capped: blocks of the size asked for only
+    bool padded = false;         // capped: some block was larger
+    uint64_t total = 0;          // bytes taken so far (nothing is released before the end)
+    DevAlloc(hipStream_t s, int dev, const bc_allocator *h) : st(s), device(dev), hook(h) {}
+    DevAlloc(hipStream_t s, void *region, uint64_t cap) : st(s), fixed((uint8_t *)region), fixed_cap(cap) {}
+    ~DevAlloc()
+    {
+        // (an error may have left work behind; with none this returns at once)
+        if (!hook && !ptrs.empty()) (void)hipStreamSynchronize(st);
+        for (const Owned &o : ptrs) {
+            if (hook) hook->free(hook->ctx, o.p, st);
+            else ScratchCache::get().put(device, o.p, o.size);
+        }
+    }
+    // bytes left in the fixed region or under the cap (else unbounded)
+    uint64_t room() const
+    {
+        if (fixed) return fixed_cap - fixed_used;
+        return cap ? (cap > total ? cap - total : 0) : ~0ull;
+    }
+    hipError_t raw(void **p, uint64_t bytes)
+    {
+        bytes = (std::max<uint64_t>(bytes, 1) + 255) & ~255ull;
+        *p = nullptr;
+        if (fixed) {
+            if (bytes > fixed_cap - fixed_used) {
+                fixed_short = true;
+                return hipErrorOutOfMemory;
+            }
+            *p = fixed + fixed_used;
+            fixed_used += bytes;
+            total += bytes;
+            return hipSuccess;
+        }
+        if (cap && bytes > room()) return hipErrorOutOfMemory;
+        void *v = nullptr;
+        if (hook) {
+            v = hook->alloc(hook->ctx, bytes, st);
+            if (!v) return hipErrorOutOfMemory;
+            ptrs.push_back({v, bytes});
+        } else if (bytes <= chunk_left) {
+            v = chunk;
+            chunk += bytes;
+            chunk_left -= bytes;
+        } else {
+            uint64_t size = bytes, got = 0;
+            const bool share = !cap && bytes <= kMostChunk;
+            if (share) {
+                while (next_chunk < bytes) next_chunk *= 2;
+                size = next_chunk;
+            } else if (!exact) {
+                const uint64_t step = 1ull << (60 - __builtin_clzll(bytes));
+                size = std::min((bytes + step - 1) / step * step, room());
+            }
+            ScratchCache &cache = ScratchCache::get();
+            const uint64_t most = exact ? size : std::min(cap ? size + size / 4 : 2 * size, room());
+            hipError_t e = cache.take(device, size, most, &v, &got);
+            if (e != hipSuccess && size != bytes)   // memory is short: no more than what is asked for
+                e = cache.take(device, bytes, cap ? bytes : 2 * bytes, &v, &got);
+            if (e != hipSuccess) return e;
+            ptrs.push_back({v, got});
+            if (cap) {
+                padded = padded || got > bytes;
+                bytes = got;
+            }
+            if (share && got > bytes) {
+                chunk = (uint8_t *)v + bytes;
+                chunk_left = got - bytes;
+                next_chunk = std::min(2 * next_chunk, kMostChunk);
+            }
+        }
+        total += bytes;
+        *p = v;
+        return hipSuccess;
+    }
+    template <typename T>
+    hipError_t get(T **p, uint64_t count)
+    {
+        void *v = nullptr;
+        hipError_t e = raw(&v, count * sizeof(T));
+        *p = (T *)v;
+        return e;
+    }
+};
+
+}  // namespace
