@@ -420,7 +420,7 @@ hipError_t graph_alloc(bc_graph *g, void **p, uint64_t bytes, hipStream_t st)
         hipError_t e = hipMalloc(p, bytes);
         if (e != hipErrorOutOfMemory) return e;
         (void)hipGetLastError();
-        ScratchCache::get().trim(0);
+        ScratchCache::get().trim(g->device, 0);
         return hipMalloc(p, bytes);
     }
     *p = g->hook.alloc(g->hook.ctx, bytes, st);
@@ -628,7 +628,7 @@ extern "C" void bc_free(bc_graph *g)
     free_side(g, g->side[0]);
     free_side(g, g->side[1]);
     delete g;
-    if (live_graphs == 0) ScratchCache::get().trim(ScratchCache::kKeepIdle);
+    if (live_graphs == 0) ScratchCache::get().trim_all(ScratchCache::kKeepIdle);
 }
 
 extern "C" bc_status bc_graph_info(const bc_graph *g, uint64_t *n_u, uint64_t *n_v, uint64_t *n_edges)
@@ -2602,7 +2602,11 @@ uint64_t estimate_scratch_bytes(const bc_graph *g, uint32_t p, uint32_t q, uint3
 
 int graph_device(const bc_graph *g) { return g->device; }
 
-void trim_scratch() { ScratchCache::get().trim(0); }
+void trim_scratch()
+{
+    int device = 0;
+    if (hipGetDevice(&device) == hipSuccess) ScratchCache::get().trim(device, 0);
+}
 
 double query_cost(const bc_graph *g, uint32_t p, uint32_t q)
 {

@@ -26,7 +26,7 @@ bc_status count_queries(const Query *qs, size_t n, const bc_opts *opts, bc_u128 
 uint64_t estimate_scratch_bytes(const bc_graph *g, uint32_t p, uint32_t q, uint32_t waves_per_cu);
 
 int graph_device(const bc_graph *g);
-// Gives the device memory kept from earlier calls back to the driver.
+// Gives the current device's memory kept from earlier calls back to the driver.
 void trim_scratch();
 // Relative time of one (p,q) count on g, from the graph alone (no device
 // work): the wedges the candidate pass scans for the cheaper anchor, times 4

@@ -14,9 +14,9 @@
 namespace {
 
 // Device memory that earlier calls have finished with, kept for the next ones:
-// at most kKeep bytes (kKeepIdle when the process's last graph goes), the
-// longest unused given back first, all of it when an allocation fails and when a
-// service sizes its budget.  A block is put here only when nothing on the
+// on each device at most kKeep bytes (kKeepIdle when the process's last graph
+// goes), the longest unused given back first, all of a device's when an
+// allocation on it fails and when a service sizes its budget there.  A block is put here only when nothing on the
 // device uses it any more, so any thread and stream may take it.
 //
 // (The runtime's own stream-ordered pool, which held this scratch before, gave
@@ -46,7 +46,6 @@ public:
             if (best != kept.size()) {
                 *p = kept[best].p;
                 *size = kept[best].size;
-                total -= kept[best].size;
                 kept.erase(kept.begin() + (ptrdiff_t)best);
                 return hipSuccess;
             }
@@ -55,7 +54,7 @@ public:
         hipError_t e = hipMalloc(p, bytes);
         if (e == hipSuccess) return e;
         (void)hipGetLastError();
-        trim(0);
+        trim(device, 0);
         e = hipMalloc(p, bytes);
         if (e != hipSuccess) (void)hipGetLastError();
         return e;
@@ -65,22 +64,39 @@ public:
         {
             std::lock_guard<std::mutex> g(mu);
             kept.push_back({p, size, device});
-            total += size;
         }
-        trim(kKeep);
+        trim(device, kKeep);
     }
-    // gives blocks back until at most `most` bytes are kept
-    void trim(uint64_t most)
+    // gives a device's blocks back until at most `most` bytes of it are kept
+    void trim(int device, uint64_t most)
     {
-        std::vector<Block> out;
+        for (;;) {
+            void *p = nullptr;
+            {
+                std::lock_guard<std::mutex> g(mu);
+                uint64_t total = 0;
+                size_t first = kept.size();
+                for (size_t i = kept.size(); i-- > 0;)
+                    if (kept[i].device == device) {
+                        total += kept[i].size;
+                        first = i;
+                    }
+                if (total <= most) return;
+                p = kept[first].p;
+                kept.erase(kept.begin() + (ptrdiff_t)first);
+            }
+            (void)hipFree(p);
+        }
+    }
+    // the same on every device
+    void trim_all(uint64_t most)
+    {
+        int last = -1;
         {
             std::lock_guard<std::mutex> g(mu);
-            size_t n = 0;
-            while (n < kept.size() && total > most) total -= kept[n++].size;
-            out.assign(kept.begin(), kept.begin() + (ptrdiff_t)n);
-            kept.erase(kept.begin(), kept.begin() + (ptrdiff_t)n);
+            for (const Block &b : kept) last = std::max(last, b.device);
         }
-        for (const Block &b : out) (void)hipFree(b.p);
+        for (int device = 0; device <= last; ++device) trim(device, most);
     }
 
 private:
@@ -91,7 +107,6 @@ private:
     };
     std::mutex mu;
     std::vector<Block> kept;   // the longest unused first
-    uint64_t total = 0;
 };
 
 // Device scratch of one call, released when the call ends.  Three sources:

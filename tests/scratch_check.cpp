@@ -95,10 +95,45 @@ static void check_cap()
     }
 }
 
+// ---- what is kept is kept per device ---------------------------------------
+static uint64_t kept_on(int dev) { return dev_used[dev]; }   // (no call is running)
+
+static void check_devices()
+{
+    const uint64_t block = 6ull << 30;
+    auto fill = [&](int dev) {
+        cur_dev = dev;
+        DevAlloc mem(nullptr, dev, nullptr);
+        void *p;
+        for (int i = 0; i < 5; ++i) CHECK(mem.raw(&p, block) == hipSuccess);
+    };
+    // each keeps its 30 GiB: less than kKeep on either, more on both
+    fill(0);
+    fill(1);
+    CHECK(kept_on(0) == 5 * block && kept_on(1) == 5 * block);
+    // a shortage on one device leaves the other's blocks alone
+    dev_size[0] = 6 * block;
+    {
+        cur_dev = 0;
+        DevAlloc mem(nullptr, 0, nullptr);
+        void *p;
+        CHECK(mem.raw(&p, 6 * block) == hipSuccess);   // only when all of device 0's are given back
+        CHECK(dev_used[0] == 6 * block && kept_on(1) == 5 * block);
+    }
+    // above kKeep the longest unused go, on that device
+    CHECK(kept_on(0) == 0 && kept_on(1) == 5 * block);
+    ScratchCache::get().trim(1, block);
+    CHECK(kept_on(1) == block);
+    fill(0);
+    ScratchCache::get().trim_all(0);
+    CHECK(kept_on(0) == 0 && kept_on(1) == 0 && live.empty());
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "cap")) check_cap();
+    else if (!strcmp(what, "devices")) check_devices();
     else return 2;
     printf("%s: bad %d, %llu mallocs\n", what, bad, (unsigned long long)n_malloc);
     return bad != 0;
