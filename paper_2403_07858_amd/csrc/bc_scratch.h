@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "bc.h"
@@ -61,11 +62,17 @@ public:
     }
     void put(int device, void *p, uint64_t size)
     {
+        bool listed = true;
         {
             std::lock_guard<std::mutex> g(mu);
-            kept.push_back({p, size, device});
+            try {   // (called from a destructor, under C entries)
+                kept.push_back({p, size, device});
+            } catch (const std::bad_alloc &) {
+                listed = false;
+            }
         }
-        trim(device, kKeep);
+        if (listed) trim(device, kKeep);
+        else (void)hipFree(p);
     }
     // gives a device's blocks back until at most `most` bytes of it are kept
     void trim(int device, uint64_t most)

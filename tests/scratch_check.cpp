@@ -4,6 +4,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <random>
 
 #include "bc_scratch.h"
@@ -42,6 +43,17 @@ extern "C" hipError_t hipStreamSynchronize(hipStream_t)
     return hipSuccess;
 }
 extern "C" hipError_t hipGetLastError(void) { return hipSuccess; }
+
+// host memory that runs out when told to
+static bool host_full = false;
+void *operator new(size_t n)
+{
+    void *p = host_full ? nullptr : malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 static int bad = 0;
 #define CHECK(x)                                             \
@@ -129,11 +141,26 @@ static void check_devices()
     CHECK(kept_on(0) == 0 && kept_on(1) == 0 && live.empty());
 }
 
+// ---- a call that ends with no host memory left still ends ------------------
+static void check_host_full()
+{
+    {
+        DevAlloc mem(nullptr, 0, nullptr);
+        void *p;
+        for (int i = 0; i < 40; ++i) CHECK(mem.raw(&p, 600ull << 20) == hipSuccess);
+        host_full = true;   // its blocks find no room in the list of kept ones
+    }
+    ScratchCache::get().trim_all(0);
+    host_full = false;
+    CHECK(live.empty());
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "cap")) check_cap();
     else if (!strcmp(what, "devices")) check_devices();
+    else if (!strcmp(what, "host_full")) check_host_full();
     else return 2;
     printf("%s: bad %d, %llu mallocs\n", what, bad, (unsigned long long)n_malloc);
     return bad != 0;

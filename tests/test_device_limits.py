@@ -21,6 +21,6 @@ def test_every_column_has_a_number_of_its_own(tmp_path):
     run_check("column_limits_check", tmp_path)
 
 
-@pytest.mark.parametrize("part", ["cap", "devices"])
+@pytest.mark.parametrize("part", ["cap", "devices", "host_full"])
 def test_scratch(part, tmp_path):
     run_check("scratch_check", tmp_path, part)
