@@ -1694,57 +1694,113 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     const uint64_t t_enum0 = bcint::steady_ns();
     unsigned long long *d_wave_clock = nullptr;   // instrumented: per-wave start / end clocks
     uint64_t n_wave_clock = 0;
+    bcdev::ActiveRoot *d_roots = nullptr;
+    uint64_t *d_pool = d_pool_fused;
+    // Runtime split (queries with p_A >= 5): a subtask ring of up to 4M
+    // entries of 16 bytes, cleared before the launch, and a heap of up to
+    // 64M words for the split tasks' level-2 blocks.
+    uint32_t split_cap = 0;
+    uint4 *d_ring = nullptr;
+    unsigned long long *d_sub = nullptr;
+    uint64_t *d_heap = nullptr;
+    uint64_t heap_words = 0;
+    // Enumeration grid: waves_per_cu wavefronts per CU; each wave owns a
+    // slab big enough for the deepest task of this plan.
+    uint32_t blocks = 0, col_blocks = 0;
+    uint64_t slab_words = 0;
+    uint64_t *d_slab = nullptr;
+    bcdev::ColRoot *d_croots = nullptr;
+    uint2 *d_split2 = nullptr;
+    bcdev::ColParams cp{};
+    // the global-set path's
+    bcdev::SetRoot *d_sroots = nullptr;
+    uint32_t *d_ids = nullptr;
+    uint32_t set_blocks = 0;
+    uint64_t *d_sslab = nullptr;
+    auto take_memory = [&]() -> hipError_t {
+        hipError_t e = hipSuccess;
+        auto get = [&](auto **p, uint64_t count) {
+            if (e == hipSuccess) e = mem.get(p, count);
+        };
+        // a grid's slabs: halved until they fit
+        auto fit_blocks = [&](uint64_t words) {
+            uint32_t n = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / bcdev::kWavesPerBlock);
+            uint64_t budget = 64ull << 30;   // bytes of HBM for all slabs
+            budget = std::min(budget, mem.room() > 512 ? mem.room() - 512 : 0);
+            while (n > 1 && (uint64_t)n * bcdev::kWavesPerBlock * words * 8 > budget) n /= 2;
+            return n;
+        };
+        if (!plan.empty()) {
+            get(&d_roots, aroots.size());
+            if (!rows_ready) get(&d_pool, pool_words);
+            bool any_deep = false;
+            for (uint32_t r = 0; r < n_row_roots; ++r) any_deep = any_deep || cjobs[aroots[r].job].pA >= 5;
+            split_cap = 0;
+            if (any_deep && split_rows != 0 && split_rows != 0xffffffffu) {
+                uint64_t cap = 1ull << 22;
+                if (ex.fixed || mem.cap) cap = std::min<uint64_t>(cap, mem.room() / 4 / sizeof(uint4));
+                uint64_t hw = 1ull << 26;
+                if (ex.fixed || mem.cap) hw = std::min<uint64_t>(hw, mem.room() / 4 / 8);
+                if (cap >= 1024 && hw >= 4096) {
+                    get(&d_ring, cap);
+                    get(&d_sub, 4);
+                    get(&d_heap, hw);
+                    split_cap = (uint32_t)cap;
+                    heap_words = hw;
+                }
+            }
+            if (!croots.empty()) {
+                get(&d_croots, croots.size());
+                get(&cp.cols, col_words);
+                if (col_units) {
+                    get(&cp.left, col_units + 2 * n_split + n_children);
+                    get(&cp.split, n_split);
+                    get(&d_split2, n_split);
+                }
+                // 16 wavefronts per CU, and the same share of them as of the row search's 12
+                col_blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / 3);
+                // no more than there are units for (the split ones: 16 a unit at most)
+                col_blocks = (uint32_t)std::min<uint64_t>(col_blocks, (n_whole + col_units * 16) / bcdev::kWavesPerBlock + 1);
+                if (col_slab) get(&cp.slab, (uint64_t)col_blocks * bcdev::kWavesPerBlock * bcdev::kColSlabWords);
+            }
+            slab_words = std::max(slab_need, left_slab_need);   // the two runs share the slabs
+            blocks = fit_blocks(slab_words);
+            get(&d_slab, (uint64_t)blocks * bcdev::kWavesPerBlock * slab_words);
+            if (instrument) get(&d_wave_clock, 2ull * blocks * bcdev::kWavesPerBlock);
+        }
+        if (!splan.empty()) {
+            get(&d_sroots, sroots.size());
+            get(&d_ids, set_ids);
+            set_blocks = fit_blocks(set_slab_need);
+            get(&d_sslab, (uint64_t)set_blocks * bcdev::kWavesPerBlock * set_slab_need);
+        }
+        return e;
+    };
+    // The columns take about as much again as the rows of their roots, and
+    // their lists: where that is too much, the row search alone may still fit.
+    const DevAlloc::Mark before = mem.mark();
+    hipError_t me = take_memory();
+    if (me == hipErrorOutOfMemory && !croots.empty()) {
+        mem.rollback(before);
+        std::fill(mode.begin(), mode.end(), (uint8_t)kByRows);
+        lay_out();
+        n_split = n_children = 0;
+        cp = bcdev::ColParams{};
+        me = take_memory();
+    }
+    if (me != hipSuccess) return hip_error(me, "device scratch of the search");
     if (!plan.empty()) {
-        bcdev::ActiveRoot *d_roots;
-        uint64_t *d_pool = d_pool_fused;
-        BC_HIP(mem.get(&d_roots, aroots.size()));
         BC_HIP(hipMemcpyAsync(d_roots, aroots.data(), aroots.size() * sizeof(bcdev::ActiveRoot), hipMemcpyHostToDevice,
                               st));
-        if (!rows_ready) {
-            BC_HIP(mem.get(&d_pool, pool_words));
+        if (!rows_ready)
             BC_HIP(bcdev::launch_rows_build(d_cjobs, d_roots, (uint32_t)aroots.size(), d_pool, rs, root_blocks,
                                             d_queue + 1, d_slots, st));
-        }
         tm.mark(3, st);
-        // Runtime split (queries with p_A >= 5): a subtask ring of up to 4M
-        // entries of 16 bytes, cleared before the launch, and a heap of up to
-        // 64M words for the split tasks' level-2 blocks.
-        uint32_t split_cap = 0;
-        uint4 *d_ring = nullptr;
-        unsigned long long *d_sub = nullptr;
-        uint64_t *d_heap = nullptr;
-        uint64_t heap_words = 0;
-        bool any_deep = false;
-        for (uint32_t r = 0; r < n_row_roots; ++r) any_deep = any_deep || cjobs[aroots[r].job].pA >= 5;
-        if (any_deep && split_rows != 0 && split_rows != 0xffffffffu) {
-            uint64_t cap = 1ull << 22;
-            if (ex.fixed || mem.cap) cap = std::min<uint64_t>(cap, mem.room() / 4 / sizeof(uint4));
-            uint64_t hw = 1ull << 26;
-            if (ex.fixed || mem.cap) hw = std::min<uint64_t>(hw, mem.room() / 4 / 8);
-            if (cap >= 1024 && hw >= 4096) {
-                BC_HIP(mem.get(&d_ring, cap));
-                BC_HIP(mem.get(&d_sub, 4));
-                BC_HIP(mem.get(&d_heap, hw));
-                BC_HIP(fill_u32((uint32_t *)d_ring, cap * 4, 0u, st));
-                BC_HIP(fill_u32((uint32_t *)d_sub, 8, 0u, st));
-                split_cap = (uint32_t)cap;
-                heap_words = hw;
-            }
+        if (split_cap) {
+            BC_HIP(fill_u32((uint32_t *)d_ring, split_cap * 4ull, 0u, st));
+            BC_HIP(fill_u32((uint32_t *)d_sub, 8, 0u, st));
         }
-        // Enumeration grid: waves_per_cu wavefronts per CU; each wave owns a
-        // slab big enough for the deepest task of this plan.
-        uint32_t blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / bcdev::kWavesPerBlock);
-        bcdev::ColParams cp{};
         if (!croots.empty()) {
-            bcdev::ColRoot *d_croots;
-            BC_HIP(mem.get(&d_croots, croots.size()));
-            BC_HIP(mem.get(&cp.cols, col_words));
-            uint2 *d_split2 = nullptr;
-            if (col_units) {
-                BC_HIP(mem.get(&cp.left, col_units + 2 * n_split + n_children));
-                BC_HIP(mem.get(&cp.split, n_split));
-                BC_HIP(mem.get(&d_split2, n_split));
-            }
             BC_HIP(hipMemcpyAsync(d_croots, croots.data(), croots.size() * sizeof(bcdev::ColRoot),
                                   hipMemcpyHostToDevice, st));
             cp.jobs = d_cjobs;
@@ -1759,12 +1815,6 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             cp.n_left = d_queue + 16;   // and the children's counter behind it
             cp.left_cap = n_children;
             cp.slots = d_slots;
-            // 16 wavefronts per CU, and the same share of them as of the row search's 12
-            uint32_t col_blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / 3);
-            // no more than there are units for (the split ones: 16 a unit at most)
-            col_blocks = (uint32_t)std::min<uint64_t>(col_blocks, (n_whole + col_units * 16) / bcdev::kWavesPerBlock + 1);
-            if (col_slab)
-                BC_HIP(mem.get(&cp.slab, (uint64_t)col_blocks * bcdev::kWavesPerBlock * bcdev::kColSlabWords));
             cp.split_cap = n_split;
             cp.n_split = d_queue + 18;
             BC_HIP(bcdev::launch_columns(cp, col_blocks, st));
@@ -1780,12 +1830,6 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 BC_HIP(bcdev::launch_columns(sp, col_blocks, st));
             }
         }
-        uint64_t slab_budget = 64ull << 30;   // bytes of HBM for all slabs
-        slab_budget = std::min(slab_budget, mem.room() > 512 ? mem.room() - 512 : 0);
-        const uint64_t slab_words = std::max(slab_need, left_slab_need);   // the two runs share the slabs
-        while (blocks > 1 && (uint64_t)blocks * bcdev::kWavesPerBlock * slab_words * 8 > slab_budget) blocks /= 2;
-        uint64_t *d_slab;
-        BC_HIP(mem.get(&d_slab, (uint64_t)blocks * bcdev::kWavesPerBlock * slab_words));
         bcdev::EnumParams prm{};
         prm.jobs = d_cjobs;
         prm.roots = d_roots;
@@ -1801,7 +1845,6 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         prm.split_cap = split_cap;
         prm.ring = d_ring;
         if (instrument) {
-            BC_HIP(mem.get(&d_wave_clock, 2ull * blocks * bcdev::kWavesPerBlock));
             BC_HIP(fill_u32((uint32_t *)d_wave_clock, 4ull * blocks * bcdev::kWavesPerBlock, 0u, st));
             n_wave_clock = (uint64_t)blocks * bcdev::kWavesPerBlock;
         }
@@ -1835,21 +1878,11 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     }
     if (!splan.empty()) {
         // global-set path: candidate ids, then the enumeration over them
-        bcdev::SetRoot *d_sroots;
-        uint32_t *d_ids;
-        BC_HIP(mem.get(&d_sroots, sroots.size()));
-        BC_HIP(mem.get(&d_ids, set_ids));
         BC_HIP(hipMemcpyAsync(d_sroots, sroots.data(), sroots.size() * sizeof(bcdev::SetRoot), hipMemcpyHostToDevice,
                               st));
         BC_HIP(bcdev::launch_cand_ids(d_cjobs, d_sroots, (uint32_t)sroots.size(), d_ids, rs,
                                       (uint32_t)std::min<uint64_t>(sroots.size(), std::max<uint32_t>(rs_blocks, 1)),
                                       d_queue + 8, d_slots, st));
-        uint32_t blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / bcdev::kWavesPerBlock);
-        uint64_t slab_budget = 64ull << 30;
-        slab_budget = std::min(slab_budget, mem.room() > 512 ? mem.room() - 512 : 0);
-        while (blocks > 1 && (uint64_t)blocks * bcdev::kWavesPerBlock * set_slab_need * 8 > slab_budget) blocks /= 2;
-        uint64_t *d_sslab;
-        BC_HIP(mem.get(&d_sslab, (uint64_t)blocks * bcdev::kWavesPerBlock * set_slab_need));
         bcdev::SetParams sp{};
         sp.jobs = d_cjobs;
         sp.roots = d_sroots;
@@ -1864,7 +1897,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         sp.slab_words = set_slab_need;
         sp.queue = task_queue(5);
         sp.slots = d_slots;
-        BC_HIP(bcdev::launch_enumerate_sets(sp, blocks, st));
+        BC_HIP(bcdev::launch_enumerate_sets(sp, set_blocks, st));
         tasks += set_tasks;
     }
     tm.mark(4, st);

@@ -220,6 +220,26 @@ struct DevAlloc {
         *p = v;
         return hipSuccess;
     }
+    // gives back what was taken since the mark (no queued work may use it)
+    struct Mark {
+        size_t n_ptrs;
+        uint8_t *chunk;
+        uint64_t chunk_left, next_chunk, fixed_used, total;
+    };
+    Mark mark() const { return {ptrs.size(), chunk, chunk_left, next_chunk, fixed_used, total}; }
+    void rollback(const Mark &m)
+    {
+        for (; ptrs.size() > m.n_ptrs; ptrs.pop_back()) {
+            if (hook) hook->free(hook->ctx, ptrs.back().p, st);
+            else ScratchCache::get().put(device, ptrs.back().p, ptrs.back().size);
+        }
+        chunk = m.chunk;
+        chunk_left = m.chunk_left;
+        next_chunk = m.next_chunk;
+        fixed_used = m.fixed_used;
+        total = m.total;
+        fixed_short = false;
+    }
     template <typename T>
     hipError_t get(T **p, uint64_t count)
     {
