@@ -72,9 +72,10 @@ enum { BC_ANCHOR_AUTO = -1, BC_ANCHOR_U = 0, BC_ANCHOR_V = 1 };
  * Device-memory hook (e.g. a framework's caching allocator).  alloc returns
  * `bytes` of device memory usable by work queued on `stream` (a hipStream_t),
  * or NULL when it cannot (the call then fails with BC_E_OOM after releasing
- * everything it took, or goes on without the column search where that fits).  free gives back a block alloc returned; the library
- * calls it with the same stream once all work it queued on the block is on
- * that stream, so a stream-ordered allocator may reuse the block at once.
+ * everything it took, or goes on without the column search where that fits).
+ * free gives back a block alloc returned; the library calls it with the same
+ * stream once all work it queued on the block is on that stream, so a
+ * stream-ordered allocator may reuse the block at once.
  * Blocks a graph keeps (bc_build) are freed by bc_free with stream NULL.
  * The hook object and ctx must outlive every call and graph that uses them.
  */

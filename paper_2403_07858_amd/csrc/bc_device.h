@@ -161,6 +161,38 @@ struct RootOut {
                             // and for roots of at most kColTripleMax neighbours)
 };
 
+// Row storage of the candidate pass: each block reserves kRowChunk pool words at
+// a time and hands them out, rows longer than an eighth of that are reserved by
+// themselves.  So less than an eighth of a used-up chunk is left over, and a pool
+// of row_pool_words(w, n) words serves n blocks whatever roots of w words in all
+// they meet, in any order.
+constexpr uint32_t kRowChunk = 4096;
+__host__ __device__ constexpr uint64_t row_pool_words(uint64_t w, uint64_t n_blocks) { return w + w / 7 + n_blocks * kRowChunk + 1; }
+struct RowChunk {
+    unsigned long long at, end;
+};
+// The offset of need words of a pool of cap, ~0 if there is no room.  chunk:
+// words reserved at once; reserve(n): the pool's head before it advanced by n.
+template <typename F>
+__host__ __device__ __forceinline__ unsigned long long take_rows(RowChunk &c, uint64_t need, uint64_t chunk, uint64_t cap, F reserve)
+{
+    if (8 * need > chunk) {
+        const unsigned long long o = reserve(need);
+        return o + need <= cap ? o : ~0ull;
+    }
+    if (c.end - c.at < need) {
+        const unsigned long long o = reserve(chunk);
+        if (o + chunk > cap) {
+            c.at = c.end = 0;
+            return o + need <= cap ? o : ~0ull;
+        }
+        c.at = o;
+        c.end = o + chunk;
+    }
+    c.at += need;
+    return c.at - need;
+}
+
 struct RootScratch {
     uint32_t *cnt;          // per block: nA_max counters, all zero between roots
     uint32_t *touched;      // per block: nA_max touched ids

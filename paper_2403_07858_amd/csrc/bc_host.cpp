@@ -1321,6 +1321,8 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             // a fixed region gives the pool at most a third of what is left;
             // roots that find no room are rebuilt into an exactly sized pool
             if (ex.fixed || mem.cap) pool_cap = std::max<uint64_t>(1, std::min<uint64_t>(pool_cap, mem.room() / 3 / 8));
+            // else the blocks reserve chunks of it, and what these leave over comes on top
+            else pool_cap = bcdev::row_pool_words(pool_cap, (uint64_t)ncu * (bcdev::kRbSmallPerCu + bcdev::kRbBigPerCu));
             BC_HIP(mem.get(&d_pool_fused, pool_cap));
             bcdev::RootParams rp{};
             rp.jobs = d_cjobs;
@@ -1330,7 +1332,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             rp.pool = d_pool_fused;
             rp.pool_cap = pool_cap;
             // a limited pool is not reserved ahead of need
-            rp.chunk = ex.fixed || mem.cap ? 0 : 4096;
+            rp.chunk = ex.fixed || mem.cap ? 0 : bcdev::kRowChunk;
             rp.out = d_found;
             // per-vertex counts of p_A = 2 jobs are attributed by this pass
             const bc_status bs = root_build(rp, d_queue + 4, any_pv);

@@ -616,7 +616,7 @@ hipError_t launch_rows_build(const Job *jobs, const ActiveRoot *roots, uint32_t 
 // |N(u) n N(w)| (the popcount) and the row.  Wider roots, and all of a large
 // block's, count in the first pass, index their candidates, and set the row
 // bits in a second pass in LDS, a group of row words at a time.  Row storage is
-// taken from the pool by bumping a chunk the block reserved, so counting and
+// taken from the pool by bumping a chunk the block reserved (take_rows), so counting and
 // row building need no host round trip.
 //
 // What bounds it is the chain of latencies of a root: its queue ticket, the
@@ -758,7 +758,8 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
     uint32_t parts_hint = 1;           // id ranges the previous root needed
     float per_wedge = 0.0f;            // 2-hop vertices per wedge of the previous root
     // thread 0's: pool words reserved, items taken, the next ticket, roots listed
-    unsigned long long chunk_at = 0, chunk_end = 0, at = 0, at_end = 0, ticket = 0;
+    RowChunk chunk{0, 0};
+    unsigned long long at = 0, at_end = 0, ticket = 0;
     uint32_t n_listed = 0;
     if (tid == 0) ticket = atomicAdd(prm.queue, 1ull);
     const unsigned long long n_items = prm.list ? *prm.n_list : prm.total_roots;
@@ -841,21 +842,10 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
                 }
             }
         };
-        // rows of need words: from the block's chunk, or a new one, or as they are
-        auto take_rows = [&](unsigned long long need) {
-            if (chunk_end - chunk_at < need) {
-                const unsigned long long want = need > prm.chunk ? need : prm.chunk;
-                const unsigned long long o = atomicAdd(prm.pool_head, want);
-                if (o + want > prm.pool_cap) {
-                    chunk_at = chunk_end = 0;
-                    if (o + need <= prm.pool_cap) s_off = o;
-                    return;
-                }
-                chunk_at = o;
-                chunk_end = o + want;
-            }
-            s_off = chunk_at;
-            chunk_at += need;
+        // room for a root's rows
+        auto take = [&](unsigned long long need) {
+            s_off = take_rows(chunk, need, prm.chunk, prm.pool_cap,
+                              [&](uint64_t n) { return atomicAdd(prm.pool_head, (unsigned long long)n); });
         };
         // The rows' bits, from a second wedge pass: groups of row planes that
         // fit the LDS, each from its own 64-neighbour runs, so that no wedge is
@@ -1020,7 +1010,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
             done = fits;
             if (fits) {
                 build = rows && k >= jb.pA - 1;
-                if (build && tid == 0) take_rows((unsigned long long)k * W1);
+                if (build && tid == 0) take((unsigned long long)k * W1);
                 __syncthreads();
                 off = s_off;
                 if (build && off != ~0ull) {
@@ -1082,7 +1072,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
                 const uint32_t at = block_excl_scan<NW>(s_bkt[tid], s_wsum, &k);
                 s_bkt[tid] = at;
                 build = k >= jb.pA - 1;
-                if (build && tid == 0) take_rows((unsigned long long)k * W1);
+                if (build && tid == 0) take((unsigned long long)k * W1);
                 __syncthreads();
                 off = s_off;
             }
@@ -1136,7 +1126,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
             __syncthreads();
             k = s_k;
             build = rows && k >= jb.pA - 1;
-            if (build && tid == 0) take_rows((unsigned long long)k * W1);
+            if (build && tid == 0) take((unsigned long long)k * W1);
             __syncthreads();
             off = s_off;
             if (build && off != ~0ull) {

@@ -24,3 +24,7 @@ def test_every_column_has_a_number_of_its_own(tmp_path):
 @pytest.mark.parametrize("part", ["cap", "devices", "host_full"])
 def test_scratch(part, tmp_path):
     run_check("scratch_check", tmp_path, part)
+
+
+def test_row_pool_serves_its_roots(tmp_path):
+    run_check("row_pool_check", tmp_path)
