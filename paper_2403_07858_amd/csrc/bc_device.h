@@ -228,6 +228,7 @@ struct ColParams {
     uint32_t n_whole;       // roots [0, n_whole) are one unit each, taken one by one
     uint32_t unit_chunk;    // consecutive units of the other roots taken per queue pop
     uint32_t instrument;
+    uint32_t timed;         // some job has a deadline
     uint64_t n_units;       // units of roots [n_whole, n_roots), or room in `units`
     const uint64_t *pool;   // candidate rows
     uint64_t *cols;         // candidate columns (k_transpose writes, k_columns reads)

@@ -1811,6 +1811,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             cp.n_whole = n_whole;
             cp.unit_chunk = roots_per_wave ? roots_per_wave : 4u;
             cp.instrument = instrument ? 1u : 0u;
+            for (const bcdev::Job &d : cjobs) cp.timed |= d.deadline != 0;
             cp.n_units = col_units;
             cp.pool = d_pool;
             cp.queue = task_queue(2);

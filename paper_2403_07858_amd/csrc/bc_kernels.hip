@@ -2798,13 +2798,16 @@ __device__ __forceinline__ void col_level(const uint64_t (&v)[NC], col_ptr<NC> b
 }
 
 // The whole sum over s columns of NC words in LDS: tuples of R columns per
-// lane, D columns in the loops.
+// lane, D columns in the loops.  False if it stopped at the deadline (0: none),
+// which it looks at once a round, and once a step of the outermost of three loops.
 template <int NC, int D, int P>
-__device__ __forceinline__ void col_search(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, Acc &acc)
+__device__ __forceinline__ bool col_search(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, uint64_t deadline,
+                                           Acc &acc)
 {
     const uint32_t ln = lane_id();
     constexpr uint32_t st = col_stride(NC) / 2;
     for (uint32_t base = 0; base < n_tup; base += kWaveSize) {
+        if (past_deadline(deadline)) return false;
         const uint32_t idx = min(base + ln, n_tup - 1);
         const uint32_t e = col_tuple_at(R, idx);
         const uint32_t bits = R == 5 ? 6 : 7, last = e >> (bits * (R - 1));
@@ -2851,6 +2854,7 @@ __device__ __forceinline__ void col_search(col_ptr<NC> buf, uint32_t s, uint32_t
                 if constexpr (D > 2) {
                     acc.t += div_factorial<P>(sum);
                     sum = 0;
+                    if (past_deadline(deadline)) return false;
                 }
             }
         }
@@ -2866,6 +2870,7 @@ __device__ __forceinline__ void col_search(col_ptr<NC> buf, uint32_t s, uint32_t
                 col_level<NC, D - 1, P>(u, buf, k + 1, s, sum);
                 acc.t += div_factorial<P>(sum);
                 sum = 0;
+                if (past_deadline(deadline)) return false;
             }
         } else {
             col_level<NC, D, P>(v, buf, k, s, sum);
@@ -2873,34 +2878,31 @@ __device__ __forceinline__ void col_search(col_ptr<NC> buf, uint32_t s, uint32_t
         }
     }
     acc_flush(acc);
+    return true;
 }
 
 template <int NC, int D>
-__device__ __forceinline__ void col_search_p(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, uint32_t p,
-                                             Acc &acc)
+__device__ __forceinline__ bool col_search_p(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, uint32_t p,
+                                             uint64_t deadline, Acc &acc)
 {
     switch (p) {
-    case 2: col_search<NC, D, 2>(buf, s, R, n_tup, acc); break;
-    case 3: col_search<NC, D, 3>(buf, s, R, n_tup, acc); break;
-    case 4: col_search<NC, D, 4>(buf, s, R, n_tup, acc); break;
-    default: col_search<NC, D, 5>(buf, s, R, n_tup, acc); break;
+    case 2: return col_search<NC, D, 2>(buf, s, R, n_tup, deadline, acc);
+    case 3: return col_search<NC, D, 3>(buf, s, R, n_tup, deadline, acc);
+    case 4: return col_search<NC, D, 4>(buf, s, R, n_tup, deadline, acc);
+    default: return col_search<NC, D, 5>(buf, s, R, n_tup, deadline, acc);
     }
 }
 
 // q columns out of s: the loops take D = col_loops(q, words) of them.
 template <int NC>
-__device__ __forceinline__ void col_search_q(col_ptr<NC> buf, uint32_t s, uint32_t q, uint32_t D, uint32_t n_tup,
-                                             uint32_t p, Acc &acc)
+__device__ __forceinline__ bool col_search_q(col_ptr<NC> buf, uint32_t s, uint32_t q, uint32_t D, uint32_t n_tup,
+                                             uint32_t p, uint64_t deadline, Acc &acc)
 {
-    switch (D) {
-    case 1: col_search_p<NC, 1>(buf, s, q - 1, n_tup, p, acc); break;
-    case 2:
-        if constexpr (NC <= 16) col_search_p<NC, 2>(buf, s, q - 2, n_tup, p, acc);
-        break;
-    default:
-        if constexpr (NC <= 8) col_search_p<NC, 3>(buf, s, q - 3, n_tup, p, acc);
-        break;
-    }
+    if (D == 1) return col_search_p<NC, 1>(buf, s, q - 1, n_tup, p, deadline, acc);
+    if constexpr (NC <= 16)
+        if (D == 2) return col_search_p<NC, 2>(buf, s, q - 2, n_tup, p, deadline, acc);
+    if constexpr (NC <= 8) return col_search_p<NC, 3>(buf, s, q - 3, n_tup, p, deadline, acc);
+    return true;   // not reached: col_loops gives no more
 }
 
 // 64 x 64 bit transpose across the wave: lane r's bit c becomes lane c's bit r.
@@ -2936,6 +2938,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_transpose(ColParams prm)
 
 constexpr uint32_t kLeftBuf = 64;   // listed units a wave gathers before it writes them out
 constexpr uint64_t kColLong = 400000;   // wave instructions (about a millisecond) past which a unit is split up
+constexpr uint32_t kColWatch = 1000;    // innermost steps past which a search looks at the deadline
 
 // Leaf sum for one more column: lane's column shares n candidates, choose p.
 __device__ __forceinline__ uint64_t leaf_falling(uint32_t n, uint32_t p)
@@ -2948,6 +2951,9 @@ __device__ __forceinline__ uint64_t leaf_falling(uint32_t n, uint32_t p)
     }
 }
 
+// TIMED: some job has a deadline.  (Looking at it inside the searches costs
+// registers: 1.2M edges (5,5) 44.8 against 42.2 ms, so calls without one do not.)
+template <bool TIMED>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_columns(ColParams prm)
 {
     __shared__ __align__(16) uint64_t s_buf[kWavesPerBlock][kColBuf];
@@ -3210,16 +3216,20 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
             const uint32_t D = col_loops(q, nc, s);
             const ColCost cost = col_costs.of(q, D, s);
             const uint32_t n_tup = __builtin_amdgcn_readfirstlane(cost.tuples);
+            // (a short one, some 20 us, does not look at the clock)
+            const uint64_t watch = TIMED ? readlane64(cost.leaf >= kColWatch ? jb.deadline : 0ull, 0) : 0ull;
+            bool done = true;
             switch (nc) {
-            case 2: col_search_q<2>((col_ptr<2>)buf, s, q, D, n_tup, p, acc); break;
-            case 4: col_search_q<4>((col_ptr<4>)buf, s, q, D, n_tup, p, acc); break;
-            case 6: col_search_q<6>((col_ptr<6>)buf, s, q, D, n_tup, p, acc); break;
-            case 8: col_search_q<8>((col_ptr<8>)buf, s, q, D, n_tup, p, acc); break;
-            case 12: col_search_q<12>((col_ptr<12>)buf, s, q, D, n_tup, p, acc); break;
-            case 16: col_search_q<16>((col_ptr<16>)buf, s, q, D, n_tup, p, acc); break;
-            case 24: col_search_q<24>((col_ptr<24>)buf, s, q, D, n_tup, p, acc); break;
-            default: col_search_q<40>((col_ptr<40>)buf, s, q, D, n_tup, p, acc); break;
+            case 2: done = col_search_q<2>((col_ptr<2>)buf, s, q, D, n_tup, p, watch, acc); break;
+            case 4: done = col_search_q<4>((col_ptr<4>)buf, s, q, D, n_tup, p, watch, acc); break;
+            case 6: done = col_search_q<6>((col_ptr<6>)buf, s, q, D, n_tup, p, watch, acc); break;
+            case 8: done = col_search_q<8>((col_ptr<8>)buf, s, q, D, n_tup, p, watch, acc); break;
+            case 12: done = col_search_q<12>((col_ptr<12>)buf, s, q, D, n_tup, p, watch, acc); break;
+            case 16: done = col_search_q<16>((col_ptr<16>)buf, s, q, D, n_tup, p, watch, acc); break;
+            case 24: done = col_search_q<24>((col_ptr<24>)buf, s, q, D, n_tup, p, watch, acc); break;
+            default: done = col_search_q<40>((col_ptr<40>)buf, s, q, D, n_tup, p, watch, acc); break;
             }
+            if (!done && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
             wave_sync();   // the next unit writes the same words
             if (instrument) {   // lane steps, and the words they AND
                 ct.pairs += cost.leaf * 64ull;
@@ -3237,7 +3247,8 @@ hipError_t launch_columns(const ColParams &prm, uint32_t n_blocks, hipStream_t s
 {
     if (prm.n_roots == 0) return hipSuccess;
     if (!prm.units) hipLaunchKernelGGL(k_transpose, dim3(min(prm.n_roots, 4096u)), dim3(kBlockThreads), 0, stream, prm);
-    hipLaunchKernelGGL(k_columns, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    if (prm.timed) hipLaunchKernelGGL(k_columns<true>, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    else hipLaunchKernelGGL(k_columns<false>, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
     return hipGetLastError();
 }
 
