@@ -895,11 +895,13 @@ bool col_whole_ok(uint32_t pA, uint32_t qA)
 
 constexpr bcdev::ColCosts kColCosts = bcdev::make_col_costs();
 
-// Cost model of served deadlines: per enumeration depth p_A, the fewest
-// nanoseconds per unit of the whole-depth planning proxy (sum over a job's
-// roots of k^(p_A - 1) W1) seen so far in a served batch holding that one
-// job.  The proxy ignores pruning, so the fewest seen is the optimistic end:
-// a job is refused only when even that rate puts it far past its deadline.
+// Cost model of served deadlines.  Roots searched by rows: per enumeration depth
+// p_A, the fewest nanoseconds per unit of the whole-depth planning proxy (sum
+// over a job's roots of k^(p_A - 1) W1) seen so far in a served batch holding
+// that one job, all by rows.  The proxy ignores pruning, so the fewest seen is
+// the optimistic end.  Roots searched by columns: their units at the device's
+// rate, without what lies under them.  A job is refused only when even these put
+// it far past its deadline.
 struct RateBook {
     std::mutex mu;
     double ns_per_unit[33] = {0};   // 0 = nothing seen yet
@@ -909,6 +911,7 @@ RateBook &rate_book()
     static RateBook rb;
     return rb;
 }
+constexpr double kInstrPerNs = 600.0;   // wave instructions, all CUs busy
 constexpr double kRefuseMargin = 4.0;   // refuse when the estimate exceeds 4x the time left
 
 // Where one run_jobs call takes its stream and device scratch from.
@@ -1377,25 +1380,6 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             spec_jobs[i] = {a};
         }
     }
-    // Served batches: a job that the cost model says cannot finish before its
-    // deadline, even at the best rate seen for its depth, is refused here,
-    // before the enumeration, instead of holding the device until it expires.
-    std::vector<char> refused(nj, 0);
-    if (short_first) {
-        RateBook &rb = rate_book();
-        std::lock_guard<std::mutex> lk(rb.mu);
-        const uint64_t now = bcint::steady_ns();
-        for (uint32_t j : cj) {
-            const uint64_t dl = specs[jobs[j].spec].deadline_ns;
-            const uint32_t pA = jobs[j].pA;
-            if (!job_live[j] || !dl || pA < 3 || pA > 32 || rb.ns_per_unit[pA] <= 0) continue;
-            const double left = dl > now ? (double)(dl - now) : 0.0;
-            if ((double)jobs[j].weight * rb.ns_per_unit[pA] > kRefuseMargin * left) {
-                refused[j] = 1;
-                job_live[j] = 0;
-            }
-        }
-    }
     struct Plan {
         uint32_t c;  // index into cj / cjobs
         uint32_t root, k, w1;
@@ -1499,10 +1483,6 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             set_slab_need = std::max<uint64_t>(set_slab_need, (uint64_t)pA * (mu + pl.k / 2 + 2) + 16);
         }
     }
-    // rows already built by the fused kernel, unless some root found no room
-    bool rows_ready = fused;
-    for (const Plan &pl : plan)
-        if (fused && found[pl.item].off == ~0ull) rows_ready = false;
     // Which search a root takes, by its estimated wave instructions: by rows
     // (a task per candidate, of which about a third keep enough common
     // neighbours), by columns (a unit per neighbour: transposes of its share
@@ -1525,13 +1505,18 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         const Side &A = side_of(pl);
         return (uint32_t)(A.h_ptr[pl.root + 1] - A.h_ptr[pl.root]);
     };
+    // all units of a root, before what lies under them
+    auto unit_cost = [&](const Plan &pl) -> double {
+        const uint64_t wk = (pl.k + 63) / 64;
+        return (double)(degree_of(pl) * (400 + 10 * wk + 65ull * pl.w1 * std::max<uint64_t>(1, wk / 4)));
+    };
     for (size_t r = 0; r < plan.size(); ++r) {
         const Plan &pl = plan[r];
         const uint32_t pA = cjobs[pl.c].pA, q = cjobs[pl.c].qA, du = degree_of(pl), wk = (pl.k + 63) / 64;
         const uint64_t k = pl.k, w1 = pl.w1;
         const uint64_t rows = pA == 3 ? k * k * w1 / 34 + 100
                                       : k * (250 + 6ull * wk * w1 + bcdev::row_estimate(k / 3, pA - 2));
-        const uint64_t units = du * (400 + 10ull * wk + 65 * w1 * std::max<uint64_t>(1, wk / 4));
+        const uint64_t units = (uint64_t)unit_cost(pl);
         if (col_units_ok(pA, q) && bcdev::col_root_fits(du, wk) &&
             units * (pA == 3 ? 1 : 4) < rows && (pA == 3 || q <= pA + 1 || du <= 192 || found[pl.item].bits > 100 * k))
             mode[r] = kByColumns;
@@ -1559,6 +1544,46 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     // search at the device's rate (6e8 wave instructions a millisecond) they
     // cost what they spare (a 20k-edge count of 0.45 ms took 0.58 ms).
     if (rows_spared < 200000000) std::fill(mode.begin(), mode.end(), (uint8_t)kByRows);
+    // Served batches: a job that the cost model says cannot finish before its
+    // deadline is refused here, before the enumeration, instead of holding the
+    // device until it expires.  Its roots are priced by the search they take.
+    std::vector<char> refused(nj, 0);
+    if (short_first) {
+        std::vector<double> units(nj, 0.0), instr(nj, 0.0);   // by rows: proxy units; by columns: wave instructions
+        for (size_t r = 0; r < plan.size(); ++r) {
+            const Plan &pl = plan[r];
+            const uint32_t j = cj[pl.c];
+            if (mode[r] == kByRows) units[j] += std::pow((double)pl.k, jobs[j].pA - 1.0) * pl.w1;
+            else instr[j] += mode[r] == kWhole ? (double)whole_cost[r] : unit_cost(pl);
+        }
+        RateBook &rb = rate_book();
+        std::lock_guard<std::mutex> lk(rb.mu);
+        const uint64_t now = bcint::steady_ns();
+        for (uint32_t j : cj) {
+            const uint64_t dl = specs[jobs[j].spec].deadline_ns;
+            const uint32_t pA = jobs[j].pA;
+            if (!job_live[j] || !dl || pA < 3 || pA > 32) continue;
+            const double left = dl > now ? (double)(dl - now) : 0.0;
+            if (units[j] * rb.ns_per_unit[pA] + instr[j] / kInstrPerNs > kRefuseMargin * left) {
+                refused[j] = 1;
+                job_live[j] = 0;
+            }
+        }
+        size_t keep = 0;
+        for (size_t r = 0; r < plan.size(); ++r) {
+            if (refused[cj[plan[r].c]]) continue;
+            plan[keep] = plan[r];
+            mode[keep] = mode[r];
+            whole_cost[keep++] = whole_cost[r];
+        }
+        plan.resize(keep);
+        mode.resize(keep);
+        whole_cost.resize(keep);
+    }
+    // rows already built by the fused kernel, unless some root found no room
+    bool rows_ready = fused;
+    for (const Plan &pl : plan)
+        if (fused && found[pl.item].off == ~0ull) rows_ready = false;
     std::vector<bcdev::ActiveRoot> aroots(plan.size());
     std::vector<bcdev::ColRoot> croots;
     uint64_t pool_words = 0, tasks = 0, row_tasks = 0, col_words = 0, col_units = 0;
@@ -1919,14 +1944,14 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         for (size_t r = 0; 2 * r < h_pv[j].size(); ++r)
             specs[jobs[j].spec].pv_out[r] = bc_u128{h_pv[j][2 * r], h_pv[j][2 * r + 1]};
     if (short_first) {
-        // learn from a served batch that enumerated exactly one job to the end
+        // learn from a served batch that enumerated exactly one job to the end, by rows
         int only = -1, live = 0;
         for (uint32_t j : cj)
             if (job_live[j] && jobs[j].pA >= 3) {
                 only = (int)j;
                 ++live;
             }
-        if (live == 1 && jobs[only].weight > 0 && !(hs[only].flags & (bcdev::FLAG_TIMEOUT | bcdev::FLAG_CAPACITY))) {
+        if (live == 1 && croots.empty() && jobs[only].weight > 0 && !(hs[only].flags & (bcdev::FLAG_TIMEOUT | bcdev::FLAG_CAPACITY))) {
             const double ns = (double)(bcint::steady_ns() - t_enum0) / (double)jobs[only].weight;
             RateBook &rb = rate_book();
             std::lock_guard<std::mutex> lk(rb.mu);
