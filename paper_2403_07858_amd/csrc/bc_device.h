@@ -145,8 +145,11 @@ constexpr uint32_t kOneChild = 0x40000000u;   // step of a child loop that ends 
 constexpr uint32_t kMaxShares = 64;        // most tasks a candidate's search is shared out to
 constexpr int kSortCap = 4096;          // candidates sorted in LDS up to this many
 constexpr int kRbWaves = 8;             // waves per large block of the fused per-root kernel
-constexpr int kRbThreads = kWaveSize * kRbWaves;
 constexpr uint32_t kRbBigPerCu = 2;     // large blocks of it on a CU
+constexpr int kRbWideWaves = 16;        // waves per wide block, one on a CU
+constexpr uint32_t kRbWideDegree = 32768;   // widest root of a job from which on the large roots take wide blocks
+static_assert(kRbWideDegree <= 65536, "large blocks count in 16 bits");
+constexpr uint32_t kRbManyWedges = 32768;   // wedges a root has on average for which small blocks are not tried
 constexpr uint32_t kRbSmallPerCu = 5;   // small blocks (four waves)
 constexpr uint32_t kQueues = 16;        // counters of a task queue,
 constexpr uint32_t kQueueStride = 16;   // this many 64-bit words apart
@@ -289,9 +292,9 @@ hipError_t launch_cand_count(const Job *jobs, const uint64_t *job_root_prefix, u
 // Candidate counts and rows in one kernel; rows go to pool[out[r].off ..]
 // (bump-allocated from *pool_head, capacity pool_cap words).  n_small blocks of
 // four waves take every root and list those too large for them in retry; then
-// n_big blocks of kRbThreads threads with 77 KiB of LDS each take these
-// (n_small 0: all).
-hipError_t launch_root_build(const RootParams &prm, uint32_t n_small, uint32_t n_big, bool per_vertex,
+// n_big large or wide blocks take these (n_small 0: all).  Large blocks: no root
+// of kRbWideDegree neighbours or more.
+hipError_t launch_root_build(const RootParams &prm, uint32_t n_small, uint32_t n_big, bool wide, bool per_vertex,
                              hipStream_t stream);
 hipError_t launch_rows_build(const Job *jobs, const ActiveRoot *roots, uint32_t n_roots,
                              uint64_t *pool, RootScratch scratch, uint32_t n_blocks,

@@ -1143,10 +1143,21 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     // every candidate-pass launch are capped at rs_blocks.
     bcdev::RootScratch rs{};
     uint32_t rs_blocks = 0;
+    uint32_t widest = 0;   // most neighbours of any root
+    double wedges_per_root = 0;
     {
+        double wedges = 0, roots = 0;
         uint32_t nA_all = 0;
         for (uint32_t j = 0; j < nj; ++j)
-            if (!jobs[j].trivial_zero && jobs[j].pA >= 2) nA_all = std::max(nA_all, hjobs[j].nA);
+            if (!jobs[j].trivial_zero && jobs[j].pA >= 2) {
+                nA_all = std::max(nA_all, hjobs[j].nA);
+                const bc_graph *g = specs[jobs[j].spec].g;
+                const double n = (double)jobs[j].root_hi - jobs[j].root_lo;
+                widest = std::max(widest, g->side[jobs[j].anchor].max_deg);
+                wedges += g->side[1 - jobs[j].anchor].deg_pairs * (n / hjobs[j].nA);
+                roots += n;
+            }
+        if (roots) wedges_per_root = wedges / roots;
         if (nA_all) {
             uint64_t nb = (uint64_t)ncu * 2;
             if (ex.fixed || mem.cap)   // at most a quarter of the fixed region or cap
@@ -1169,8 +1180,20 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         const uint32_t wpc = std::min(waves_per_cu, 12u);
         const bool limited = ex.fixed || mem.cap;
         const uint32_t room = limited ? std::max(1u, rs_blocks / 2) : rs_blocks;
+        // Roots of very many wedges are no work for four waves, and where there
+        // are few of them no work for eight either, since the longest one is the
+        // time of the pass; a root of tens of thousands of neighbours is a long
+        // chain by itself (64 neighbours a step).  (2,2), before the small blocks
+        // came, with them, and with this rule: 200 roots of 10000 neighbours 0.66,
+        // 1.37 and 0.77 ms, 40 of 60000 2.0, 2.7 and 1.9, 1000 of 3000 1.0, 1.25 and
+        // 0.85, 4000 with 40 hubs of 70000 2.6, 5.5 and 2.4; 6000 with 40 hubs of
+        // 40000 1.8 and 1.5.  The limits lie where these and 100k roots of 5200
+        // wedges (2M edges, small and large blocks: 5.1 against 6.8 ms) part.
+        const bool many = wedges_per_root > bcdev::kRbManyWedges;
+        const bool wide = widest >= bcdev::kRbWideDegree || (many && prm.total_roots <= 4ull * ncu);
+        const uint32_t per_cu = wide ? 1 : bcdev::kRbBigPerCu;
         const uint32_t n_big = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(prm.total_roots, room),
-                                                            std::max<uint64_t>(1, (uint64_t)ncu * bcdev::kRbBigPerCu * wpc / 12));
+                                                            std::max<uint64_t>(1, (uint64_t)ncu * per_cu * wpc / 12));
         uint32_t n_small = (uint32_t)std::min<uint64_t>(
             prm.total_roots, std::max<uint64_t>(1, (uint64_t)ncu * bcdev::kRbSmallPerCu * wpc / 12));
         prm.sc = rs;
@@ -1179,7 +1202,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         prm.n_retry = q + 2;
         prm.queue_big = q + 3;
         prm.slots = d_slots;
-        if (prm.total_roots >> 32)
+        if (many || prm.total_roots >> 32)
             n_small = 0;
         else if ((uint64_t)(rs_blocks - n_big) * rs.stride >= prm.total_roots)
             prm.retry = rs.cand + (uint64_t)n_big * rs.stride;
@@ -1187,7 +1210,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             BC_HIP(mem.get(&prm.retry, prm.total_roots));
         else
             n_small = 0;
-        BC_HIP(bcdev::launch_root_build(prm, n_small, n_big, pv, st));
+        BC_HIP(bcdev::launch_root_build(prm, n_small, n_big, wide, pv, st));
         return BC_OK;
     };
 

@@ -54,6 +54,13 @@ __device__ __forceinline__ uint64_t bcast64(uint64_t v, int src)
     return ((uint64_t)hi << 32) | lo;
 }
 
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t lane)
+{
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, (int)lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)lane);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Orders this wave's earlier LDS / global writes before its later reads.
 __device__ __forceinline__ void wave_sync()
 {
@@ -334,8 +341,9 @@ __device__ __forceinline__ void wedges_flat(const Job &jb, uint64_t ub, uint32_t
 #pragma unroll
             for (uint32_t b = 32; b; b >>= 1) {
                 // la + b <= 63: the larger steps already taken add up to at most 64 - 2b
-                if (__shfl(excl, (int)(la + b)) <= xa) la += b;
-                if (__shfl(excl, (int)(lb + b)) <= xb) lb += b;
+                const uint32_t ea = __shfl(excl, (int)(la + b)), eb = __shfl(excl, (int)(lb + b));   // both in flight
+                la += ea <= xa ? b : 0u;
+                lb += eb <= xb ? b : 0u;
             }
             const uint64_t pa = bcast64(base, (int)la) + xa, pb = bcast64(base, (int)lb) + xb;
             uint32_t wa = 0, wb = 0;
@@ -374,8 +382,9 @@ __device__ __forceinline__ void wedges_flat_capped(const Job &jb, uint64_t ub, u
             uint32_t la = 0, lb = 0;
 #pragma unroll
             for (uint32_t b = 32; b; b >>= 1) {
-                if (__shfl(excl, (int)(la + b)) <= xa) la += b;
-                if (__shfl(excl, (int)(lb + b)) <= xb) lb += b;
+                const uint32_t ea = __shfl(excl, (int)(la + b)), eb = __shfl(excl, (int)(lb + b));   // both in flight
+                la += ea <= xa ? b : 0u;
+                lb += eb <= xb ? b : 0u;
             }
             const uint64_t pa = bcast64(base, (int)la) + xa, pb = bcast64(base, (int)lb) + xb;
             uint32_t wa = 0, wb = 0;
@@ -622,17 +631,23 @@ hipError_t launch_rows_build(const Job *jobs, const ActiveRoot *roots, uint32_t 
 // What bounds it is the chain of latencies of a root: its queue ticket, the
 // offsets of its neighbours' rows, the wedges, the scans between barriers.  So
 // it runs twice: blocks of four waves with a small table, five to a CU, which
-// take the roots whose 2-hop vertices fit and list the others (BIG false); then
-// blocks of eight waves, two to a CU, over that list, with 16-bit counts.  A
-// job's fields and leaf values are read when the job changes.  Against one
+// take the roots whose 2-hop vertices fit and list the others (RB_SMALL); then
+// blocks of eight waves, two to a CU, over that list, with 16-bit counts
+// (RB_LARGE).  Where there are few roots (a root's own time is what counts) or
+// roots of 65536 neighbours and more, the list goes to blocks of sixteen waves,
+// one to a CU, with 32-bit counts instead (RB_WIDE).  A job's fields and leaf
+// values are read when the job changes.  Against one
 // block of sixteen waves a CU for every root, one ticket a root and a sort of
 // each root's candidates: 2M edges (4,4) 7.0 against 8.9 ms, 5M (3,3) 14.2
 // against 22.6, 1.2M (5,5) 3.2 against 4.5, 256 small graphs 3.6 against 17.4,
 // 150k edges 0.44 against 0.79 ms.
 
-constexpr uint32_t kHashSlots = 8192;       // LDS table entries of the large blocks
+constexpr uint32_t kHashSlots = 8192;       // LDS table entries of the large and wide blocks
 constexpr uint32_t kSmallSlots = 2048;      // and of the small ones
 constexpr uint32_t kBigRowBuf = 3072;       // words of rows a large block builds at once
+constexpr uint32_t kWideRowBuf = 8192;      // and a wide one
+constexpr uint32_t kSmallWedges = 1u << 17; // wedges of a root past which a small block leaves it to the others,
+constexpr uint32_t kSmallDegree = 4096;     // and neighbours
 constexpr uint32_t kSmallDistinct = 1500;   // 2-hop vertices a small table is tried for
 constexpr uint32_t kSmallCap = 1800;        // and holds
 constexpr uint32_t kHashProbes = 128;       // longest probe sequence before falling back
@@ -718,17 +733,23 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wsum
 
 // PV: per-vertex counts for p_A = 2 jobs that ask for them (each leaf {u, w}
 // adds its C(|N(u) n N(w)|, q_A) to w at once and, summed per wave, to u).
-template <bool PV, int NW, uint32_t SLOTS>
-__global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k_root_build(RootParams prm)
+enum RootBlock { RB_SMALL, RB_LARGE, RB_WIDE };
+constexpr int rb_waves(RootBlock k) { return k == RB_SMALL ? 4 : k == RB_LARGE ? kRbWaves : kRbWideWaves; }
+
+template <bool PV, RootBlock KIND>
+__global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4) void k_root_build(RootParams prm)
 {
-    constexpr bool BIG = SLOTS == kHashSlots;
+    constexpr bool BIG = KIND != RB_SMALL;
+    constexpr int NW = rb_waves(KIND);
+    constexpr uint32_t SLOTS = BIG ? kHashSlots : kSmallSlots;
     constexpr uint32_t NT = NW * kWaveSize, PER = SLOTS / NT;   // threads; slots of each in the scans
-    constexpr uint32_t BUF = BIG ? kBigRowBuf : SLOTS;
+    constexpr uint32_t BUF = KIND == RB_SMALL ? SLOTS : KIND == RB_LARGE ? kBigRowBuf : kWideRowBuf;
     static_assert(!BIG || 2 * BUF >= kRowsCap);
+    using map_t = std::conditional_t<KIND == RB_WIDE, uint32_t, uint16_t>;
     __shared__ uint32_t s_key[SLOTS];                 // w + 1, 0 = empty
     __shared__ unsigned long long s_row[BUF];         // small: row word or count of the slot; LDS rows
-    __shared__ __align__(4) uint16_t s_map[SLOTS];    // row index of the slot's vertex, kNoRow if none;
-                                                      // large: the slot's count before that
+    __shared__ __align__(4) map_t s_map[SLOTS];       // row index of the slot's vertex, kNoRow if none;
+                                                      // large, wide: the slot's count before that
     uint32_t *s_sort = (uint32_t *)s_row;             // large: candidates being sorted (id ranges)
     __shared__ uint32_t s_bkt[NT];                  // candidates by rank interval
     __shared__ uint64_t s_leaf[kLeafLen];           // C(n, qA) below 2^64
@@ -745,7 +766,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
         for (uint32_t x = tid; x < SLOTS; x += NT) {
             s_key[x] = 0;
             if constexpr (!BIG) s_row[x] = 0;
-            else if (x < SLOTS / 2) ((uint32_t *)s_map)[x] = 0;
+            else if (x < SLOTS * sizeof(map_t) / 4) ((uint32_t *)s_map)[x] = 0;
         }
     };
     clear_table();
@@ -873,23 +894,29 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
             }
         };
         volatile uint32_t *flag = &s_flag;
-        // large blocks: the slot's 16-bit count, two to a word (du < 2^16)
-        auto count_one = [&](int h) { atomicAdd((uint32_t *)s_map + (h >> 1), 1u << (16 * (h & 1))); };
+        // the slot's count: large blocks, 16 bits of it, two to a word (du < 2^16)
+        auto count_one = [&](int h) {
+            if constexpr (KIND == RB_WIDE) atomicAdd(&s_map[h], 1u);
+            else atomicAdd((uint32_t *)s_map + (h >> 1), 1u << (16 * (h & 1)));
+        };
         bool in_lds = false;
         if constexpr (!BIG) {
             // wedges of the root: every wave sums them over its lanes
-            uint32_t wedges = 0;
-            if (jb.nA - u - 1u > kSmallDistinct) {
+            const uint32_t after = jb.nA - u - 1u;
+            const bool hub = du > kSmallDegree;
+            uint64_t wedges = 0;
+            if (!hub && (after > kSmallDistinct || (uint64_t)after * du > kSmallWedges)) {
                 for (uint32_t j = lane_id(); j < du; j += kWaveSize) {
                     const uint32_t v = jb.adjA[ub + j];
-                    wedges += (uint32_t)(jb.ptrB[v + 1] - (jb.ptrB[v] + jb.rposA[ub + j] + 1));
+                    wedges += jb.ptrB[v + 1] - (jb.ptrB[v] + jb.rposA[ub + j] + 1);
                 }
-                wedges = (uint32_t)wave_sum_u64(wedges);
-                wedges = (uint32_t)__builtin_amdgcn_readfirstlane((int)wedges);
+                wedges = readlane64(wave_sum_u64(wedges), 0);
             }
             // more 2-hop vertices than the table is for, by the previous
-            // root's ratio (neighbouring ranks are alike): a large block's
-            const bool try_it = (float)wedges * per_wedge <= (float)kSmallDistinct;
+            // root's ratio (neighbouring ranks are alike), or more neighbours
+            // or wedges than four waves should walk: a large block's
+            const bool few = !hub && wedges <= kSmallWedges;
+            const bool try_it = few && (float)wedges * per_wedge <= (float)kSmallDistinct;
             if (try_it) {
                 wedges_flat_capped<NW, true>(jb, ub, du, kSmallCap, &s_claimed, flag, [&](uint32_t jj, uint32_t w) {
                     bool fresh;
@@ -902,7 +929,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
                 __syncthreads();
                 in_lds = s_flag == 0;
                 if (wedges) per_wedge = (float)(in_lds ? s_claimed : 2 * SLOTS) / (float)wedges;
-            } else {
+            } else if (few) {
                 per_wedge *= 0.98f;   // so that a change of the ratio is found out
             }
             if (!in_lds) {
@@ -921,7 +948,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
         // wider ones count.  It gives up at the first insert that finds no
         // slot within kHashProbes, and is skipped when the previous root of
         // this block needed several id ranges.
-        if (BIG && parts_hint == 1 && du < 65536u) {
+        if (BIG && parts_hint == 1) {
             wedges_flat_capped<NW, false>(jb, ub, du, 0, &s_claimed, flag, [&](uint32_t, uint32_t w) {
                 bool fresh;
                 const int h = hash_insert<SLOTS>(s_key, w, &fresh);
@@ -937,7 +964,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
         uint64_t off = ~0ull;
         bool build = false;
         bool done = in_lds;
-        if (BIG && !in_lds && du < 65536u) {
+        if (BIG && !in_lds) {
             // The candidates are the ids above u.  Take them in id ranges, each
             // counted in a fresh table of at most kCapRange distinct vertices;
             // a range that passes it is halved and counted again, and the width
@@ -1023,7 +1050,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
                         const uint32_t kv = s_sort[x] + 1u;
                         uint32_t h = hash_slot<SLOTS>(kv - 1u);
                         while (atomicCAS(&s_key[h], 0u, kv) != 0u) h = (h + 1) & (SLOTS - 1);
-                        s_map[h] = (uint16_t)x;
+                        s_map[h] = (map_t)x;
                     }
                     __syncthreads();   // s_sort has been read
                     rows_by_planes(k, off, [&](uint32_t w) {
@@ -1087,7 +1114,7 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
                     if (!cand) continue;
                     const uint32_t x = atomicAdd(&s_bkt[(kv - 1u - u) >> sh], 1u);
                     if (one) pool[off + x] = e;
-                    else s_map[h] = (uint16_t)x;
+                    else s_map[h] = (map_t)x;
                 }
                 if (!one) {
                     __syncthreads();   // every count has been read
@@ -1169,25 +1196,28 @@ __global__ __launch_bounds__(NW *kWaveSize, SLOTS == kSmallSlots ? 5 : 4) void k
     if (cur_job != 0xffffffffu) wave_flush(slots, jb.slot, acc, ovf, 0, 0);
 }
 
-hipError_t launch_root_build(const RootParams &prm, uint32_t n_small, uint32_t n_big, bool per_vertex,
+template <RootBlock KIND>
+static void run_root_build(const RootParams &p, uint32_t n_blocks, bool per_vertex, hipStream_t stream)
+{
+    constexpr int threads = rb_waves(KIND) * kWaveSize;
+    if (per_vertex) hipLaunchKernelGGL((k_root_build<true, KIND>), dim3(n_blocks), dim3(threads), 0, stream, p);
+    else hipLaunchKernelGGL((k_root_build<false, KIND>), dim3(n_blocks), dim3(threads), 0, stream, p);
+}
+
+hipError_t launch_root_build(const RootParams &prm, uint32_t n_small, uint32_t n_big, bool wide, bool per_vertex,
                              hipStream_t stream)
 {
     if (prm.total_roots == 0) return hipSuccess;
     RootParams p = prm;
     if (n_small) {
-        if (per_vertex)
-            hipLaunchKernelGGL((k_root_build<true, 4, kSmallSlots>), dim3(n_small), dim3(4 * kWaveSize), 0, stream, p);
-        else
-            hipLaunchKernelGGL((k_root_build<false, 4, kSmallSlots>), dim3(n_small), dim3(4 * kWaveSize), 0, stream, p);
+        run_root_build<RB_SMALL>(p, n_small, per_vertex, stream);
         // what they listed
         p.list = prm.retry;
         p.n_list = prm.n_retry;
         p.queue = prm.queue_big;
     }
-    if (per_vertex)
-        hipLaunchKernelGGL((k_root_build<true, kRbWaves, kHashSlots>), dim3(n_big), dim3(kRbThreads), 0, stream, p);
-    else
-        hipLaunchKernelGGL((k_root_build<false, kRbWaves, kHashSlots>), dim3(n_big), dim3(kRbThreads), 0, stream, p);
+    if (wide) run_root_build<RB_WIDE>(p, n_big, per_vertex, stream);
+    else run_root_build<RB_LARGE>(p, n_big, per_vertex, stream);
     return hipGetLastError();
 }
 
@@ -1216,13 +1246,6 @@ __device__ __forceinline__ void leaf_add(Acc &a, const u128 *binom, uint32_t n_o
         return;
     }
     a.ovf |= __builtin_add_overflow(a.v, binom[n], &a.v);
-}
-
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t lane)
-{
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, (int)lane);
-    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)lane);
-    return ((uint64_t)hi << 32) | lo;
 }
 
 // Per-wave copy of the low 64 bits of C(n, q) for n < len, valid for the job
