@@ -1185,7 +1185,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         // time of the pass; a root of tens of thousands of neighbours is a long
         // chain by itself (64 neighbours a step).  (2,2), before the small blocks
         // came, with them, and with this rule: 200 roots of 10000 neighbours 0.66,
-        // 1.37 and 0.77 ms, 40 of 60000 2.0, 2.7 and 1.9, 1000 of 3000 1.0, 1.25 and
+        // 1.37 and 0.53 ms, 40 of 60000 2.0, 2.7 and 1.9, 1000 of 3000 1.0, 1.25 and
         // 0.85, 4000 with 40 hubs of 70000 2.6, 5.5 and 2.4; 6000 with 40 hubs of
         // 40000 1.8 and 1.5.  The limits lie where these and 100k roots of 5200
         // wedges (2M edges, small and large blocks: 5.1 against 6.8 ms) part.

@@ -782,8 +782,12 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
     RowChunk chunk{0, 0};
     unsigned long long at = 0, at_end = 0, ticket = 0;
     uint32_t n_listed = 0;
-    if (tid == 0) ticket = atomicAdd(prm.queue, 1ull);
     const unsigned long long n_items = prm.list ? *prm.n_list : prm.total_roots;
+    // The next ticket is drawn while a root is worked on, unless there are few
+    // for each block: then blocks that start early would hold roots that a later
+    // one could take at once (200 roots of 10000 neighbours (2,2): 0.41 against 0.61 ms).
+    const bool ahead = n_items >= 4ull * gridDim.x;
+    if (tid == 0 && ahead) ticket = atomicAdd(prm.queue, 1ull);
     // A ticket is up to eight roots: the queue's atomics go one after another,
     // about 20 ns each (100k roots at one a ticket: 2.3 ms, whatever they held).
     const uint32_t batch = (uint32_t)max(1ull, min(8ull, n_items / (8ull * gridDim.x)));
@@ -796,11 +800,12 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
         if (tid == 0) {
             const bool fetch = at == at_end;
             if (fetch) {
+                if (!ahead) ticket = atomicAdd(prm.queue, 1ull);
                 at = ticket * batch;
                 at_end = min(at + batch, n_items);
             }
             s_item = at >= n_items ? ~0ull : prm.list ? (unsigned long long)prm.list[at] : at;
-            if (fetch) ticket = atomicAdd(prm.queue, 1ull);
+            if (fetch && ahead) ticket = atomicAdd(prm.queue, 1ull);
             ++at;
             s_k = 0;
             s_nt = 0;
