@@ -246,6 +246,9 @@ struct ColParams {
     uint4 *left;            // units that the row search takes: the same, and one child row or kNoJ
     unsigned long long *n_left;
     uint64_t left_cap;      // room in left: every unit fits, and a heavy one's children if they do
+    uint64_t left_room;     // its entries: the long units lie from the end down,
+    unsigned long long *n_long;   // this many
+    uint32_t deep;          // a deep run may take them
     Slot *slots;
 };
 
@@ -256,10 +259,11 @@ struct EnumParams {
     uint32_t task_chunk;    // consecutive tasks taken per queue pop (>= 1)
     uint64_t n_tasks;
     // the column search's roots and the units that it left to the row search
-    // (the instances with COLS): tasks are left[0 .. *n_left)
+    // (the instances with COLS): task t is left[t * left_step], t < *n_left
     const ColRoot *col_roots;
     const uint4 *left;
     const unsigned long long *n_left;
+    int32_t left_step;      // 1, or -1 for the long units (from the list's end down)
     const uint64_t *cols;
     const uint64_t *pool;
     uint64_t *slab;         // per-wave global scratch
@@ -303,6 +307,9 @@ hipError_t launch_enumerate(const EnumParams &prm, uint32_t n_blocks, hipStream_
 // The column search: k_transpose writes the columns of n_roots roots, k_columns
 // counts their units and lists those that the row search has to take.
 hipError_t launch_columns(const ColParams &prm, uint32_t n_blocks, hipStream_t stream);
+// The long units that k_columns left: to the row search's list, or searched by
+// columns after all.
+hipError_t launch_columns_long(const ColParams &prm, uint32_t n_blocks, hipStream_t stream);
 // The row search over the units listed by k_columns.
 hipError_t launch_enumerate_left(const EnumParams &prm, uint32_t n_blocks, hipStream_t stream);
 // Candidate ids of the global-set roots: for root r, the w > u sharing >= qA

@@ -28,6 +28,7 @@ using bcdev::u128;
 namespace {
 
 thread_local std::string g_last_error;
+thread_local bcint::ColumnWork g_columns{};
 
 bc_status set_error(bc_status s, const std::string &msg)
 {
@@ -1090,7 +1091,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     BC_HIP(mem.get(&d_tab, tab_off[nj]));
     BC_HIP(mem.get(&d_slots, nj + 1));   // slot nj: sample jobs
     // single counters, then the task queues of the searches' launches
-    constexpr uint32_t kSingles = 32, kTaskQueues = 6;
+    constexpr uint32_t kSingles = 32, kTaskQueues = 8;
     BC_HIP(mem.get(&d_queue, kSingles + kTaskQueues * bcdev::kQueueWords));
     auto task_queue = [&](uint32_t x) { return d_queue + kSingles + x * bcdev::kQueueWords; };
     {
@@ -1612,6 +1613,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     uint64_t pool_words = 0, tasks = 0, row_tasks = 0, col_words = 0, col_units = 0;
     uint64_t slab_need = 64, left_slab_need = 64;   // words per wave: row search, its run over left units
     uint32_t n_row_roots = 0, n_whole = 0;
+    bool any_wide_unit = false;
     // The work under a candidate grows with the (p_A - 2)-subsets of the rows it
     // keeps, and one wavefront does it.  On a graph whose row search is that of
     // a few hubs (some eighty candidates each, wide rows that keep each other)
@@ -1646,6 +1648,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         pool_words = tasks = row_tasks = col_words = col_units = 0;
         slab_need = left_slab_need = 64;
         n_row_roots = n_whole = 0;
+        any_wide_unit = false;
         croots.clear();
         // active roots: by rows, then by columns, then whole ones, the longest first
         std::vector<uint32_t> order, whole;
@@ -1699,7 +1702,12 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 c.whole = m == kWhole;
                 c.n_units = m == kWhole ? 1u : c.du - (cjobs[pl.c].qA - 1);
                 col_words += (uint64_t)c.du * c.wk;
-                if (m == kByColumns) col_units += c.n_units;
+                if (m == kByColumns) {
+                    col_units += c.n_units;
+                    // (any number of columns up to these can be searched: col_fits)
+                    any_wide_unit = any_wide_unit || c.du > bcdev::kColQuadMax || c.wk > bcdev::kColWords ||
+                                    (c.du > bcdev::kColQuintMax && c.wk > 16);
+                }
             }
             if (m == kWhole) continue;   // no row search, no slab
             // per task: S2 and its prefix counts (2 W1), the compress table of
@@ -1718,9 +1726,10 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         }
     };
     lay_out();
-    // units split by a further column, twice: room for 16 per unit, 8M at most;
-    // units left to the row search child by child: 4 per unit, 1M at most
-    uint64_t n_split = std::min<uint64_t>(col_units * 16, 8ull << 20);
+    // units split by a further column, twice: room for 16 per unit, 1M to 8M (a
+    // few units of the fullest roots split up a hundredfold, and what finds no room
+    // runs on one wavefront); units left to the row search child by child: 4 per unit, 1M at most
+    uint64_t n_split = std::min<uint64_t>(std::max<uint64_t>(col_units * 16, 1ull << 20), 8ull << 20);
     uint64_t n_children = std::min<uint64_t>(col_units * 4, 1ull << 20);
     if ((ex.fixed || mem.cap) && !croots.empty()) {
         // limited scratch: shorter lists, and columns only when they leave half
@@ -1809,8 +1818,8 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 }
                 // 16 wavefronts per CU, and the same share of them as of the row search's 12
                 col_blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ncu * waves_per_cu / 3);
-                // no more than there are units for (the split ones: 16 a unit at most)
-                col_blocks = (uint32_t)std::min<uint64_t>(col_blocks, (n_whole + col_units * 16) / bcdev::kWavesPerBlock + 1);
+                // no more than there are units for
+                col_blocks = (uint32_t)std::min<uint64_t>(col_blocks, (n_whole + (col_units ? col_units + n_split : 0)) / bcdev::kWavesPerBlock + 1);
                 if (col_slab) get(&cp.slab, (uint64_t)col_blocks * bcdev::kWavesPerBlock * bcdev::kColSlabWords);
             }
             slab_words = std::max(slab_need, left_slab_need);   // the two runs share the slabs
@@ -1865,6 +1874,9 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             cp.queue = task_queue(2);
             cp.n_left = d_queue + 16;   // and the children's counter behind it
             cp.left_cap = n_children;
+            cp.deep = any_wide_unit ? 1u : 0u;
+            cp.n_long = d_queue + 20;
+            cp.left_room = col_units + 2 * n_split + n_children;
             cp.slots = d_slots;
             cp.split_cap = n_split;
             cp.n_split = d_queue + 18;
@@ -1879,6 +1891,13 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                 sp.n_split = d_queue + 19;
                 sp.queue = task_queue(3 + x);
                 BC_HIP(bcdev::launch_columns(sp, col_blocks, st));
+            }
+            if (col_units) {
+                bcdev::ColParams sp = cp;
+                sp.unit_chunk = 1;
+                sp.split = nullptr;
+                sp.queue = task_queue(6);
+                BC_HIP(bcdev::launch_columns_long(sp, col_blocks, st));
             }
         }
         bcdev::EnumParams prm{};
@@ -1918,10 +1937,17 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             lp.cols = cp.cols;
             lp.left = cp.left;
             lp.n_left = cp.n_left;
+            lp.left_step = 1;
             lp.split_cap = 0;
             lp.task_chunk = roots_per_wave ? roots_per_wave : 1u;
             lp.wave_clock = nullptr;
             lp.queue = task_queue(1);
+            BC_HIP(bcdev::launch_enumerate_left(lp, blocks, st));
+            // the long units that were neither shared out nor searched by columns
+            lp.left = cp.left + (cp.left_room - 1);
+            lp.left_step = -1;
+            lp.n_left = cp.n_long;
+            lp.queue = task_queue(7);
             BC_HIP(bcdev::launch_enumerate_left(lp, blocks, st));
         }
     } else {
@@ -2008,6 +2034,15 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
             overall = BC_E_DEVICE;
         } else {
             out[i] = bc_u128{s.lo, s.hi};
+        }
+    }
+    if (instrument) {
+        g_columns = bcint::ColumnWork{};
+        if (!croots.empty()) {
+            unsigned long long c[5];   // left, of these children, split once, split twice, long
+            BC_HIP(hipMemcpy(c, d_queue + 16, sizeof(c), hipMemcpyDeviceToHost));
+            g_columns = {n_whole, col_units, std::min<uint64_t>(c[2], n_split), std::min<uint64_t>(c[3], n_split),
+                         c[0], std::min<uint64_t>(c[1], n_children), c[4]};
         }
     }
     if (stats) {
@@ -2685,6 +2720,8 @@ uint64_t estimate_scratch_bytes(const bc_graph *g, uint32_t p, uint32_t q, uint3
 }
 
 int graph_device(const bc_graph *g) { return g->device; }
+
+extern "C" void bcint_last_columns(ColumnWork *out) { *out = g_columns; }
 
 void trim_scratch()
 {

@@ -28,6 +28,15 @@ uint64_t estimate_scratch_bytes(const bc_graph *g, uint32_t p, uint32_t q, uint3
 int graph_device(const bc_graph *g);
 // Gives the current device's memory kept from earlier calls back to the driver.
 void trim_scratch();
+// What the column search of this thread's last instrumented count did (all 0 if
+// no root went by columns): whole roots; units; units with two columns fixed, and
+// with three; units left to the row search, children among them (of units shared
+// out); long units, which are shared out or searched by the deep run.  For the
+// tests, which have to know that they reach each of these.
+struct ColumnWork {
+    uint64_t whole, units, split2, split3, left, children, n_long;
+};
+extern "C" void bcint_last_columns(ColumnWork *out);
 // Relative time of one (p,q) count on g, from the graph alone (no device
 // work): the wedges the candidate pass scans for the cheaper anchor, times 4
 // per level of L beyond two and halved per common neighbour asked beyond two.

@@ -2530,7 +2530,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
             uint32_t i, child = 0, step = 1, n_fixed = 1;
             const uint64_t *cols = nullptr;
             if constexpr (COLS) {
-                const uint4 e = prm.left[t];
+                const uint4 e = prm.left[(int64_t)t * prm.left_step];
+                if (__builtin_amdgcn_readfirstlane(e.w) != 0) continue;   // a long unit that went elsewhere
                 r = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
                 i = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
                 const uint32_t z = (uint32_t)__builtin_amdgcn_readfirstlane(e.z);
@@ -2964,9 +2965,22 @@ __global__ __launch_bounds__(kBlockThreads) void k_transpose(ColParams prm)
     }
 }
 
-constexpr uint32_t kLeftBuf = 64;   // listed units a wave gathers before it writes them out
+constexpr uint32_t kShared = 1;   // a long unit shared out child by child
+constexpr uint32_t kLeftBuf = kWaveSize;   // listed units a wave gathers before it writes them out
 constexpr uint64_t kColLong = 400000;   // wave instructions (about a millisecond) past which a unit is split up
 constexpr uint32_t kColWatch = 1000;    // innermost steps past which a search looks at the deadline
+
+// The size of a long unit left to the row search: its columns, its rows, and how
+// many are chosen of each.
+__device__ __forceinline__ uint32_t left_pack(uint32_t s, uint32_t m, uint32_t q, uint32_t p)
+{
+    static_assert(kColRootMax < 1u << 10 && 64 * kColRootWords < 1u << 13 && kColMaxQ < 8 && kColMaxP < 8);
+    return s | (m << 10) | (q << 23) | (p << 26) | (1u << 31);
+}
+__device__ __forceinline__ uint32_t left_size(uint32_t pack, uint32_t i)
+{
+    return i == 0 ? pack & 1023u : i == 1 ? (pack >> 10) & 8191u : i == 2 ? (pack >> 23) & 7u : (pack >> 26) & 7u;
+}
 
 // Leaf sum for one more column: lane's column shares n candidates, choose p.
 __device__ __forceinline__ uint64_t leaf_falling(uint32_t n, uint32_t p)
@@ -2981,11 +2995,17 @@ __device__ __forceinline__ uint64_t leaf_falling(uint32_t n, uint32_t p)
 
 // TIMED: some job has a deadline.  (Looking at it inside the searches costs
 // registers: 1.2M edges (5,5) 44.8 against 42.2 ms, so calls without one do not.)
-template <bool TIMED>
+// DEEP: the units that k_left_long leaves at the end of prm.left, too many columns
+// for one search and no list to split them into: one more column is fixed in place, and one more under
+// that, until a search takes the rest.  (That costs registers too, 42.4 -> 45.6 ms,
+// so only this run has it.)
+template <bool TIMED, bool DEEP>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_columns(ColParams prm)
 {
     __shared__ __align__(16) uint64_t s_buf[kWavesPerBlock][kColBuf];
-    __shared__ uint64_t s_kept[kWavesPerBlock][kColRootPlanes];
+    constexpr uint32_t kLevels = DEEP ? kColMaxQ - 1 : 1;
+    __shared__ uint64_t s_kept[kWavesPerBlock][kLevels][kColRootPlanes];   // a level's kept columns
+    __shared__ uint32_t s_extra[kWavesPerBlock][kLevels];                  // columns fixed in place
     __shared__ uint32_t s_rank[kWavesPerBlock][kColRootPlanes];
     __shared__ uint16_t s_list[kWavesPerBlock][2 * kWaveSize];
     __shared__ uint4 s_left[kWavesPerBlock][kLeftBuf];
@@ -3000,17 +3020,27 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
     acc.t = 0;
     Counters ct{};
     uint32_t cur_job = 0xffffffffu, n_left = 0;
+    // lists the units gathered, the long ones (w: their size) from the end down
     auto write_left = [&]() {
-        unsigned long long at = 0;
-        if (ln == 0) at = atomicAdd(prm.n_left, (unsigned long long)n_left);
-        at = bcast64(at, 0);
         wave_sync();
-        if (ln < n_left) prm.left[at + ln] = s_left[wv][ln];
+        uint4 e{};
+        if (ln < n_left) e = s_left[wv][ln];
+        const uint64_t longs = __ballot(ln < n_left && e.w != 0), rest = __ballot(ln < n_left) & ~longs;
+        unsigned long long at = 0, back = 0;
+        if (ln == 0) at = atomicAdd(prm.n_left, (unsigned long long)__popcll(rest));
+        if (longs != 0 && ln == 0) back = atomicAdd(prm.n_long, (unsigned long long)__popcll(longs));
+        at = bcast64(at, 0) + mbcnt64(rest);
+        if (longs != 0) {
+            back = prm.left_room - 1 - bcast64(back, 0) - mbcnt64(longs);
+            if ((longs >> ln) & 1u) at = back;
+        }
+        if (ln < n_left) prm.left[at] = e;
         wave_sync();
         n_left = 0;
     };
-    const uint64_t n_units = prm.units ? min((uint64_t)*prm.n_listed, prm.n_units) : prm.n_units;
-    const uint32_t n_whole = prm.units ? 0u : prm.n_whole;
+    const bool listed = DEEP || prm.units;
+    const uint64_t n_units = DEEP ? (uint64_t)*prm.n_long : prm.units ? min((uint64_t)*prm.n_listed, prm.n_units) : prm.n_units;
+    const uint32_t n_whole = listed ? 0u : prm.n_whole;
     const unsigned long long n_tickets = n_whole + (n_units + prm.unit_chunk - 1) / prm.unit_chunk;
     uint32_t home = (blockIdx.x * kWavesPerBlock + wv) % kQueues;
     for (;;) {
@@ -3026,7 +3056,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
         } else {
             t0 = (tk - n_whole) * prm.unit_chunk;
             t1 = min(t0 + prm.unit_chunk, n_units);
-            if (!prm.units) {
+            if (!listed) {
                 uint32_t hi = prm.n_roots;
                 r = prm.n_whole;
                 while (hi - r > 1) {
@@ -3039,7 +3069,13 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
         }
         for (uint64_t t = t0; t < t1; ++t) {
             uint32_t fixed = col_pack(kColNone, kColNone, kColNone);   // the unit's fixed columns
-            if (prm.units) {
+            if constexpr (DEEP) {
+                const uint4 e = prm.left[prm.left_room - 1 - t];
+                if (__builtin_amdgcn_readfirstlane(e.w) >= 0) continue;   // (bit 31 of left_pack)
+                r = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
+                fixed = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
+                rt = prm.roots[r];
+            } else if (prm.units) {
                 const uint2 e = prm.units[t];
                 r = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
                 fixed = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
@@ -3054,216 +3090,247 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
                 cur_job = rt.job;
             }
             const Job &jb = prm.jobs[rt.job];
-            if (past_deadline(jb.deadline)) {
-                if (ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
-                continue;
-            }
-            uint64_t c0 = instrument ? cycles() : 0;
-            // the search below: q of s items (bitmaps of nw words) that share p
-            const uint64_t *cols = prm.cols + rt.col_off;
-            uint32_t q = jb.qA, p = jb.pA - 1, s, nc;
-            uint64_t *buf = lds;
-            if (!prm.units && tk < n_whole) {
-                s = rt.du;
-                const uint32_t nw = rt.wk;
-                nc = col_words(nw, s);
-                const uint32_t st = col_stride(nc);
-                if (s * st > kColBuf) buf = slab;
-                for (uint32_t x = ln; x < s * nc; x += kWaveSize) {
-                    const uint32_t w = x / s, c = x - w * s;
-                    buf[c * st + w] = w < nw ? cols[(uint64_t)w * s + c] : 0ull;
-                }
-            } else {
-                // the fixed columns are the last of the unit's subsets: q more
-                // before them, and p of the candidates that hold them
-                uint32_t n_fixed;
-                const uint32_t end = unit_first(fixed, &n_fixed), planes = (end + 63) >> 6;
-                q -= n_fixed;
-                const uint64_t cw = unit_rows(cols, rt.du, rt.wk, fixed);
-                const uint32_t m = (uint32_t)wave_sum_u64(__popcll(cw));
-                if (m < p) continue;
-                s = 0;
-                for (uint32_t pl = 0; pl < planes; ++pl) {
-                    const uint32_t n = col_plane_count(cols, rt.du, rt.wk, cw, pl, end);
-                    if (q == 1) {   // each of these columns ends a subset
-                        acc.t += leaf_falling(n, p);
+            // the unit, then (DEEP) the nodes under it: one more column fixed
+            // at each of `depth` levels
+            uint32_t depth = 0;
+            // the next node: the last column of the deepest level not yet taken
+            // that has enough others before it
+            auto next_node = [&]() {
+                while (depth != 0) {
+                    wave_sync();
+                    uint32_t fixed_before;
+                    const uint32_t end = unit_first(fixed, &fixed_before);
+                    const uint32_t planes = ((depth > 1 ? s_extra[wv][depth - 2] : end) + 63) >> 6;
+                    const uint64_t x = ln < planes ? s_kept[wv][depth - 1][ln] : 0ull;
+                    const uint32_t have = (uint32_t)wave_sum_u64(__popcll(x));
+                    if (have + fixed_before + depth <= jb.qA) {   // too few for the rest of a subset
+                        --depth;
                         continue;
                     }
-                    const uint64_t kept = __ballot(n >= p);
-                    if (ln == 0) {
-                        s_kept[wv][pl] = kept;
-                        s_rank[wv][pl] = s;
-                    }
-                    s += (uint32_t)__popcll(kept);
+                    const uint32_t pl = 63u - (uint32_t)__builtin_clzll(__ballot(x != 0));
+                    const uint32_t c = 63u - (uint32_t)__builtin_clzll(readlane64(x, pl));
+                    wave_sync();
+                    if (ln == pl) s_kept[wv][depth - 1][pl] = x & ~(1ull << c);
+                    if (ln == 0) s_extra[wv][depth - 1] = pl * kWaveSize + c;
+                    wave_sync();
+                    return true;
                 }
-                if (q == 1) acc_flush(acc);
-                if (instrument) ct.filter_words += (uint64_t)end * rt.wk;
-                if (s < q) {
-                    if (instrument) ct.cyc_setup += cycles() - c0;
+                return false;
+            };
+            for (bool node = true; node; node = DEEP && next_node()) {
+                if (past_deadline(jb.deadline)) {
+                    if (ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
+                    depth = 0;
                     continue;
                 }
-                // the cheapest of: q-subsets of the columns, p-subsets of the
-                // rows as bitmaps over the columns, units with one more column
-                // fixed (about 700 instructions each, and a search over half
-                // the columns and words), the row search
-                wave_sync();
-                const uint32_t mw = (m + 63) >> 6, sw = (s + 63) >> 6;
-                const uint32_t mc = col_words(mw, s), sc = col_words(sw, m);
-                const uint32_t dc = col_loops(q, mc, s), dr = col_loops(p, sc, m);
-                const uint64_t er = row_estimate(m, p) + 400 + 20ull * rt.wk;
-                uint64_t best = er;
-                uint32_t how = 0;
-                if (col_fits(s, mw, q, slab != nullptr)) {
-                    const uint64_t e = col_estimate(col_costs.of(q, dc, s), mc, q - dc);
-                    if (e <= best) {
-                        best = e;
-                        how = 1;
+                uint64_t c0 = instrument ? cycles() : 0;
+                // the search below: q of s items (bitmaps of nw words) that share p
+                const uint64_t *cols = prm.cols + rt.col_off;
+                uint32_t q = jb.qA, p = jb.pA - 1, s, nc;
+                uint64_t *buf = lds;
+                if (!listed && tk < n_whole) {
+                    s = rt.du;
+                    const uint32_t nw = rt.wk;
+                    nc = col_words(nw, s);
+                    const uint32_t st = col_stride(nc);
+                    if (s * st > kColBuf) buf = slab;
+                    for (uint32_t x = ln; x < s * nc; x += kWaveSize) {
+                        const uint32_t w = x / s, c = x - w * s;
+                        buf[c * st + w] = w < nw ? cols[(uint64_t)w * s + c] : 0ull;
                     }
-                }
-                if (m <= (uint32_t)kWaveSize && q <= kColMaxP && sc < 16 && col_fits(m, sw, p, false) &&
-                    m * col_stride(sc) + s <= kColBuf) {
-                    const uint64_t e = col_estimate(col_costs.of(p, dr, m), sc, p - dr);
-                    if (e < best) {
-                        best = e;
-                        how = 2;
-                    }
-                }
-                if (prm.split) {
-                    uint64_t e = 700;
-                    if (q > 2) {
-                        const uint32_t sh = min(s / 2, kColTripleMax), hc = col_words((mw + 1) / 2, sh);
-                        const uint32_t dh = col_loops(q - 1, hc, sh);
-                        e += col_estimate(col_costs.of(q - 1, dh, sh), hc, q - 1 - dh);
-                    }
-                    // (a long unit is split in any case: it runs on one wave)
-                    if (s * e < best || best > kColLong) {
-                        const uint32_t n_sub = s - (q - 1);   // kept columns with q - 1 more below them
-                        unsigned long long at = 0;
-                        if (ln == 0) at = atomicAdd(prm.n_split, (unsigned long long)n_sub);
-                        at = bcast64(at, 0);
-                        if (at + n_sub <= prm.split_cap) {
-                            for (uint32_t pl = 0; pl < planes; ++pl) {
-                                const uint64_t kept = s_kept[wv][pl];
-                                const uint32_t rank = s_rank[wv][pl] + mbcnt64(kept), c = pl * kWaveSize + ln;
-                                const uint32_t more = n_fixed == 1 ? col_pack(col_fixed(fixed, 0), c, kColNone)
-                                                                   : col_pack(col_fixed(fixed, 0), col_fixed(fixed, 1), c);
-                                if (((kept >> ln) & 1u) && rank >= q - 1)
-                                    prm.split[at + rank - (q - 1)] = make_uint2(r, more);
-                            }
-                            if (instrument) ct.cyc_setup += cycles() - c0;
+                } else {
+                    // the fixed columns are the last of the unit's subsets: q more
+                    // before them, and p of the candidates that hold them
+                    uint32_t n_fixed;
+                    uint32_t end = unit_first(fixed, &n_fixed);
+                    uint64_t cw = unit_rows(cols, rt.du, rt.wk, fixed);
+                    if constexpr (DEEP)
+                        for (uint32_t x = 0; x < depth; ++x) {
+                            end = __builtin_amdgcn_readfirstlane(s_extra[wv][x]);
+                            if (ln < rt.wk) cw &= cols[(uint64_t)ln * rt.du + end];
+                        }
+                    const uint32_t planes = __builtin_amdgcn_readfirstlane((end + 63) >> 6);
+                    const uint32_t lv = DEEP ? depth : 0u;   // (of s_kept)
+                    if constexpr (DEEP) n_fixed += depth;
+                    q -= n_fixed;
+                    const uint32_t m = (uint32_t)wave_sum_u64(__popcll(cw));
+                    if (m < p) continue;
+                    s = 0;
+#pragma unroll 1
+                    for (uint32_t pl = 0; pl < planes; ++pl) {
+                        const uint32_t n = col_plane_count(cols, rt.du, rt.wk, cw, pl, end);
+                        if (q == 1) {   // each of these columns ends a subset
+                            acc.t += leaf_falling(n, p);
                             continue;
                         }
-                        // no room (from now on): the entries up to the end
-                        // are marked unused, and the next best is taken
-                        for (uint64_t x = at + ln; x < prm.split_cap; x += kWaveSize)
-                            prm.split[x] = make_uint2(kNoJ, 0);
+                        const uint64_t kept = __ballot(n >= p);
+                        if (ln == 0) {
+                            s_kept[wv][lv][pl] = kept;
+                            s_rank[wv][pl] = s;
+                        }
+                        s += (uint32_t)__popcll(kept);
                     }
-                }
-                if (how == 0) {
-                    // a long one goes child by child (p >= 3: its search
-                    // descends into them), when there is room for them
-                    bool one = true;
-                    if (er > kColLong && p >= 3) {
-                        unsigned long long at = 0;
-                        if (ln == 0) at = atomicAdd(prm.n_left + 1, (unsigned long long)m);
-                        at = bcast64(at, 0);
-                        if (at + m <= prm.left_cap) {
-                            if (ln == 0) at = atomicAdd(prm.n_left, (unsigned long long)m);
-                            at = bcast64(at, 0);
-                            for (uint32_t x = ln; x < m; x += kWaveSize) prm.left[at + x] = make_uint4(r, fixed, x, 0);
-                            one = false;
+                    if (q == 1) acc_flush(acc);
+                    if (instrument) ct.filter_words += (uint64_t)end * rt.wk;
+                    if (s < q) {
+                        if (instrument) ct.cyc_setup += cycles() - c0;
+                        continue;
+                    }
+                    // the cheapest of: q-subsets of the columns, p-subsets of the
+                    // rows as bitmaps over the columns, units with one more column
+                    // fixed (about 700 instructions each, and a search over half
+                    // the columns and words), the row search
+                    wave_sync();
+                    const uint32_t mw = (m + 63) >> 6, sw = (s + 63) >> 6;
+                    const uint32_t mc = col_words(mw, s), sc = col_words(sw, m);
+                    const uint32_t dc = col_loops(q, mc, s), dr = col_loops(p, sc, m);
+                    const uint64_t er = row_estimate(m, p) + 400 + 20ull * rt.wk;
+                    uint64_t best = er;
+                    uint32_t how = 0;
+                    if (col_fits(s, mw, q, slab != nullptr)) {
+                        const uint64_t e = col_estimate(col_costs.of(q, dc, s), mc, q - dc);
+                        if (e <= best) {
+                            best = e;
+                            how = 1;
                         }
                     }
-                    if (one) {
-                        if (ln == 0) s_left[wv][n_left] = make_uint4(r, fixed, kNoJ, 0);
-                        if (++n_left == kLeftBuf) write_left();
+                    if (m <= (uint32_t)kWaveSize && q <= kColMaxP && sc < 16 && col_fits(m, sw, p, false) &&
+                        m * col_stride(sc) + s <= kColBuf) {
+                        const uint64_t e = col_estimate(col_costs.of(p, dr, m), sc, p - dr);
+                        if (e < best) {
+                            best = e;
+                            how = 2;
+                        }
                     }
-                    if (instrument) ct.cyc_setup += cycles() - c0;
-                    continue;
+                    if (!DEEP && prm.split) {
+                        uint64_t e = 700;
+                        if (q > 2) {
+                            const uint32_t sh = min(s / 2, kColTripleMax), hc = col_words((mw + 1) / 2, sh);
+                            const uint32_t dh = col_loops(q - 1, hc, sh);
+                            e += col_estimate(col_costs.of(q - 1, dh, sh), hc, q - 1 - dh);
+                        }
+                        // (a long unit is split in any case: it runs on one wave)
+                        if (s * e < best || best > kColLong) {
+                            const uint32_t n_sub = s - (q - 1);   // kept columns with q - 1 more below them
+                            unsigned long long at = 0;
+                            if (ln == 0) at = atomicAdd(prm.n_split, (unsigned long long)n_sub);
+                            at = bcast64(at, 0);
+                            if (at + n_sub <= prm.split_cap) {
+#pragma unroll 1
+                                for (uint32_t pl = 0; pl < planes; ++pl) {
+                                    const uint64_t kept = s_kept[wv][lv][pl];
+                                    const uint32_t rank = s_rank[wv][pl] + mbcnt64(kept), c = pl * kWaveSize + ln;
+                                    const uint32_t more = n_fixed == 1 ? col_pack(col_fixed(fixed, 0), c, kColNone)
+                                                                       : col_pack(col_fixed(fixed, 0), col_fixed(fixed, 1), c);
+                                    if (((kept >> ln) & 1u) && rank >= q - 1)
+                                        prm.split[at + rank - (q - 1)] = make_uint2(r, more);
+                                }
+                                if (instrument) ct.cyc_setup += cycles() - c0;
+                                continue;
+                            }
+                            // no room (from now on): the entries up to the end
+                            // are marked unused, and the next best is taken
+                            for (uint64_t x = at + ln; x < prm.split_cap; x += kWaveSize)
+                                prm.split[x] = make_uint2(kNoJ, 0);
+                        }
+                    }
+                    if (how == 0) {
+                        if (instrument) ct.cyc_setup += cycles() - c0;
+                        if constexpr (DEEP) {   // one more column
+                            ++depth;
+                        } else {
+                            if (ln == 0)
+                                s_left[wv][n_left] = make_uint4(r, fixed, kNoJ, er > kColLong ? left_pack(s, m, q, p) : 0u);
+                            if (++n_left == kLeftBuf) write_left();
+                        }
+                        continue;
+                    }
+                    if (instrument) {
+                        const uint64_t c1 = cycles();
+                        ct.cyc_setup += c1 - c0;
+                        c0 = c1;
+                    }
+                    // list the rows, and transpose them 64 at a time into the kept
+                    // columns (one word a column when the rows are what is searched)
+                    const uint64_t *rows = prm.pool + rt.pool_off;
+                    const uint32_t cst = how == 1 ? col_stride(mc) : 1u;
+                    if (how == 1 && s * cst > kColBuf) buf = slab;
+                    uint64_t *cbuf = how == 1 ? buf : buf + (kColBuf - s);
+                    uint32_t have = 0, done = 0, ch = 0;
+                    auto chunk = [&]() {
+                        wave_sync();
+                        const bool live = done + ln < have;
+                        const uint32_t row = list[(done + ln) & (2 * kWaveSize - 1)];
+#pragma unroll 1
+                        for (uint32_t pl = 0; pl < planes; ++pl) {
+                            const uint64_t kept = s_kept[wv][lv][pl];
+                            if (kept == 0) continue;
+                            const uint64_t x = transpose64(live ? rows[(uint64_t)pl * rt.k + row] : 0ull);
+                            if ((kept >> ln) & 1u) cbuf[(s_rank[wv][pl] + mbcnt64(kept)) * cst + ch] = x;
+                        }
+                        wave_sync();
+                        done = min(done + kWaveSize, have);
+                        ++ch;
+                    };
+                    for (uint64_t nz = __ballot(cw != 0); nz != 0; nz &= nz - 1) {
+                        const uint32_t w = (uint32_t)__builtin_ctzll(nz);
+                        const uint64_t word = readlane64(cw, w);
+                        if ((word >> ln) & 1u)
+                            list[(have + mbcnt64(word)) & (2 * kWaveSize - 1)] = (uint16_t)(w * kWaveSize + ln);
+                        have += (uint32_t)__popcll(word);
+                        if (have - done >= (uint32_t)kWaveSize) chunk();
+                    }
+                    if (have > done) chunk();
+                    if (how == 1) {
+                        nc = mc;
+                        for (uint32_t c = ln; c < s; c += kWaveSize)
+                            for (uint32_t w = mw; w < nc; ++w) buf[c * cst + w] = 0;
+                    } else {   // back into rows of the kept columns
+                        nc = sc;
+                        const uint32_t st = col_stride(nc);
+                        for (uint32_t w = 0; w < nc; ++w) {
+                            const uint32_t c = w * kWaveSize + ln;
+                            const uint64_t x = transpose64(c < s ? cbuf[c] : 0ull);
+                            if (ln < m) buf[ln * st + w] = x;
+                        }
+                        s = m;
+                        const uint32_t x = p;
+                        p = q;
+                        q = x;
+                    }
                 }
+                wave_sync();
                 if (instrument) {
                     const uint64_t c1 = cycles();
-                    ct.cyc_setup += c1 - c0;
+                    ct.cyc_compact += c1 - c0;
                     c0 = c1;
                 }
-                // list the rows, and transpose them 64 at a time into the kept
-                // columns (one word a column when the rows are what is searched)
-                const uint64_t *rows = prm.pool + rt.pool_off;
-                const uint32_t cst = how == 1 ? col_stride(mc) : 1u;
-                if (how == 1 && s * cst > kColBuf) buf = slab;
-                uint64_t *cbuf = how == 1 ? buf : buf + (kColBuf - s);
-                uint32_t have = 0, done = 0, ch = 0;
-                auto chunk = [&]() {
-                    wave_sync();
-                    const bool live = done + ln < have;
-                    const uint32_t row = list[(done + ln) & (2 * kWaveSize - 1)];
-                    for (uint32_t pl = 0; pl < planes; ++pl) {
-                        const uint64_t kept = s_kept[wv][pl];
-                        if (kept == 0) continue;
-                        const uint64_t x = transpose64(live ? rows[(uint64_t)pl * rt.k + row] : 0ull);
-                        if ((kept >> ln) & 1u) cbuf[(s_rank[wv][pl] + mbcnt64(kept)) * cst + ch] = x;
-                    }
-                    wave_sync();
-                    done = min(done + kWaveSize, have);
-                    ++ch;
-                };
-                for (uint64_t nz = __ballot(cw != 0); nz != 0; nz &= nz - 1) {
-                    const uint32_t w = (uint32_t)__builtin_ctzll(nz);
-                    const uint64_t word = readlane64(cw, w);
-                    if ((word >> ln) & 1u)
-                        list[(have + mbcnt64(word)) & (2 * kWaveSize - 1)] = (uint16_t)(w * kWaveSize + ln);
-                    have += (uint32_t)__popcll(word);
-                    if (have - done >= (uint32_t)kWaveSize) chunk();
+                s = __builtin_amdgcn_readfirstlane(s);
+                const uint32_t D = col_loops(q, nc, s);
+                const ColCost cost = col_costs.of(q, D, s);
+                const uint32_t n_tup = __builtin_amdgcn_readfirstlane(cost.tuples);
+                // (a short one, some 20 us, does not look at the clock)
+                const uint64_t watch = TIMED ? readlane64(cost.leaf >= kColWatch ? jb.deadline : 0ull, 0) : 0ull;
+                bool done = true;
+                switch (nc) {
+                case 2: done = col_search_q<2>((col_ptr<2>)buf, s, q, D, n_tup, p, watch, acc); break;
+                case 4: done = col_search_q<4>((col_ptr<4>)buf, s, q, D, n_tup, p, watch, acc); break;
+                case 6: done = col_search_q<6>((col_ptr<6>)buf, s, q, D, n_tup, p, watch, acc); break;
+                case 8: done = col_search_q<8>((col_ptr<8>)buf, s, q, D, n_tup, p, watch, acc); break;
+                case 12: done = col_search_q<12>((col_ptr<12>)buf, s, q, D, n_tup, p, watch, acc); break;
+                case 16: done = col_search_q<16>((col_ptr<16>)buf, s, q, D, n_tup, p, watch, acc); break;
+                case 24: done = col_search_q<24>((col_ptr<24>)buf, s, q, D, n_tup, p, watch, acc); break;
+                default: done = col_search_q<40>((col_ptr<40>)buf, s, q, D, n_tup, p, watch, acc); break;
                 }
-                if (have > done) chunk();
-                if (how == 1) {
-                    nc = mc;
-                    for (uint32_t c = ln; c < s; c += kWaveSize)
-                        for (uint32_t w = mw; w < nc; ++w) buf[c * cst + w] = 0;
-                } else {   // back into rows of the kept columns
-                    nc = sc;
-                    const uint32_t st = col_stride(nc);
-                    for (uint32_t w = 0; w < nc; ++w) {
-                        const uint32_t c = w * kWaveSize + ln;
-                        const uint64_t x = transpose64(c < s ? cbuf[c] : 0ull);
-                        if (ln < m) buf[ln * st + w] = x;
-                    }
-                    s = m;
-                    const uint32_t x = p;
-                    p = q;
-                    q = x;
+                if (!done && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
+                if (!done) depth = 0;
+                wave_sync();   // the next unit writes the same words
+                if (instrument) {   // lane steps, and the words they AND
+                    ct.pairs += cost.leaf * 64ull;
+                    ct.pair_slots += cost.leaf * 64ull;
+                    ct.pair_words += ((uint64_t)cost.leaf + cost.outer) * 64 * nc;
+                    ct.cyc_pair += cycles() - c0;
                 }
-            }
-            wave_sync();
-            if (instrument) {
-                const uint64_t c1 = cycles();
-                ct.cyc_compact += c1 - c0;
-                c0 = c1;
-            }
-            s = __builtin_amdgcn_readfirstlane(s);
-            const uint32_t D = col_loops(q, nc, s);
-            const ColCost cost = col_costs.of(q, D, s);
-            const uint32_t n_tup = __builtin_amdgcn_readfirstlane(cost.tuples);
-            // (a short one, some 20 us, does not look at the clock)
-            const uint64_t watch = TIMED ? readlane64(cost.leaf >= kColWatch ? jb.deadline : 0ull, 0) : 0ull;
-            bool done = true;
-            switch (nc) {
-            case 2: done = col_search_q<2>((col_ptr<2>)buf, s, q, D, n_tup, p, watch, acc); break;
-            case 4: done = col_search_q<4>((col_ptr<4>)buf, s, q, D, n_tup, p, watch, acc); break;
-            case 6: done = col_search_q<6>((col_ptr<6>)buf, s, q, D, n_tup, p, watch, acc); break;
-            case 8: done = col_search_q<8>((col_ptr<8>)buf, s, q, D, n_tup, p, watch, acc); break;
-            case 12: done = col_search_q<12>((col_ptr<12>)buf, s, q, D, n_tup, p, watch, acc); break;
-            case 16: done = col_search_q<16>((col_ptr<16>)buf, s, q, D, n_tup, p, watch, acc); break;
-            case 24: done = col_search_q<24>((col_ptr<24>)buf, s, q, D, n_tup, p, watch, acc); break;
-            default: done = col_search_q<40>((col_ptr<40>)buf, s, q, D, n_tup, p, watch, acc); break;
-            }
-            if (!done && ln == 0) atomicOr(&prm.slots[jb.slot].flags, FLAG_TIMEOUT);
-            wave_sync();   // the next unit writes the same words
-            if (instrument) {   // lane steps, and the words they AND
-                ct.pairs += cost.leaf * 64ull;
-                ct.pair_slots += cost.leaf * 64ull;
-                ct.pair_words += ((uint64_t)cost.leaf + cost.outer) * 64 * nc;
-                ct.cyc_pair += cycles() - c0;
             }
         }
     }
@@ -3271,12 +3338,57 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
     if (cur_job != 0xffffffffu) enum_flush(prm.slots, prm.jobs[cur_job].slot, acc, ct, instrument);
 }
 
+// The long units that k_columns left to the row search.  Too many columns for one
+// search, and no more lists (the third run, or no room): a row search of each such
+// unit would go over the same rows again and again (K_{1000,150} (4,4): over a
+// second, by rows alone 22 ms).  Where its rows cost more than all its columns'
+// subsets (rows that keep all of each other), a unit is the deep run's.  The others
+// are the row search's, child by child (p >= 3: it descends into them) when there
+// is room.  (In k_columns itself this cost 2 to 3 % of the counts, in registers.)
+__global__ __launch_bounds__(kBlockThreads) void k_left_long(ColParams prm)
+{
+    const uint32_t ln = lane_id();
+    const uint64_t n_long = *prm.n_long, step = (uint64_t)gridDim.x * kBlockThreads;
+    for (uint64_t t0 = (uint64_t)blockIdx.x * kBlockThreads + (threadIdx.x & ~(kWaveSize - 1u)); t0 < n_long; t0 += step) {
+        const bool mine = t0 + ln < n_long;
+        uint4 *at_end = prm.left + (prm.left_room - 1 - (mine ? t0 + ln : t0));
+        const uint4 e = *at_end;
+        const uint32_t s = left_size(e.w, 0), m = left_size(e.w, 1), q = left_size(e.w, 2), p = left_size(e.w, 3);
+        float subsets = 1.0f;   // of s columns
+        for (uint32_t x = 0; x < q; ++x) subsets *= (float)(s - x) / (float)(x + 1);
+        const float by_cols = subsets / 64 * (float)(4 * col_words((m + 63) >> 6, s) + 8) + (float)s * 700;
+        const bool deep = prm.deep && by_cols < (float)row_estimate(m, p);
+        uint64_t shared = 0;
+        for (uint64_t todo = __ballot(mine && !deep); todo != 0; todo &= todo - 1) {
+            const uint32_t i = (uint32_t)__builtin_ctzll(todo);
+            const uint32_t n = bcast32(m, (int)i), r = bcast32(e.x, (int)i), fixed = bcast32(e.y, (int)i);
+            if (bcast32(p, (int)i) < 3) continue;
+            unsigned long long at = 0;
+            if (ln == 0) at = atomicAdd(prm.n_left + 1, (unsigned long long)n);
+            if (bcast64(at, 0) + n > prm.left_cap) continue;
+            if (ln == 0) at = atomicAdd(prm.n_left, (unsigned long long)n);
+            at = bcast64(at, 0);
+            for (uint32_t x = ln; x < n; x += kWaveSize) prm.left[at + x] = make_uint4(r, fixed, x, 0);
+            shared |= 1ull << i;
+        }
+        // (the row search takes the others where they are)
+        if (mine && !deep) at_end->w = (shared >> ln) & 1u ? kShared : 0u;
+    }
+}
+
+hipError_t launch_columns_long(const ColParams &prm, uint32_t n_blocks, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_left_long, dim3(64), dim3(kBlockThreads), 0, stream, prm);
+    if (prm.deep) hipLaunchKernelGGL((k_columns<true, true>), dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    return hipGetLastError();
+}
+
 hipError_t launch_columns(const ColParams &prm, uint32_t n_blocks, hipStream_t stream)
 {
     if (prm.n_roots == 0) return hipSuccess;
     if (!prm.units) hipLaunchKernelGGL(k_transpose, dim3(min(prm.n_roots, 4096u)), dim3(kBlockThreads), 0, stream, prm);
-    if (prm.timed) hipLaunchKernelGGL(k_columns<true>, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
-    else hipLaunchKernelGGL(k_columns<false>, dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    if (prm.timed) hipLaunchKernelGGL((k_columns<true, false>), dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
+    else hipLaunchKernelGGL((k_columns<false, false>), dim3(n_blocks), dim3(kBlockThreads), 0, stream, prm);
     return hipGetLastError();
 }
 
