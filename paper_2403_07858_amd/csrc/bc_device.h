@@ -156,12 +156,16 @@ constexpr uint32_t kQueueStride = 16;   // this many 64-bit words apart
 constexpr uint32_t kQueueWords = kQueues * kQueueStride;
 constexpr uint32_t kSlotFlag = 0x80000000u;
 
+constexpr uint32_t kShapeDegree = 32;   // neighbours past which a root's fill and spread are taken
+constexpr float kSpreadUnit = 4096.0f;
+
 // What the candidate pass finds of one root.
 struct RootOut {
     uint64_t off;           // first word of its rows in the pool (~0: no rows)
     uint32_t k;             // candidates
-    uint32_t bits;          // set bits of their rows (2^32 - 1 and more count as that; 0 from k_cand_count,
-                            // and for roots of at most kColTripleMax neighbours)
+    // of roots of more than kShapeDegree neighbours, from k_root_build (else 0):
+    uint16_t fill;          // share of the rows' bits that are set, times 65535
+    uint16_t spread;        // variance of the rows' bit counts over their mean squared, times kSpreadUnit, at most 65535
 };
 
 // Row storage of the candidate pass: each block reserves kRowChunk pool words at

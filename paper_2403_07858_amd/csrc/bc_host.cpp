@@ -1542,16 +1542,29 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
                                       : k * (250 + 6ull * wk * w1 + bcdev::row_estimate(k / 3, pA - 2));
         const uint64_t units = (uint64_t)unit_cost(pl);
         if (col_units_ok(pA, q) && bcdev::col_root_fits(du, wk) &&
-            units * (pA == 3 ? 1 : 4) < rows && (pA == 3 || q <= pA + 1 || du <= 192 || found[pl.item].bits > 100 * k))
+            units * (pA == 3 ? 1 : 4) < rows && (pA == 3 || q <= pA + 1 || du <= 192 || found[pl.item].fill / 65535.0 * du > 100))
             mode[r] = kByColumns;
-        // a dense root (bits: set bits of its rows): nothing is pruned, so the
-        // searches cost what all its subsets do, of columns or of rows
-        if (mode[r] == kByColumns && du > bcdev::kColTripleMax && fused) {
-            const double fill = (double)found[pl.item].bits / ((double)k * du);
-            if (fill > 0.35) {
-                const double by_cols = (double)bcdev::choose(du, q) / 64 * (4.0 * fill * wk + 8);
+        // A root with a fuller neighbourhood: what the searches cost where nothing
+        // is pruned is the subsets of its columns against those of its rows.
+        if (mode[r] == kByColumns && du > bcdev::kShapeDegree && fused) {
+            const double fill = found[pl.item].fill / 65535.0, spread = found[pl.item].spread / bcdev::kSpreadUnit;
+            // Rows whose lengths differ no more than chance has it (complete and
+            // random graphs; the length of a row of n bits then has variance
+            // n (1 - fill)) and that q_A has not cut off short: p_A - 2 of them share
+            // columns like chance has it too, and the rows of the last list are those
+            // that still share enough.  Measured on such graphs, by_cols is about a
+            // quarter of the time and by_rows half of it to twice.  Power-law hubs have
+            // ten times that spread, their small roots rows of 1.3 to 1.6 q_A bits.
+            const bool uniform = spread < 1.5 * (1 - fill) / (fill * du) + 0.002 && fill * du >= 1.9 * q;
+            auto by_cols = [&] { return (double)bcdev::choose(du, q) / 64 * (4.0 * fill * wk + 8); };
+            if (uniform) {
+                const double share = std::pow(fill, std::max(1.0, pA - 2.0)), var = du * share * (1 - share);
+                const double kept = 0.5 * std::erfc((q - 0.5 - du * share) / std::sqrt(2 * var + 1e-6));
+                const double by_rows = (double)k * (double)bcdev::row_estimate((uint64_t)(2 * k / 3.0 * kept), pA == 3 ? 1 : pA - 2);
+                if (by_cols() > (pA == 4 ? 0.1 : 0.25) * by_rows) mode[r] = kByRows;
+            } else if (fill > 0.35 && du > bcdev::kColTripleMax) {
                 const double by_rows = (double)k * (double)bcdev::row_estimate(2 * k / 3, pA == 3 ? 1 : pA - 2);
-                if (by_cols > 2.0 * by_rows) mode[r] = kByRows;
+                if (by_cols() > 2.0 * by_rows) mode[r] = kByRows;
             }
         }
         if (col_whole_ok(pA, q) && bcdev::col_fits(du, wk, q, col_slab)) {
@@ -1629,7 +1642,7 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
         const uint32_t du = degree_of(pl);
         double rows = pl.k / 3.0, common = du / 3.0;
         if (du > bcdev::kColTripleMax && fused) {
-            const double fill = (double)found[pl.item].bits / ((double)pl.k * du);
+            const double fill = std::max<uint32_t>(found[pl.item].fill, 1) / 65535.0;
             common = fill * du;
             // (hubs' rows overlap more than chance)
             if (std::pow(fill, (double)jb.pA - 4) * du >= jb.qA) rows = pl.k - 1.0;

@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_cand_count(const Job *jobs, c
             __syncthreads();
             k = s_k;
         }
-        if (tid == 0) out[item] = RootOut{~0ull, k, 0u};
+        if (tid == 0) out[item] = RootOut{~0ull, k, 0, 0};
         __syncthreads();
     }
     if (cur_job != 0xffffffffu) wave_flush(slots, jobs[cur_job].slot, acc, ovf, 0, 0);
@@ -755,7 +755,7 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
     __shared__ uint64_t s_leaf[kLeafLen];           // C(n, qA) below 2^64
     __shared__ uint32_t s_wsum[NW];
     __shared__ uint32_t s_listed[BIG ? 1 : kListed];  // roots for the large blocks
-    __shared__ unsigned long long s_item, s_off, s_bits;
+    __shared__ unsigned long long s_item, s_off, s_bits, s_squares;
     __shared__ uint32_t s_k, s_nt, s_flag, s_claimed;
     const Job *jobs = prm.jobs;
     Slot *slots = prm.slots;
@@ -813,6 +813,7 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
             s_off = ~0ull;
             s_claimed = 0;
             s_bits = 0;
+            s_squares = 0;
         }
         __syncthreads();
         const uint64_t item = s_item;
@@ -846,14 +847,14 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
             __syncthreads();
         }
         if (du < jb.qA || s_flag == 4) {
-            if (tid == 0) prm.out[item] = RootOut{~0ull, 0u, 0u};
+            if (tid == 0) prm.out[item] = RootOut{~0ull, 0u, 0, 0};
             __syncthreads();
             continue;
         }
         const bool one = !BIG && W1 == 1;
         const bool rows = jb.pA >= 3;
         u128 rsum = 0;       // PV: this thread's part of the root's leaves
-        uint64_t bits = 0;   // row bits of this thread's candidates
+        uint64_t bits = 0, squares = 0;   // row bits of this thread's candidates, and their squares
         // a candidate's leaf (p_A = 2)
         auto leaf = [&](uint32_t w, uint32_t c) {
             u128 x = 0;
@@ -1015,6 +1016,7 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
                     if (s_key[h] != 0u && c >= jb.qA) {
                         ++mine;
                         bits += c;
+                        squares += (uint64_t)c * c;
                         if (!rows) leaf(s_key[h] - 1u, c);
                     }
                 }
@@ -1093,6 +1095,7 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
                 if (cand) {
                     ++mine;
                     bits += c;
+                    squares += (uint64_t)c * c;
                     if (rows) atomicAdd(&s_bkt[(kv - 1u - u) >> sh], 1u);
                     else leaf(kv - 1u, c);
                 }
@@ -1132,7 +1135,7 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
             uint32_t *cnt = prm.sc.cnt + (uint64_t)blockIdx.x * prm.sc.stride;
             uint32_t *touched = prm.sc.touched + (uint64_t)blockIdx.x * prm.sc.stride;
             uint32_t *cand_g = prm.sc.cand + (uint64_t)blockIdx.x * prm.sc.stride;
-            bits = 0;
+            bits = squares = 0;
             wedges_flat<NW>(jb, ub, du, [&](uint32_t, uint32_t w) {
                 if (atomicAdd(&cnt[w], 1u) == 0u) touched[atomicAdd(&s_nt, 1u)] = w;
             });
@@ -1144,6 +1147,7 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
                 if (c >= jb.qA) {
                     const uint32_t s = atomicAdd(&s_k, 1u);
                     bits += c;
+                    squares += (uint64_t)c * c;
                     if (rows) {
                         cand_g[s] = w;
                         atomicExch(&cnt[w], kSlotFlag | s);
@@ -1188,12 +1192,25 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
                 if (lane_id() == 0 && t != 0) pv_add(jb.pv, u, t);
             }
         }
-        if (rows && du > kColTripleMax) {   // (what the plan asks of it)
+        const bool shape = rows && du > kShapeDegree;   // (what the plan asks of it)
+        if (shape) {
             bits = wave_sum_u64(bits);
-            if (lane_id() == 0 && bits) atomicAdd(&s_bits, (unsigned long long)bits);
+            squares = wave_sum_u64(squares);
+            if (lane_id() == 0 && bits) {
+                atomicAdd(&s_bits, (unsigned long long)bits);
+                atomicAdd(&s_squares, (unsigned long long)squares);
+            }
         }
         __syncthreads();
-        if (tid == 0) prm.out[item] = RootOut{build ? off : ~0ull, k, (uint32_t)min(s_bits, 0xffffffffull)};
+        if (tid == 0) {
+            RootOut o{build ? off : ~0ull, k, 0, 0};
+            if (shape && k != 0) {
+                const float mean = (float)s_bits / (float)k, sq = (float)s_squares / (float)k;
+                o.fill = (uint16_t)min(65535.0f, mean / (float)du * 65535.0f);
+                o.spread = (uint16_t)min(65535.0f, max(0.0f, sq / (mean * mean) - 1.0f) * kSpreadUnit);
+            }
+            prm.out[item] = o;
+        }
         clear_table();
         __syncthreads();
     }
