@@ -207,10 +207,11 @@ def main():
     roots = sum(st["roots"] for (_, _, _, st) in results[0])
     value = total_count / (ms_per_step / 1000)
 
-    # roofline of the enumeration kernel (the dominant one): algorithmic
-    # word-intersections (leaf pairs and child filters, from the instrumented
-    # pass) x 8 bytes per launch, over its mean launch time (HIP events on the
-    # stream it runs on), against the LDS bandwidth measured on this device
+    # roofline of the enumeration (k_transpose, k_columns and k_enumerate, the
+    # dominant part): algorithmic word-intersections (column steps, leaf pairs and
+    # child filters, from the instrumented pass) x 8 bytes a query, over its mean
+    # time (HIP events on the stream it runs on), against the LDS bandwidth
+    # measured on this device
     enum_ms = {}
     for r in results:
         for (p, q, c, st) in r:
@@ -262,7 +263,7 @@ def main():
                    "sha256": g.manifest["sha256"]},
         "root_vertices_per_s": roots / (ms_per_step / 1000),
         "per_query": per_query,
-        "roofline": {"bound": "lds", "kernel": "k_enumerate", "achieved": achieved / 1e9,
+        "roofline": {"bound": "lds", "kernel": "k_columns + k_enumerate", "achieved": achieved / 1e9,
                      "peak": peaks["lds_bytes_per_s"] / 1e9, "unit": "GB/s",
                      "frac": achieved / peaks["lds_bytes_per_s"], "traffic": traffic,
                      "traffic_unit": f"HBM bytes per k_enumerate launch of (4,4) on {TRAFFIC_WORKLOAD}",

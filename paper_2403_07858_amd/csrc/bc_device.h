@@ -297,6 +297,8 @@ hipError_t launch_degree_sum(const Job *jobs, const uint32_t *job_ids, uint32_t 
 hipError_t launch_cand_count(const Job *jobs, const uint64_t *job_root_prefix, uint32_t n_jobs,
                              uint64_t total_roots, RootScratch scratch, uint32_t n_blocks,
                              unsigned long long *queue, RootOut *out, Slot *slots, hipStream_t stream);
+// LDS of the largest block of launch_root_build.
+uint32_t root_build_lds();
 // Candidate counts and rows in one kernel; rows go to pool[out[r].off ..]
 // (bump-allocated from *pool_head, capacity pool_cap words).  n_small blocks of
 // four waves take every root and list those too large for them in retry; then

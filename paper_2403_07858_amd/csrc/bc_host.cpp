@@ -1136,9 +1136,9 @@ bc_status run_jobs_impl(const std::vector<JobSpec> &specs, const bc_opts *opts, 
     }
 
     // The fused per-root kernel (LDS counting, rows bump-allocated on the
-    // device) needs 144 KiB of LDS per block and a pool sized up front; the
+    // device) needs 135 KiB of LDS for its wide blocks and a pool sized up front; the
     // two-kernel path (count, plan, rows) is the fallback.
-    const bool fused = !two_pass && lds_per_block(device) >= 148 * 1024;
+    const bool fused = !two_pass && (uint32_t)lds_per_block(device) >= bcdev::root_build_lds();
     // Counter scratch of the candidate passes: per block, three u32 arrays over
     // the widest anchor side of any job (all zero between roots).  Blocks of
     // every candidate-pass launch are capped at rs_blocks.

@@ -1218,6 +1218,12 @@ __global__ __launch_bounds__(rb_waves(KIND) *kWaveSize, KIND == RB_SMALL ? 5 : 4
     if (cur_job != 0xffffffffu) wave_flush(slots, jb.slot, acc, ovf, 0, 0);
 }
 
+uint32_t root_build_lds()
+{
+    // a wide block: keys, rows, row indices, rank intervals, leaf values, and what is single
+    return kHashSlots * 4 + kWideRowBuf * 8 + kHashSlots * 4 + rb_waves(RB_WIDE) * kWaveSize * 4 + kLeafLen * 8 + 1024;
+}
+
 template <RootBlock KIND>
 static void run_root_build(const RootParams &p, uint32_t n_blocks, bool per_vertex, hipStream_t stream)
 {
@@ -2774,7 +2780,9 @@ typedef uint64_t v2u64 __attribute__((ext_vector_type(2)));
 template <int NC>
 using col_ptr = std::conditional_t<(NC < 16), __attribute__((address_space(3))) const v2u64 *, const v2u64 *>;
 
-// n (n - 1) ... (n - P + 1), n <= 64 kColWords = 2560.
+// n (n - 1) ... (n - P + 1) for n up to 64 NC, and up to 64 kColRootWords = 4096
+// candidates of a root's whole columns (NC as it is by default).
+static_assert(64 * kColRootWords * (64 * kColRootWords - 1) < 1u << 24, "the products of falling fit 24 bits");
 template <int P, int NC = kColWords>
 __device__ __forceinline__ uint64_t falling(uint32_t n)
 {
@@ -2811,8 +2819,15 @@ __device__ __forceinline__ uint32_t col_count(const uint64_t (&v)[NC], col_ptr<N
 }
 
 // Adds falling<P>(candidates of v and D more columns) over the D-subsets of
-// columns k0 .. s-1.  One loop's sum stays below 2^64: falling<5>(1024) <
-// 2^50, and at most C(126, 2) terms are added between two folds.
+// columns k0 .. s-1.  One loop's sum stays below 2^64 (col_sum_fits): between two
+// folds a search adds at most kColMax terms with one loop, C(kColMax, 2) with more.
+constexpr bool col_sum_fits(uint32_t nc, uint32_t loops, uint32_t p)
+{
+    u128 most = loops == 1 ? kColMax : choose(kColMax, 2);
+    for (uint32_t x = 0; x < p; ++x) most *= 64 * nc - x;
+    return most >> 64 == 0;
+}
+static_assert(kColMax * (uint64_t)(64 * kColWords) * (64 * kColWords - 1) < 1ull << 32, "32-bit sums of falling<2>");
 template <int NC, int D, int P>
 __device__ __forceinline__ void col_level(const uint64_t (&v)[NC], col_ptr<NC> buf, uint32_t k0, uint32_t s,
                                           uint64_t &sum)
@@ -2850,6 +2865,7 @@ template <int NC, int D, int P>
 __device__ __forceinline__ bool col_search(col_ptr<NC> buf, uint32_t s, uint32_t R, uint32_t n_tup, uint64_t deadline,
                                            Acc &acc)
 {
+    static_assert(col_sum_fits(NC, D, P), "sums between two folds");
     const uint32_t ln = lane_id();
     constexpr uint32_t st = col_stride(NC) / 2;
     for (uint32_t base = 0; base < n_tup; base += kWaveSize) {
