@@ -2725,7 +2725,9 @@ hipError_t launch_enumerate_left(const EnumParams &prm, uint32_t n_blocks, hipSt
 // remaining columns run through wave-uniform loops, their words broadcast from
 // LDS.  In that order the lanes of a wave share almost the same last column,
 // so the loops, which start behind it, waste few lanes.  What bounds it is the
-// VALU: two operations (AND, popcount with add) per 32 candidates and tuple.
+// VALU: two operations (AND, popcount with add) per 32 candidates and tuple
+// (counters: 91 % of the issue slots on 1.2M edges (5,5); 64 % on 2M (4,4), whose
+// units are short).
 // Whole counts when it came, against rows alone, power-law graphs: 1.2M edges
 // (5,5) 48 against 989 ms, 300k (6,6) 43 against 445 ms, 2M (4,4) 26 against 86,
 // (6,4) 38 against 47, 5M (3,3) 65 against 89 (43, 22, 21, 33 and 47 with the
